@@ -70,100 +70,208 @@ __global__ void k_symmetrize(int n, double* __restrict__ A) {
 // ---------------------------------------------------- Gauss-Jordan inverse
 
 constexpr int GJ_NB = GJ_BLOCK;
+constexpr int GJ_TILE = 64;            // update tile
+static_assert(GJ_NB == 32, "the thread maps below are written for 32 x 32 pivot blocks");
 
-// Invert the nb x nb diagonal block at k0 in LDS (Gauss-Jordan, no
-// pivoting); Dinv -> dinv; flag on a non-positive or non-finite pivot.
-__global__ __launch_bounds__(256) void k_gj_pivot(int n, int k0, int nb, const double* __restrict__ A,
-                                                  double* __restrict__ dinv, int* __restrict__ flag) {
-  __shared__ double D[GJ_NB][GJ_NB + 1];
-  __shared__ double prow[GJ_NB], pcol[GJ_NB];
-  __shared__ double piv;
-  for (int t = threadIdx.x; t < nb * nb; t += blockDim.x) {
-    int r = t / nb, c = t % nb;
-    D[r][c] = A[(size_t)(k0 + r) * n + k0 + c];
-  }
+typedef double gj_double4 __attribute__((ext_vector_type(4)));
+
+// Scratch of the pivot inversion: the pivot row and column of the current
+// and the next elimination step.
+struct GJPivotLds {
+  double prow[2][GJ_NB], pcol[2][GJ_NB];
+};
+
+// Invert an nb x nb pivot block (Gauss-Jordan, no pivoting) held four
+// consecutive elements of a row per thread (v, row threadIdx.x / 8): inverse
+// to dinv, flag on a non-positive or non-finite pivot.  256 threads.
+// Bound by the latency of its nb dependent steps (a reciprocal, two LDS
+// reads, a barrier): the elements stay in registers and the next step's row
+// and column go to the other LDS buffer, so a step has one barrier instead
+// of three and no pass over the block in LDS.
+__device__ __forceinline__ void gj_invert_block(double v[4], int nb, double* __restrict__ dinv, int* __restrict__ flag,
+                                                GJPivotLds& l) {
+  const int r = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * 4;
+  if (r == 0)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) l.prow[0][c0 + k] = v[k];
+  if (c0 == 0) l.pcol[0][r] = v[0];
   __syncthreads();
-  for (int p = 0; p < nb; ++p) {
-    if (threadIdx.x == 0) {
-      piv = D[p][p];
-      if (!(piv > 0.0) || !isfinite(piv)) { atomicOr(flag, 1); piv = 1.0; }
+  // (four steps per trip: the column to publish is then a fixed element)
+  for (int p0 = 0; p0 < nb; p0 += 4) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int p = p0 + q;
+      if (p >= nb) break;
+      const int buf = q & 1;
+      double piv = l.prow[buf][p];
+      if (!(piv > 0.0) || !isfinite(piv)) {
+        if (threadIdx.x == 0) atomicOr(flag, 1);
+        piv = 1.0;
+      }
+      const double ip = 1.0 / piv;
+      const double pc = l.pcol[buf][r];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        // (selected, not branched: 16 short divergent paths a step cost more than the step)
+        const int c = c0 + k;
+        const double pr = l.prow[buf][c];
+        const double in_row = c == p ? ip : pr * ip;
+        const double in_col = -pc * ip, rest = v[k] - pc * pr * ip;
+        const double off_row = c == p ? in_col : rest;
+        v[k] = r == p ? in_row : off_row;
+      }
+      if (r == p + 1)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) l.prow[buf ^ 1][c0 + k] = v[k];
+      if (c0 == (q < 3 ? p0 : p0 + 4)) l.pcol[buf ^ 1][r] = v[(q + 1) & 3];
+      __syncthreads();
     }
-    __syncthreads();
-    double ip = 1.0 / piv;
-    for (int t = threadIdx.x; t < nb; t += blockDim.x) { prow[t] = D[p][t]; pcol[t] = D[t][p]; }
-    __syncthreads();
-    for (int t = threadIdx.x; t < nb * nb; t += blockDim.x) {
-      int r = t / nb, c = t % nb;
-      double v;
-      if (r == p && c == p) v = ip;
-      else if (r == p) v = prow[c] * ip;
-      else if (c == p) v = -pcol[r] * ip;
-      else v = D[r][c] - pcol[r] * prow[c] * ip;
-      D[r][c] = v;
-    }
-    __syncthreads();
   }
-  for (int t = threadIdx.x; t < nb * nb; t += blockDim.x) {
-    int r = t / nb, c = t % nb;
-    dinv[r * nb + c] = D[r][c];
-  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    if (r < nb && c0 + k < nb) dinv[r * nb + c0 + k] = v[k];
+}
+
+// The first pivot block (the later ones are inverted by k_gj_update).
+__global__ __launch_bounds__(256) void k_gj_pivot(int n, int nb, const double* __restrict__ A,
+                                                  double* __restrict__ dinv, int* __restrict__ flag) {
+  __shared__ GJPivotLds l;
+  const int r = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * 4;
+  double v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = (r < nb && c0 + k < nb) ? A[(size_t)r * n + c0 + k] : 0.0;
+  gj_invert_block(v, nb, dinv, flag, l);
 }
 
 // Panels: pc[i][t] = A[i][k0+t] (column block, i outside the pivot rows is
 // what the update needs) and rx[t][j] = (Dinv A[k0.., j]) for j outside the
-// block, Dinv[t][j-k0] inside it.
+// block, Dinv[t][j-k0] inside it.  A workgroup takes 32 columns j, thread
+// (j, g) the four rows t = g, g + 8, g + 16, g + 24 (four independent
+// chains).  Latency of one load and 32 dependent FMAs; a thread per column
+// with the whole 32 x 32 product took 152 us at n = 1760 (7 workgroups).
+constexpr int GJ_PCOLS = 32;
 __global__ __launch_bounds__(256) void k_gj_panels(int n, int k0, int nb, const double* __restrict__ A,
                                                    const double* __restrict__ dinv, double* __restrict__ pc,
                                                    double* __restrict__ rx) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+  __shared__ double Ds[GJ_NB][GJ_NB + 1], Cs[GJ_NB][GJ_PCOLS + 1];
+  const int j0 = blockIdx.x * GJ_PCOLS;
+  for (int e = threadIdx.x; e < GJ_NB * GJ_PCOLS; e += 256) {
+    const int t = e / GJ_PCOLS, c = e % GJ_PCOLS;
+    Cs[t][c] = (t < nb && j0 + c < n) ? A[(size_t)(k0 + t) * n + j0 + c] : 0.0;
+    // the same thread map transposed: column block row j0 + t, entry c
+    if (j0 + t < n && c < nb) pc[(size_t)(j0 + t) * nb + c] = A[(size_t)(j0 + t) * n + k0 + c];
+    Ds[t][c] = (t < nb && c < nb) ? dinv[t * nb + c] : 0.0;
+  }
+  __syncthreads();
+  const int c = threadIdx.x % GJ_PCOLS, g = threadIdx.x / GJ_PCOLS, j = j0 + c;
   if (j >= n) return;
-  for (int t = 0; t < nb; ++t) pc[(size_t)j * nb + t] = A[(size_t)j * n + k0 + t];
   if (j >= k0 && j < k0 + nb) {
-    for (int t = 0; t < nb; ++t) rx[(size_t)t * n + j] = dinv[t * nb + (j - k0)];
+    for (int t = g; t < nb; t += 8) rx[(size_t)t * n + j] = Ds[t][j - k0];
   } else {
-    double col[GJ_NB];
-    for (int t = 0; t < nb; ++t) col[t] = A[(size_t)(k0 + t) * n + j];
-    for (int t = 0; t < nb; ++t) {
-      double s = 0.0;
-      for (int u = 0; u < nb; ++u) s += dinv[t * nb + u] * col[u];
-      rx[(size_t)t * n + j] = s;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int u = 0; u < nb; ++u) {
+      const double a = Cs[u][c];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[k] = fma(Ds[g + 8 * k][u], a, s[k]);
     }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (g + 8 * k < nb) rx[(size_t)(g + 8 * k) * n + j] = s[k];
   }
 }
 
-// A[i][j] = rx[i-k0][j] for i in the block, else (j in block ? 0 : A[i][j]) - sum_t pc[i][t] rx[t][j]
-__global__ __launch_bounds__(256) void k_gj_update(int n, int k0, int nb, double* __restrict__ A,
-                                                   const double* __restrict__ pc, const double* __restrict__ rx) {
-  __shared__ double Ps[64][GJ_NB + 1];
-  __shared__ double Rs[GJ_NB][64 + 1];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-  for (int t = threadIdx.x; t < 64 * nb; t += 256) {
-    int r = t / nb, c = t % nb;
-    Ps[r][c] = (i0 + r < n) ? pc[(size_t)(i0 + r) * nb + c] : 0.0;
+// A[i][j] = rx[i-k0][j] for i in the block, else (j in block ? 0 : A[i][j]) - sum_t pc[i][t] rx[t][j].
+// A 64 x 64 tile per workgroup on v_mfma_f64_16x16x4 (the tiling and lane
+// layout of k_gemm.hip).  Workgroup 0 takes the next pivot block alone (the
+// tile around it leaves it out) and inverts it into dinv, beside the other
+// tiles' work: a step is two launches, and the pivot's latency is hidden by
+// the update.
+__global__ __launch_bounds__(256) void k_gj_update(int n, int k0, int nb, int k1, int nb1, double* __restrict__ A,
+                                                   const double* __restrict__ pc, const double* __restrict__ rx,
+                                                   double* __restrict__ dinv, int* __restrict__ flag) {
+  // (row strides of 72 and 160 dwords: the operand reads meet every bank twice)
+  __shared__ double Ps[GJ_TILE][GJ_NB + 4];
+  __shared__ double Rs[GJ_NB][GJ_TILE + 16];
+  if (blockIdx.x == 0) {
+    // rows and columns k1 .. k1 + nb1 - 1, four elements of a row per thread
+    // (all beyond the pivot block, so the update's general case)
+    __shared__ GJPivotLds l;
+    if (nb1 <= 0) return;
+    const int r = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * 4;
+    double v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = (r < nb1 && c0 + k < nb1) ? A[(size_t)(k1 + r) * n + k1 + c0 + k] : 0.0;
+    for (int e = threadIdx.x; e < GJ_NB * GJ_NB; e += 256) {
+      const int a = e / GJ_NB, b = e % GJ_NB;
+      Ps[a][b] = (a < nb1 && b < nb) ? pc[(size_t)(k1 + a) * nb + b] : 0.0;
+      Rs[a][b] = (a < nb && b < nb1) ? rx[(size_t)a * n + k1 + b] : 0.0;
+    }
+    __syncthreads();
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+    for (int t = 0; t < nb; ++t) {
+      const double a = Ps[r][t];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[k] = fma(a, Rs[t][c0 + k], s[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = v[k] - s[k];
+      if (r < nb1 && c0 + k < nb1) A[(size_t)(k1 + r) * n + k1 + c0 + k] = v[k];
+    }
+    gj_invert_block(v, nb1, dinv, flag, l);
+    return;
   }
-  for (int t = threadIdx.x; t < nb * 64; t += 256) {
-    int r = t / 64, c = t % 64;
-    Rs[r][c] = (j0 + c < n) ? rx[(size_t)r * n + j0 + c] : 0.0;
+  const int nt = (n + GJ_TILE - 1) / GJ_TILE, tile = blockIdx.x - 1;
+  const int i0 = (tile / nt) * GJ_TILE, j0 = (tile % nt) * GJ_TILE;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32, lr = lane & 15, kq = lane >> 4;
+  // the elements of this lane (MFMA result layout), in flight during staging
+  double base[2][2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int gi = i0 + wm + 16 * a + 4 * t + kq, gj = j0 + wn + 16 * b + lr;
+        base[a][b][t] = (gi < n && gj < n && !(gj >= k0 && gj < k0 + nb)) ? A[(size_t)gi * n + gj] : 0.0;
+      }
+  for (int t = threadIdx.x; t < GJ_TILE * GJ_NB; t += 256) {
+    const int r = t / GJ_NB, c = t % GJ_NB;
+    Ps[r][c] = (i0 + r < n && c < nb) ? pc[(size_t)(i0 + r) * nb + c] : 0.0;
+    const int tr = t / GJ_TILE, tc = t % GJ_TILE;
+    Rs[tr][tc] = (j0 + tc < n && tr < nb) ? rx[(size_t)tr * n + j0 + tc] : 0.0;
   }
   __syncthreads();
+  gj_double4 acc[2][2];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      int li = ty + 16 * u, lj = tx + 16 * v;
-      int gi = i0 + li, gj = j0 + lj;
-      if (gi >= n || gj >= n) continue;
-      double* a = A + (size_t)gi * n + gj;
-      if (gi >= k0 && gi < k0 + nb) {
-        *a = Rs[gi - k0][lj];
-      } else {
-        double s = 0.0;
-        for (int t = 0; t < nb; ++t) s = fma(Ps[li][t], Rs[t][lj], s);
-        double base = (gj >= k0 && gj < k0 + nb) ? 0.0 : *a;
-        *a = base - s;
+    for (int b = 0; b < 2; ++b) acc[a][b] = gj_double4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int kk = 0; kk < GJ_NB; kk += 4) {
+    double av[2], bv[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) av[a] = Ps[wm + 16 * a + lr][kk + kq];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) bv[b] = Rs[kk + kq][wn + 16 * b + lr];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int gi = i0 + wm + 16 * a + 4 * t + kq, lj = wn + 16 * b + lr, gj = j0 + lj;
+        const bool next = gi >= k1 && gi < k1 + nb1 && gj >= k1 && gj < k1 + nb1;   // workgroup 0's
+        if (gi < n && gj < n && !next)
+          A[(size_t)gi * n + gj] = (gi >= k0 && gi < k0 + nb) ? Rs[gi - k0][lj] : base[a][b][t] - acc[a][b][t];
       }
-    }
 }
 
 // ------------------------------------------------------------ projections
@@ -367,11 +475,13 @@ void launch_symmetrize(hipStream_t s, int n, double* A) {
   hipLaunchKernelGGL(k_symmetrize, dim3((n + 15) / 16, (n + 15) / 16), dim3(256), 0, s, n, A);
 }
 void launch_gj_invert(hipStream_t s, int n, double* A, double* dinv, double* pc, double* rx, int* flag) {
+  const int nt = (n + GJ_TILE - 1) / GJ_TILE;
+  hipLaunchKernelGGL(k_gj_pivot, dim3(1), dim3(256), 0, s, n, n < GJ_NB ? n : GJ_NB, A, dinv, flag);
   for (int k0 = 0; k0 < n; k0 += GJ_NB) {
-    int nb = n - k0 < GJ_NB ? n - k0 : GJ_NB;
-    hipLaunchKernelGGL(k_gj_pivot, dim3(1), dim3(256), 0, s, n, k0, nb, A, dinv, flag);
-    hipLaunchKernelGGL(k_gj_panels, dim3((n + 255) / 256), dim3(256), 0, s, n, k0, nb, A, dinv, pc, rx);
-    hipLaunchKernelGGL(k_gj_update, dim3((n + 63) / 64, (n + 63) / 64), dim3(256), 0, s, n, k0, nb, A, pc, rx);
+    const int nb = n - k0 < GJ_NB ? n - k0 : GJ_NB;
+    const int k1 = k0 + nb, nb1 = n - k1 < GJ_NB ? n - k1 : GJ_NB;
+    hipLaunchKernelGGL(k_gj_panels, dim3((n + GJ_PCOLS - 1) / GJ_PCOLS), dim3(256), 0, s, n, k0, nb, A, dinv, pc, rx);
+    hipLaunchKernelGGL(k_gj_update, dim3(1 + nt * nt), dim3(256), 0, s, n, k0, nb, k1, nb1, A, pc, rx, dinv, flag);
   }
 }
 void launch_matvec(hipStream_t s, int n, const double* Mx, const double* x, double* y) {
