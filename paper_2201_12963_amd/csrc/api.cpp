@@ -104,6 +104,7 @@ struct cpm_ctx {
 
   // ---- potential profile: distinct electrode heights and the histogram scratch
   int n_heights = 0;
+  std::vector<int> height_of;              // height index of every electrode atom (host)
   int* d_height_of = nullptr;
   double* d_heights = nullptr;
   double* d_prof = nullptr;
@@ -973,6 +974,89 @@ int tune_batch_chunk(cpm_ctx* c, int n_frames, Run run) {
   return rc;
 }
 
+// The k-space part of A, added to d_A; the device buffers it allocates go to
+// temps (the caller frees them once the stream is idle).
+//
+// Two forms of the same sum.  Flat electrodes (few distinct heights) take the
+// separable one (k_gemm.hip), whose inner dimension is the x-y parts of the
+// k-vectors, ~130 times fewer than the k-vectors of the paper cells: it pays
+// while a height has ELAST_MIN_ATOMS atoms or more on average (its lists are
+// padded to 64 atoms per height, at most 4 times the atoms; the product form
+// costs more than that in every cell whose z mesh the method uses).  Other
+// electrodes take the product form, A += C C^T over chunks of k-vectors; so
+// do mixed contexts, whose FP32 and bf16 copies of S are roundings of it and
+// move by whole units in the last place where S moves by its own rounding.
+constexpr int ELAST_MIN_ATOMS = 16;
+int enqueue_elastance_kspace(cpm_ctx* c, std::vector<void*>& temps) {
+  const int n = c->n_elec;
+  hipStream_t s = c->stream;
+  const double vol = c->box[0] * c->box[1] * c->box[2];
+  auto up = [&](auto** p, const auto& h) -> int { TRY(upload(c, p, h)); temps.push_back(*p); return CPM_OK; };
+  auto get = [&](auto** p, size_t m) -> int { TRY(dalloc(c, p, m)); temps.push_back(*p); return CPM_OK; };
+  if (c->precision != CPM_MIXED && (long long)c->n_heights * ELAST_MIN_ATOMS <= n) {
+    // x-y parts of the half space (0 first), with the largest |n_z| of each
+    // (the product form's vectors: the same expressions and bounds)
+    const double kc2 = c->kcut_b * c->kcut_b;
+    std::vector<double> kx, ky, kxy;
+    std::vector<int> nz;
+    int nmax[3];
+    for (int k = 0; k < 3; ++k) nmax[k] = (int)std::floor(c->kcut_b * c->box[k] / (2 * M_PI));
+    for (int a = 0; a <= nmax[0]; ++a)
+      for (int b = a == 0 ? 0 : -nmax[1]; b <= nmax[1]; ++b) {
+        const double k0 = 2 * M_PI * a / c->box[0], k1 = 2 * M_PI * b / c->box[1];
+        int m = -1;
+        for (int z = 0; z <= nmax[2]; ++z) {
+          const double k2 = 2 * M_PI * z / c->box[2];
+          if (k0 * k0 + k1 * k1 + k2 * k2 > kc2) break;
+          m = z;
+        }
+        if (m < 0) continue;
+        kx.push_back(k0); ky.push_back(k1);
+        nz.push_back(m);
+      }
+    const int nk = (int)nz.size(), nkp = (nk + ELAST_SLAB - 1) / ELAST_SLAB * ELAST_SLAB, H = c->n_heights;
+    kxy = kx;
+    kxy.insert(kxy.end(), ky.begin(), ky.end());
+    // the atoms height by height, each height padded to whole tiles
+    std::vector<std::vector<int>> of(H);
+    for (int i = 0; i < n; ++i) of[c->height_of[i]].push_back(i);
+    std::vector<int> atoms, tile_h;
+    for (int h = 0; h < H; ++h) {
+      for (size_t k = 0; k < of[h].size(); ++k) {
+        if (k % ELAST_TILE == 0) tile_h.push_back(h);
+        atoms.push_back(of[h][k]);
+      }
+      while (atoms.size() % ELAST_TILE) atoms.push_back(-1);
+    }
+    double *d_kxy, *d_W, *d_P;
+    int *d_nz, *d_atoms, *d_th;
+    TRY(up(&d_kxy, kxy)); TRY(up(&d_nz, nz)); TRY(up(&d_atoms, atoms)); TRY(up(&d_th, tile_h));
+    TRY(get(&d_W, (size_t)H * H * nkp)); TRY(get(&d_P, atoms.size() * 2 * nkp));
+    launch_elastance_kspace(s, n, (int)atoms.size(), d_atoms, d_th, H, c->d_heights, nk, nkp, d_kxy, d_nz, 2 * M_PI / c->box[2],
+                            1.0 / (4.0 * c->alpha_b * c->alpha_b), 2.0 * KE * 4.0 * M_PI / vol, c->d_ex, c->d_ey, d_W,
+                            d_P, c->d_A);
+    return CPM_OK;
+  }
+  std::vector<double> kx, ky, kz;
+  half_kvectors(c->box, c->kcut_b, kx, ky, kz);
+  const int nk = (int)kx.size();
+  std::vector<double> kv(3 * (size_t)nk), sk(nk);
+  for (int k = 0; k < nk; ++k) {
+    kv[k] = kx[k]; kv[nk + k] = ky[k]; kv[2 * nk + k] = kz[k];
+    double k2 = kx[k] * kx[k] + ky[k] * ky[k] + kz[k] * kz[k];
+    sk[k] = std::sqrt(2 * KE * kweight_host(k2, c->alpha_b, vol));
+  }
+  double *d_kv = nullptr, *d_sk = nullptr, *d_C = nullptr;
+  const int chunk = std::max(64, std::min(nk, (int)((size_t)(256u << 20) / (16 * (size_t)n))));
+  TRY(up(&d_kv, kv)); TRY(up(&d_sk, sk)); TRY(get(&d_C, (size_t)n * 2 * chunk));
+  for (int k0 = 0; k0 < nk; k0 += chunk) {
+    int nkc = std::min(chunk, nk - k0);
+    launch_phase_matrix(s, n, nkc, k0, nk, d_kv, d_sk, c->d_ex, c->d_ey, c->d_ez, d_C);
+    launch_syrk_nt(s, n, 2 * nkc, 1.0, d_C, 2 * nkc, 1.0, c->d_A, n);
+  }
+  return CPM_OK;
+}
+
 // z.(S c) for the slab's batched dV sweep (host copy of S c; the stream is idle)
 int slab_zsc(cpm_ctx* c) {
   if (c->geometry != CPM_SLAB) return CPM_OK;
@@ -1227,6 +1311,7 @@ int cpm_create(const cpm_desc* d, void* hip_stream, cpm_ctx** out) {
     hs.erase(std::unique(hs.begin(), hs.end()), hs.end());
     for (int i = 0; i < ne; ++i) hof[i] = (int)(std::lower_bound(hs.begin(), hs.end(), ze[i]) - hs.begin());
     c->n_heights = (int)hs.size();
+    c->height_of = hof;
     if ((r = upload(c, &c->d_height_of, hof)) || (r = upload(c, &c->d_heights, hs))) return bad(r);
   }
   // electrode atoms in reach of every cell: the stencil cells' ranges of the
@@ -1460,27 +1545,8 @@ int cpm_build_elastance(cpm_ctx* c) {
   // real space and self term
   const double self_term = (std::sqrt(2.0) * c->eta - 2.0 * c->alpha_b) / std::sqrt(M_PI);
   launch_elastance_real(s, n, c->d_ex, c->d_ey, c->d_ez, c->cell_b, c->alpha_b, c->eta, c->rcut_b, self_term, c->d_A);
-  // k space: A += C C^T over chunks of k-vectors
-  std::vector<double> kx, ky, kz;
-  half_kvectors(c->box, c->kcut_b, kx, ky, kz);
-  const int nk = (int)kx.size();
-  const double vol = c->box[0] * c->box[1] * c->box[2];
-  std::vector<double> kv(3 * (size_t)nk), sk(nk);
-  for (int k = 0; k < nk; ++k) {
-    kv[k] = kx[k]; kv[nk + k] = ky[k]; kv[2 * nk + k] = kz[k];
-    double k2 = kx[k] * kx[k] + ky[k] * ky[k] + kz[k] * kz[k];
-    sk[k] = std::sqrt(2 * KE * kweight_host(k2, c->alpha_b, vol));
-  }
-  double *d_kv = nullptr, *d_sk = nullptr, *d_C = nullptr, *d_work = nullptr;
-  int r;
-  const int chunk = std::max(64, std::min(nk, (int)((size_t)(256u << 20) / (16 * (size_t)n))));
-  if ((r = upload(c, &d_kv, kv)) || (r = upload(c, &d_sk, sk)) || (r = dalloc(c, &d_C, (size_t)n * 2 * chunk)))
-    return r;
-  for (int k0 = 0; k0 < nk; k0 += chunk) {
-    int nkc = std::min(chunk, nk - k0);
-    launch_phase_matrix(s, n, nkc, k0, nk, d_kv, d_sk, c->d_ex, c->d_ey, c->d_ez, d_C);
-    launch_gemm_nt(s, n, n, 2 * nkc, 1.0, d_C, 2 * nkc, d_C, 2 * nkc, 1.0, c->d_A, n);
-  }
+  std::vector<void*> temps;
+  TRY(enqueue_elastance_kspace(c, temps));
   launch_symmetrize(s, n, c->d_A);
   if (c->geometry == CPM_SLAB) {
     // the dipole correction's electrode block: A += kappa z z^T (a rank-one
@@ -1493,6 +1559,7 @@ int cpm_build_elastance(cpm_ctx* c) {
   // inverse (in d_S), projections
   HIP_TRY(c, hipMemcpyAsync(c->d_S, c->d_A, (size_t)n * n * sizeof(double), hipMemcpyDeviceToDevice, s));
   double *dinv, *pc, *rx, *u;
+  int r;
   if ((r = dalloc(c, &dinv, GJ_BLOCK * GJ_BLOCK)) || (r = dalloc(c, &pc, (size_t)n * GJ_BLOCK)) ||
       (r = dalloc(c, &rx, (size_t)n * GJ_BLOCK)) || (r = dalloc(c, &u, n)))
     return r;
@@ -1521,7 +1588,8 @@ int cpm_build_elastance(cpm_ctx* c) {
   HIP_TRY(c, hipStreamSynchronize(s));
   TRY(slab_zsc(c));
   // the chunk buffers are released now (they are large)
-  for (void* p : {(void*)d_kv, (void*)d_sk, (void*)d_C, (void*)dinv, (void*)pc, (void*)rx, (void*)u}) {
+  for (void* p : {(void*)dinv, (void*)pc, (void*)rx, (void*)u}) temps.push_back(p);
+  for (void* p : temps) {
     (void)hipFree(p);
     c->allocs.erase(std::remove(c->allocs.begin(), c->allocs.end(), p), c->allocs.end());
   }

@@ -30,14 +30,29 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
+static_assert(ELAST_TILE == 64 && ELAST_SLAB == 16, "the padded lists match the tiles here");
 constexpr int G64_TILE = 64, G64_K = 16, G64_LD = G64_K + 1;   // LDS rows padded against bank conflicts
 
+// (row, column) of tile t of a lower triangle listed row by row
+__device__ __forceinline__ void tri_tile(int t, int& row, int& col) {
+  row = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
+  while (row * (row + 1) / 2 > t) --row;                 // the estimate may be one off
+  while ((row + 1) * (row + 2) / 2 <= t) ++row;
+  col = t - row * (row + 1) / 2;
+}
+
+// SYM: A and B are the same matrix, so D's product part is symmetric: only
+// the tiles of the lower triangle are computed (blockIdx.x lists them) and
+// each is added at both places, half the matrix work.
+template <bool SYM>
 __global__ __launch_bounds__(256) void k_gemm_f64_mfma(int M, int N, int K, double alpha, const double* __restrict__ A,
                                                        int lda, const double* __restrict__ B, int ldb, double beta,
                                                        double* __restrict__ D, int ldd) {
   __shared__ double sA[2][G64_TILE * G64_LD], sB[2][G64_TILE * G64_LD];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m0 = blockIdx.y * G64_TILE, n0 = blockIdx.x * G64_TILE;
+  int tm = blockIdx.y, tn = blockIdx.x;
+  if (SYM) tri_tile(blockIdx.x, tm, tn);
+  const int m0 = tm * G64_TILE, n0 = tn * G64_TILE;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   // loader: thread t moves 4 consecutive k of row t / 4 of each operand
   const int lrow = threadIdx.x >> 2, lk = (threadIdx.x & 3) * 4;
@@ -116,7 +131,145 @@ __global__ __launch_bounds__(256) void k_gemm_f64_mfma(int M, int N, int K, doub
         if (gm < M && gn < N) {
           double* d = D + (size_t)gm * ldd + gn;
           *d = (beta == 0.0 ? 0.0 : beta * *d) + alpha * acc[a][b][t];
+          if (SYM && tm != tn) {
+            d = D + (size_t)gn * ldd + gm;
+            *d = (beta == 0.0 ? 0.0 : beta * *d) + alpha * acc[a][b][t];
+          }
         }
+      }
+}
+
+// ------------------------------------------------ elastance, k space by heights
+
+// For electrode atoms that share a few heights z_h (flat sheets) the k-space
+// part of A is separable: with the k-vectors grouped by their x-y part,
+//   sum_k 2 k_e w(k) cos(k.(r_i - r_j))
+//     = sum_kxy W[h_i][h_j][kxy] (c_i c_j + s_i s_j),
+// c, s the cos and sin of kxy.r, W the sum over k_z of 2 k_e w cos(k_z (z_h -
+// z_h')) (k and -k of one kxy paired, so the sin terms of z cancel).  The
+// inner dimension falls from twice the k-vectors to twice the x-y parts: at
+// the doubled paper cell (n = 1760) 2 x 36.6 k to 2 x 288, and the build's
+// k-space part from 12.4 ms of FP64 matrix products to ~0.1 ms.
+
+// W[h][h'][c]; kxy[2][nk], nz[c]: the largest |n_z| with |k| <= kcut of that
+// x-y part; entries nk .. nkp are zero.  The first x-y part is 0, whose
+// half space holds n_z > 0 only.
+// Sixteen lanes share an entry's k_z (an exp and a cos each, ~100 of them in
+// a chain cost 34 us at the doubled paper cell with one lane per entry).
+__global__ __launch_bounds__(256) void k_height_weights(int H, int nk, int nkp, const double* __restrict__ heights,
+                                                        const double* __restrict__ kxy, const int* __restrict__ nz,
+                                                        double dkz, double inv4a2, double scale,
+                                                        double* __restrict__ W) {
+  const int c = blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4);     // nkp is a multiple of 16
+  const int pair = blockIdx.y;
+  double acc = 0.0, k2 = 0.0;
+  if (c < nk) {
+    const double dz = heights[pair / H] - heights[pair % H];
+    k2 = kxy[c] * kxy[c] + kxy[nk + c] * kxy[nk + c];
+    for (int m = 1 + (threadIdx.x & 15); m <= nz[c]; m += 16) {
+      const double kz = dkz * m, kk = k2 + kz * kz;
+      acc += exp(-kk * inv4a2) / kk * cos(kz * dz);
+    }
+  }
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+  if (c > 0 && c < nk) acc = 2.0 * acc + exp(-k2 * inv4a2) / k2;
+  if ((threadIdx.x & 15) == 0) W[(size_t)pair * nkp + c] = scale * acc;
+}
+
+// P[a][c] = cos(kxy_c . r_a), P[a][nkp + c] = sin, for the atoms listed by
+// height (atom < 0: padding, zeros)
+__global__ __launch_bounds__(256) void k_phase_xy(int nk, int nkp, const int* __restrict__ atoms,
+                                                  const double* __restrict__ kxy, const double* __restrict__ ex,
+                                                  const double* __restrict__ ey, double* __restrict__ P) {
+  const int c = blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= nkp) return;
+  const int a = atoms[blockIdx.y];
+  double s = 0.0, co = 0.0;
+  if (a >= 0 && c < nk) sincos(kxy[c] * ex[a] + kxy[nk + c] * ey[a], &s, &co);
+  double* row = P + (size_t)blockIdx.y * 2 * nkp;
+  row[c] = co;
+  row[nkp + c] = s;
+}
+
+// A[i][j] += sum_c W[h_i][h_j][c] (c_i c_j + s_i s_j) over the tiles of the
+// lower triangle of the height-sorted atom list (64 atoms of one height per
+// tile, so W is one vector per tile), added at both places; MFMA tiling and
+// double buffering as in k_gemm_f64_mfma, W applied to the row operand as it
+// is staged.
+__global__ __launch_bounds__(256) void k_elastance_kspace(int n, int H, int nkp, const int* __restrict__ atoms,
+                                                          const int* __restrict__ tile_h,
+                                                          const double* __restrict__ P, const double* __restrict__ W,
+                                                          double* __restrict__ A) {
+  __shared__ double sA[2][G64_TILE * G64_LD], sB[2][G64_TILE * G64_LD];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int tm, tn;
+  tri_tile(blockIdx.x, tm, tn);
+  const int m0 = tm * G64_TILE, n0 = tn * G64_TILE;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const int lrow = threadIdx.x >> 2, lk = (threadIdx.x & 3) * 4;
+  const double* pa0 = P + (size_t)(m0 + lrow) * 2 * nkp + lk;
+  const double* pb0 = P + (size_t)(n0 + lrow) * 2 * nkp + lk;
+  const double* w0 = W + (size_t)(tile_h[tm] * H + tile_h[tn]) * nkp + lk;
+  double2 ra[2], rb[2], rw[2];
+  auto load = [&](int k0) {
+    const int c0 = k0 < nkp ? k0 : k0 - nkp;             // nkp is a multiple of the slab
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      ra[t] = *reinterpret_cast<const double2*>(pa0 + k0 + 2 * t);
+      rb[t] = *reinterpret_cast<const double2*>(pb0 + k0 + 2 * t);
+      rw[t] = *reinterpret_cast<const double2*>(w0 + c0 + 2 * t);
+    }
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      sA[buf][lrow * G64_LD + lk + 2 * t] = ra[t].x * rw[t].x;
+      sA[buf][lrow * G64_LD + lk + 2 * t + 1] = ra[t].y * rw[t].y;
+      sB[buf][lrow * G64_LD + lk + 2 * t] = rb[t].x;
+      sB[buf][lrow * G64_LD + lk + 2 * t + 1] = rb[t].y;
+    }
+  };
+  double4_t acc[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc[a][b] = double4_t{0.0, 0.0, 0.0, 0.0};
+  const int r = lane & 15, kq = lane >> 4;
+  const int n_slabs = 2 * nkp / G64_K;
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int s = 0; s < n_slabs; ++s) {
+    const int buf = s & 1;
+    if (s + 1 < n_slabs) load((s + 1) * G64_K);
+    const double* pa = sA[buf];
+    const double* pb = sB[buf];
+#pragma unroll
+    for (int kk = 0; kk < G64_K; kk += 4) {
+      double av[2], bv[2];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) av[a] = pa[(wm + 16 * a + r) * G64_LD + kk + kq];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) bv[b] = pb[(wn + 16 * b + r) * G64_LD + kk + kq];
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+    }
+    if (s + 1 < n_slabs) store(buf ^ 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int i = atoms[m0 + wm + 16 * a + 4 * t + kq], j = atoms[n0 + wn + 16 * b + r];
+        if (i < 0 || j < 0) continue;
+        A[(size_t)i * n + j] += acc[a][b][t];
+        if (tm != tn) A[(size_t)j * n + i] += acc[a][b][t];
       }
 }
 
@@ -202,8 +355,27 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x6_mfma(int M, int N, int K, c
 void launch_gemm_nt(hipStream_t s, int M, int N, int K, double alpha, const double* A, int lda, const double* B,
                     int ldb, double beta, double* D, int ldd) {
   if (M <= 0 || N <= 0) return;
-  hipLaunchKernelGGL(k_gemm_f64_mfma, dim3((N + G64_TILE - 1) / G64_TILE, (M + G64_TILE - 1) / G64_TILE), dim3(256), 0,
+  hipLaunchKernelGGL(k_gemm_f64_mfma<false>, dim3((N + G64_TILE - 1) / G64_TILE, (M + G64_TILE - 1) / G64_TILE), dim3(256), 0,
                      s, M, N, K, alpha, A, lda, B, ldb, beta, D, ldd);
+}
+
+void launch_syrk_nt(hipStream_t s, int M, int K, double alpha, const double* A, int lda, double beta, double* D,
+                    int ldd) {
+  if (M <= 0) return;
+  const int t = (M + G64_TILE - 1) / G64_TILE;
+  hipLaunchKernelGGL(k_gemm_f64_mfma<true>, dim3(t * (t + 1) / 2), dim3(256), 0, s, M, M, K, alpha, A, lda, A, lda,
+                     beta, D, ldd);
+}
+
+void launch_elastance_kspace(hipStream_t s, int n, int n_list, const int* atoms, const int* tile_h, int H,
+                             const double* heights, int nk, int nkp, const double* kxy, const int* nz, double dkz,
+                             double inv4a2, double scale, const double* ex, const double* ey, double* W, double* P,
+                             double* A) {
+  const int t = n_list / ELAST_TILE;
+  hipLaunchKernelGGL(k_height_weights, dim3(nkp / 16, H * H), dim3(256), 0, s, H, nk, nkp, heights, kxy, nz,
+                     dkz, inv4a2, scale, W);
+  hipLaunchKernelGGL(k_phase_xy, dim3((nkp + 255) / 256, n_list), dim3(256), 0, s, nk, nkp, atoms, kxy, ex, ey, P);
+  hipLaunchKernelGGL(k_elastance_kspace, dim3(t * (t + 1) / 2), dim3(256), 0, s, n, H, nkp, atoms, tile_h, P, W, A);
 }
 
 void launch_gemm_bf16x6(hipStream_t s, int M, int N, int K, const unsigned short* A, size_t a_plane,

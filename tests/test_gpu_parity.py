@@ -70,6 +70,44 @@ def test_elastance_and_projection(torch_dev, name, geometry):
         assert np.abs(Sg @ w.elec_sub.astype(float)).max() < 1e-10 * np.abs(Sg).max()
     ctx.close()
 
+@pytest.mark.parametrize("n_low,n_up,flat,geometry", [(1, 1, True, "ff"), (17, 15, True, "ff"), (20, 13, True, "dc"),
+                                                      (64, 1, True, "slab"), (65, 63, True, "ff"),
+                                                      (72, 72, True, "slab"), (21, 20, False, "ff"),
+                                                      (70, 67, False, "dc")])
+def test_elastance_atom_counts_and_heights(torch_dev, n_low, n_up, flat, geometry):
+    """Atom counts around the 32-wide pivot blocks and the 64-atom tiles, flat
+    electrodes (the k-space sum by heights) and corrugated ones, every atom at
+    a height of its own (the product form)."""
+    import dataclasses
+    _say(f"[gpu] elastance {n_low}+{n_up} flat={flat} {geometry}")
+    from workloads import make_workload
+    w = make_workload("tiny", "ff")
+    rng = np.random.default_rng(11)
+    low, up = np.flatnonzero(w.elec_side < 0)[:n_low], np.flatnonzero(w.elec_side > 0)[:n_up]
+    keep = np.concatenate([low, up])
+    xyz = w.elec_xyz[:, keep].copy()
+    xyz[2] += 0.3
+    if not flat:
+        xyz[2] += rng.uniform(-0.05, 0.05, keep.size)
+    side, sub, box = w.elec_side[keep], None, w.box.copy()
+    if geometry == "dc":
+        xyz = np.concatenate([xyz, xyz + np.array([[0.0], [0.0], [box[2]]])], axis=1)
+        sub = np.repeat(np.array([1, 0], np.uint8), keep.size)
+        side, box[2] = np.concatenate([side, -side]), 2 * box[2]
+    elif geometry == "slab":
+        xyz[2] += box[2]
+        box[2] *= 3
+    sites = w.site_xyz.copy()
+    sites[2] += 0.3
+    w = dataclasses.replace(w, geometry=geometry, box=box, elec_xyz=np.ascontiguousarray(xyz),
+                            elec_side=np.ascontiguousarray(side), elec_sub=sub, site_xyz=sites)
+    A, S = cpm.build(w)
+    ctx, _ = gpu_context(torch_dev, w)
+    a, s = ctx.get_matrix(0), ctx.get_matrix(1)
+    assert np.abs(a - A).max() < TIGHT * np.abs(A).max()
+    assert np.abs(s - S).max() < TIGHT * np.abs(S).max()
+    ctx.close()
+
 
 @pytest.mark.parametrize("name,geometry", CASES)
 def test_step_parity(torch_dev, name, geometry):
