@@ -74,8 +74,8 @@ def poisson_matrix(n_bins, h, geometry):
         D[0, 0] = -1.0              # ghost point psi_{-1} = psi_0 (zero flux)
         D[-1, -1] = -1.0            # ghost point psi_n = psi_{n-1}
     else:
-        D[0, -1] = 1.0              # periodic neighbours across the boundary
-        D[-1, 0] = 1.0
+        D[0, -1] += 1.0             # periodic neighbours across the boundary (of two bins, the
+        D[-1, 0] += 1.0             # same neighbour on both sides)
     return D / (h * h)
 
 

@@ -597,7 +597,7 @@ void launch_gemm_bf16x6(hipStream_t s, int M, int N, int K, const unsigned short
 
 // ------------------------------------------- potential profile (k_profile.hip)
 
-constexpr int PROFILE_THREADS = 256;          // histogram workgroups
+constexpr int PROFILE_THREADS = 1024;         // histogram workgroups
 constexpr int PROFILE_SOLVE_THREADS = 1024;   // the one solving workgroup (n_bins <= 2048)
 constexpr int PROFILE_MAX_BINS = 2048;
 constexpr int PROFILE_MAX_HEIGHTS = 2048;

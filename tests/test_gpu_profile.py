@@ -87,6 +87,17 @@ def test_profile_many_frames_most_partitions(torch_dev):
     run_case(torch_dev, w, 4096, 2048, np.array([0.0, 1.0]), 1)
 
 
+@pytest.mark.parametrize("n_frames,n_bins", [(1, 2), (7, 63), (59, 64), (455, 65), (512, 1025)])
+def test_profile_partition_edges(torch_dev, n_frames, n_bins):
+    """Fewer sites and atoms than threads; 1, 1, 2, 8 (summed by the solving
+    workgroup) and 9 partitions (summed by the pass before it)."""
+    import dataclasses
+    from workloads import make_workload
+    _say(f"[gpu] profile tiny ff, {n_frames} frames, {n_bins} bins")
+    w = dataclasses.replace(make_workload("tiny", "ff"), kspace="pppm")
+    run_case(torch_dev, w, n_frames, n_bins, np.array([0.0, 1.5]), 1)
+
+
 def test_profile_rejects_bad_arguments(torch_dev):
     torch = torch_dev
     from paper_2201_12963_amd import Context, CpmError
