@@ -181,7 +181,8 @@ __global__ __launch_bounds__(256) void k_site_forces(Cell cell, ElecSet<T> el, S
   // the charges in the atoms' sorted order, loaded with their positions
   const double* qa = fa.qa_s + (size_t)frame * fa.qa_frame_stride;
   int n = 0;
-  walk_runs(rlo, rhi, nruns,
+  const bool no_img = (cell.img[0] | cell.img[1] | cell.img[2]) == 0;
+  walk_runs<2>(rlo, rhi, nruns,
             [&](int k, bool v) {
               ElecPartner<T> p{0, 0, 0, (T)0, (T)0};
               if (v) {
@@ -194,17 +195,13 @@ __global__ __launch_bounds__(256) void k_site_forces(Cell cell, ElecSet<T> el, S
             [&](const ElecPartner<T>& p, int k, bool valid) {
               const T ca = p.a, cb = p.b;
               const Disp d = min_disp(cell, xj, yj, zj, p.x, p.y, p.z);
-              for (int ix = -cell.img[0]; ix <= cell.img[0]; ++ix)
-                for (int iy = -cell.img[1]; iy <= cell.img[1]; ++iy)
-                  for (int iz = -cell.img[2]; iz <= cell.img[2]; ++iz) {
-                    T dx, dy, dz;
-                    const bool in = image_pair(cell, d, ix, iy, iz, fa.rc2, dx, dy, dz) && valid;
-                    n = queue_push(Q, n, in, dx, dy, dz, ca, cb);
-                    if (n >= WAVE) {
-                      eval_g1<T, TWO>(Q, lane, fa.alpha, fa.eta, fr, frb);
-                      n = queue_pop(Q, n);
-                    }
-                  }
+              each_image<T>(cell, no_img, d, fa.rc2, valid, false, [&](T dx, T dy, T dz, bool in) {
+                n = queue_push<T, TWO>(Q, n, in, dx, dy, dz, ca, cb);
+                if (n >= WAVE) {
+                  eval_g1<T, TWO>(Q, lane, fa.alpha, fa.eta, fr, frb);
+                  n = queue_pop<T, TWO>(Q, n);
+                }
+              });
             });
   if (lane < n) eval_g1<T, TWO>(Q, lane, fa.alpha, fa.eta, fr, frb);
   }

@@ -89,29 +89,30 @@ struct WaveQueue {
   }
 };
 
-// append this lane's pair if `in`; returns the new queue length (< 2 * WAVE
+// append this lane's pair if `in` (B2: with its second charge b); returns the new queue length (< 2 * WAVE
 // when called with fewer than WAVE entries queued)
-template <typename T>
+template <typename T, bool B2>
 __device__ __forceinline__ int queue_push(WaveQueue<T>& q, int n, bool in, T dx, T dy, T dz, T a, T b) {
   const int lane = threadIdx.x & (WAVE - 1);
   const unsigned long long m = __ballot(in);
   if (in) {
     const int pos = n + __popcll(m & ((1ull << lane) - 1ull));
-    q.x[pos] = dx; q.y[pos] = dy; q.z[pos] = dz; q.a[pos] = a; q.b[pos] = b;
+    q.x[pos] = dx; q.y[pos] = dy; q.z[pos] = dz; q.a[pos] = a;
+    if (B2) q.b[pos] = b;
   }
   __builtin_amdgcn_wave_barrier();
   return n + __popcll(m);
 }
 
 // drop the first WAVE entries (already consumed), moving the rest down
-template <typename T>
+template <typename T, bool B2>
 __device__ __forceinline__ int queue_pop(WaveQueue<T>& q, int n) {
   const int lane = threadIdx.x & (WAVE - 1);
   const int rest = n - WAVE;
   T x = 0, y = 0, z = 0, a = 0, b = 0;
-  if (lane < rest) { x = q.x[WAVE + lane]; y = q.y[WAVE + lane]; z = q.z[WAVE + lane]; a = q.a[WAVE + lane]; b = q.b[WAVE + lane]; }
+  if (lane < rest) { x = q.x[WAVE + lane]; y = q.y[WAVE + lane]; z = q.z[WAVE + lane]; a = q.a[WAVE + lane]; if (B2) b = q.b[WAVE + lane]; }
   __builtin_amdgcn_wave_barrier();
-  if (lane < rest) { q.x[lane] = x; q.y[lane] = y; q.z[lane] = z; q.a[lane] = a; q.b[lane] = b; }
+  if (lane < rest) { q.x[lane] = x; q.y[lane] = y; q.z[lane] = z; q.a[lane] = a; if (B2) q.b[lane] = b; }
   __builtin_amdgcn_wave_barrier();
   return rest;
 }
@@ -199,36 +200,69 @@ __device__ __forceinline__ void split_runs(int* rlo, int* rhi, int nruns, int pa
 
 // Walks the partners listed by the runs 64 at a time: load(k, valid)
 // returns the data of partner k (lane's index in the chunk), body(data, k,
-// valid) consumes it.  The loads of the next chunk are issued before the
-// body of the current one runs.
-template <typename Load, typename Body>
-__device__ __forceinline__ void walk_runs(const int* rlo, const int* rhi, int nruns, Load load, Body body) {
+// valid) consumes it.  Called by a whole wavefront; the run table is
+// consumed.
+//
+// The runs are walked as one list, so that every chunk but the last is full
+// however short the runs are (in a cell of 5 x 5 columns a run is three cells
+// of ~13 sites: 20 chunks a site run by run, 10 as one list), and
+// AHEAD chunks of loads are in flight: the walk is a chain of loads
+// from other chiplets' caches, not of arithmetic.  A lane finds the run of
+// its list position by a binary search over the runs' starts in LDS (two
+// steps for the one to three runs of a narrow cell).  The partners come in
+// the order of the runs either way, and the queue cuts that order into 64s,
+// so the sums do not depend on the chunks.
+template <int AHEAD, typename Load, typename Body>
+__device__ __forceinline__ void walk_runs(int* rlo, int* rhi, int nruns, Load load, Body body) {
+  if (nruns == 0) return;
   const int lane = threadIdx.x & (WAVE - 1);
-  int r = 0, base = 0, end = 0;
-  if (nruns > 0) { base = rlo[0]; end = rhi[0]; }
-  while (r < nruns && base >= end) {
-    ++r;
-    if (r < nruns) { base = rlo[r]; end = rhi[r]; }
+  int lo = 0, len = 0;
+  if (lane < nruns) { lo = rlo[lane]; len = rhi[lane] - lo; }
+  int incl = len;                               // inclusive prefix over the (at most 32) runs
+  for (int off = 1; off < nruns; off <<= 1) {
+    const int t = __shfl_up(incl, off, WAVE);
+    if (lane >= off) incl += t;
   }
-  if (r >= nruns) return;
-  int ck = base + lane;
-  bool cv = ck < end;
-  auto cur = load(ck, cv);
-  for (;;) {
-    base += WAVE;
-    while (r < nruns && base >= end) {
-      ++r;
-      if (r < nruns) { base = rlo[r]; end = rhi[r]; }
+  const int total = __builtin_amdgcn_readlane(incl, nruns - 1);
+  __builtin_amdgcn_wave_barrier();
+  // rhi: list position of every run's first partner; rlo: partner index
+  // minus list position
+  if (lane < 32) {
+    rhi[lane] = lane < nruns ? incl - len : 0x7fffffff;
+    rlo[lane] = lo - (incl - len);
+  }
+  __builtin_amdgcn_wave_barrier();
+  int top = 1;
+  while (top < nruns) top <<= 1;
+  // partner index of list position f (the last run that starts at or before it)
+  auto partner = [&](int f) {
+    int r = 0;
+    for (int step = top >> 1; step > 0; step >>= 1) r += rhi[r + step] <= f ? step : 0;
+    return f + rlo[r];
+  };
+  using Data = decltype(load(0, false));
+  Data p[AHEAD];
+  int pk[AHEAD];
+#pragma unroll
+  for (int s = 0; s < AHEAD; ++s) {
+    const int f = s * WAVE + lane;
+    const bool v = f < total;
+    pk[s] = v ? partner(f) : 0;
+    p[s] = load(pk[s], v);
+  }
+  for (int base = 0; base < total; base += AHEAD * WAVE) {
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) {
+      const int b0 = base + s * WAVE;
+      if (b0 >= total) break;
+      body(p[s], pk[s], b0 + lane < total);
+      const int f = b0 + AHEAD * WAVE + lane;
+      if (b0 + AHEAD * WAVE < total) {
+        const bool v = f < total;
+        pk[s] = v ? partner(f) : 0;
+        p[s] = load(pk[s], v);
+      }
     }
-    const bool more = r < nruns;
-    const int nk = base + lane;
-    const bool nv = more && nk < end;
-    auto nxt = load(nk, nv);
-    body(cur, ck, cv);
-    if (!more) break;
-    cur = nxt;
-    ck = nk;
-    cv = nv;
   }
 }
 
@@ -271,6 +305,30 @@ __device__ __forceinline__ bool image_pair(const Cell& cell, const Disp& d, int 
   return x * x + y * y + z * z < rc2;
 }
 
+// test(d, first): runs body(dx, dy, dz, in) for the pair's minimum image, or
+// for every periodic image where the cell has any (cells shorter than two
+// cutoffs along an axis); `self` marks the pair of a site with itself, left
+// out at the minimum image.  The common case without images is straight-line
+// code: the image loops and their products were half of a test's
+// instructions, and the walk is bound by its instruction issue as much as by
+// its latency.
+template <typename T, typename Push>
+__device__ __forceinline__ void each_image(const Cell& cell, bool no_img, const Disp& d, double rc2, bool valid,
+                                           bool self, Push push) {
+  if (no_img) {
+    push((T)d.d0, (T)d.d1, (T)d.d2, d.d0 * d.d0 + d.d1 * d.d1 + d.d2 * d.d2 < rc2 && valid && !self);
+    return;
+  }
+  for (int ix = -cell.img[0]; ix <= cell.img[0]; ++ix)
+    for (int iy = -cell.img[1]; iy <= cell.img[1]; ++iy)
+      for (int iz = -cell.img[2]; iz <= cell.img[2]; ++iz) {
+        T dx, dy, dz;
+        const bool in = image_pair(cell, d, ix, iy, iz, rc2, dx, dy, dz) && valid &&
+                        !(self && ix == 0 && iy == 0 && iz == 0);
+        push(dx, dy, dz, in);
+      }
+}
+
 // ------------------------------------------------------------------ b real
 
 // erfc(eta r) and exp(-eta^2 r^2) are below 1e-18 for eta r > 6.5, far under
@@ -310,7 +368,8 @@ __device__ __forceinline__ void real_b_wave(const Cell& cell, T alpha, T eta, do
   const int nruns = stencil_runs(cell, c, cs, rlo, rhi);
   T acc = 0;
   int n = 0;
-  walk_runs(rlo, rhi, nruns,
+  const bool no_img = (cell.img[0] | cell.img[1] | cell.img[2]) == 0;
+  walk_runs<sizeof(T) == 8 ? 2 : 4>(rlo, rhi, nruns,
             [&](int k, bool v) {
               Partner<T> p{0, 0, 0, (T)0};
               if (v) { p.x = sx[k]; p.y = sy[k]; p.z = sz[k]; p.a = (T)sq[k]; }
@@ -318,17 +377,13 @@ __device__ __forceinline__ void real_b_wave(const Cell& cell, T alpha, T eta, do
             },
             [&](const Partner<T>& p, int k, bool valid) {
               const Disp d = min_disp(cell, ex, ey, ez, p.x, p.y, p.z);
-              for (int ix = -cell.img[0]; ix <= cell.img[0]; ++ix)
-                for (int iy = -cell.img[1]; iy <= cell.img[1]; ++iy)
-                  for (int iz = -cell.img[2]; iz <= cell.img[2]; ++iz) {
-                    T dx, dy, dz;
-                    const bool in = image_pair(cell, d, ix, iy, iz, rc2, dx, dy, dz) && valid;
-                    n = queue_push(Q, n, in, dx, dy, dz, p.a, (T)0);
-                    if (n >= WAVE) {
-                      acc += g1_potential(Q.x[lane], Q.y[lane], Q.z[lane], Q.a[lane], alpha, eta);
-                      n = queue_pop(Q, n);
-                    }
-                  }
+              each_image<T>(cell, no_img, d, rc2, valid, false, [&](T dx, T dy, T dz, bool in) {
+                n = queue_push<T, false>(Q, n, in, dx, dy, dz, p.a, (T)0);
+                if (n >= WAVE) {
+                  acc += g1_potential(Q.x[lane], Q.y[lane], Q.z[lane], Q.a[lane], alpha, eta);
+                  n = queue_pop<T, false>(Q, n);
+                }
+              });
             });
   if (lane < n) acc += g1_potential(Q.x[lane], Q.y[lane], Q.z[lane], Q.a[lane], alpha, eta);
   acc = wave_sum(acc);
@@ -408,7 +463,8 @@ __device__ __forceinline__ void site_pairs_wave(const Cell& cell, const SiteSet<
   T fr[3] = {0, 0, 0};
   T u = 0;
   int n = 0;
-  walk_runs(rlo, rhi, nruns,
+  const bool no_img = (cell.img[0] | cell.img[1] | cell.img[2]) == 0;
+  walk_runs<sizeof(T) == 8 ? 2 : 4>(rlo, rhi, nruns,
             [&](int k, bool v) {
               Partner<T> p{0, 0, 0, (T)0};
               if (v) { p.x = sx[k]; p.y = sy[k]; p.z = sz[k]; p.a = (T)sq[k]; }
@@ -416,18 +472,13 @@ __device__ __forceinline__ void site_pairs_wave(const Cell& cell, const SiteSet<
             },
             [&](const Partner<T>& p, int k, bool valid) {
               const Disp d = min_disp(cell, xj, yj, zj, p.x, p.y, p.z);
-              for (int ix = -cell.img[0]; ix <= cell.img[0]; ++ix)
-                for (int iy = -cell.img[1]; iy <= cell.img[1]; ++iy)
-                  for (int iz = -cell.img[2]; iz <= cell.img[2]; ++iz) {
-                    T dx, dy, dz;
-                    const bool self = k == j && ix == 0 && iy == 0 && iz == 0;
-                    const bool in = image_pair(cell, d, ix, iy, iz, rc2, dx, dy, dz) && valid && !self;
-                    n = queue_push(Q, n, in, dx, dy, dz, p.a, (T)0);
-                    if (n >= WAVE) {
-                      eval_g0(Q, lane, alpha, fr, u);
-                      n = queue_pop(Q, n);
-                    }
-                  }
+              each_image<T>(cell, no_img, d, rc2, valid, k == j, [&](T dx, T dy, T dz, bool in) {
+                n = queue_push<T, false>(Q, n, in, dx, dy, dz, p.a, (T)0);
+                if (n >= WAVE) {
+                  eval_g0(Q, lane, alpha, fr, u);
+                  n = queue_pop<T, false>(Q, n);
+                }
+              });
             });
   if (lane < n) eval_g0(Q, lane, alpha, fr, u);
   const T v8[8] = {fr[0], fr[1], fr[2], u, (T)0, (T)0, (T)0, (T)0};
