@@ -212,11 +212,15 @@ int upload(cpm_ctx* c, T** p, const std::vector<T>& h) {
 bool factorize(int n, FFTPlan1D& p) {
   p.n = n;
   p.nfac = 0;
-  int m = n;
-  while (m % 4 == 0) { p.fac[p.nfac++] = 4; m /= 4; if (p.nfac >= MAX_FFT_FACTORS) return false; }
-  while (m % 2 == 0) { p.fac[p.nfac++] = 2; m /= 2; if (p.nfac >= MAX_FFT_FACTORS) return false; }
-  while (m % 3 == 0) { p.fac[p.nfac++] = 3; m /= 3; if (p.nfac >= MAX_FFT_FACTORS) return false; }
-  while (m % 5 == 0) { p.fac[p.nfac++] = 5; m /= 5; if (p.nfac >= MAX_FFT_FACTORS) return false; }
+  if (n < 1 || n > 8191) return false;      // (far beyond what the planes and columns admit)
+  int m = n, ns = 1;
+  for (int R : {4, 2, 3, 5})
+    while (m % R == 0) {
+      if (p.nfac >= MAX_FFT_FACTORS) return false;
+      p.stage[p.nfac++] = R | (n / R) << 3 | (n / (ns * R)) << 16;
+      ns *= R;
+      m /= R;
+    }
   return m == 1;
 }
 

@@ -43,9 +43,13 @@ struct Cell {          // periodic orthorhombic cell and its cell-list grid
 };
 
 struct FFTPlan1D {     // mixed-radix Stockham plan for one axis
-  int n;
+  int n;               // at most 8191 points
   int nfac;
-  int fac[MAX_FFT_FACTORS];
+  // per stage: radix R (bits 0-2), butterflies n/R (bits 3-15) and twiddle
+  // step n/(Ns R), Ns the product of the radices before it (from bit 16); the
+  // integer divisions that gave these on the device were half of a stage's
+  // latency
+  int stage[MAX_FFT_FACTORS];
   const double2* tw;   // e^{-2 pi i t / n}, t = 0..n-1
   const float2* twf;
   int planes;          // x plan only: most planes per many-frame x-y workgroup (0: as many as fit)
@@ -308,7 +312,8 @@ struct PairArgs {
 // z pass: a lane prefetches the multiplier (and saved spectrum) of the
 // first ZPASS_PREFETCH of its column's points into registers, the rest is
 // read when used; columns of at most ZPASS_MAX_POINTS points
-constexpr int ZPASS_PREFETCH = 8;
+// (one-frame passes, a lane per point of one column: 256 points)
+constexpr int ZPASS_PREFETCH = 8, ZPASS_PREFETCH_ONE = 4;
 constexpr int ZPASS_MAX_POINTS = 2048;
 
 struct ZPassArgs {
@@ -316,6 +321,7 @@ struct ZPassArgs {
   int cpw;                 // (x, y) columns per workgroup, one wavefront each (<= 4)
   int n_blocks;            // workgroups per frame: ceil(Kx Ky / cpw)
   int mode;                // 0: potential, 1: field (ik)
+  int lines;               // LDS lines per column (set by the launch)
   double twopi_L[3];       // 2 pi / L_d
 };
 

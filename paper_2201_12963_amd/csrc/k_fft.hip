@@ -99,15 +99,17 @@ __device__ __forceinline__ void load_twiddles(const FFTPlan1D& p, T2* dst) {
 // dependent chain of a stage.
 __device__ __forceinline__ int div_small(int u, float rd) { return (int)(((float)u + 0.5f) * rd); }
 
+// its reciprocal: the hardware estimate (1 ulp, well inside that margin)
+__device__ __forceinline__ float rcp_small(int d) { return __builtin_amdgcn_rcpf((float)d); }
+
 // One Stockham stage of radix R over nlines lines (see the file comment) of
-// each of nplanes planes pstride apart.
+// each of nplanes planes pstride apart; nb butterflies a line, twiddle step
+// tstep (FFTPlan1D).
 template <int R, typename T2>
-__device__ __forceinline__ void fft_stage(const T2* src, T2* dst, int N, int Ns, int nlines, int es, int ls,
-                                          const T2* tw, int sigma, int nplanes, int pstride) {
-  const int nb = N / R;
-  const int tstep = N / (Ns * R);
+__device__ __forceinline__ void fft_stage(const T2* src, T2* dst, int nb, int tstep, int Ns, int nlines, int es,
+                                          int ls, const T2* tw, int sigma, int nplanes, int pstride) {
   const int lnb = nlines * nb;
-  const float rnb = 1.0f / (float)nb, rns = 1.0f / (float)Ns, rlnb = 1.0f / (float)lnb;
+  const float rnb = rcp_small(nb), rns = rcp_small(Ns), rlnb = rcp_small(lnb);
   for (int u = threadIdx.x; u < nplanes * lnb; u += blockDim.x) {
     const int pl = nplanes > 1 ? div_small(u, rlnb) : 0;
     const int ul = u - pl * lnb;
@@ -138,17 +140,19 @@ __device__ __forceinline__ void fft_stage(const T2* src, T2* dst, int N, int Ns,
 template <typename T2>
 __device__ T2* fft_lines(T2* a, T2* b, const FFTPlan1D& p, const T2* tw, int nlines, int es, int ls, int sigma,
                          int nplanes = 1, int pstride = 0) {
-  const int N = p.n;
   T2* src = a;
   T2* dst = b;
   int Ns = 1;
+  int next = p.stage[0];
   for (int f = 0; f < p.nfac; ++f) {
-    const int R = p.fac[f];
+    const int st = next;
+    next = p.stage[min(f + 1, MAX_FFT_FACTORS - 1)];        // read ahead of its use
+    const int R = st & 7, nb = (st >> 3) & 0x1fff, ts = st >> 16;
     switch (R) {
-      case 2: fft_stage<2>(src, dst, N, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
-      case 3: fft_stage<3>(src, dst, N, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
-      case 4: fft_stage<4>(src, dst, N, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
-      default: fft_stage<5>(src, dst, N, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
+      case 2: fft_stage<2>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
+      case 3: fft_stage<3>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
+      case 4: fft_stage<4>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
+      default: fft_stage<5>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
     }
     __syncthreads();
     T2* t = src; src = dst; dst = t;
@@ -241,12 +245,10 @@ __device__ T2* plane_lines(T2* a, T2* b, const FFTPlan1D& p, const T2* tw, int n
 // One Stockham stage of radix R over one contiguous line, by the lanes of
 // one wavefront (no workgroup barrier; the caller orders the stages)
 template <int R, typename T2>
-__device__ __forceinline__ void fft_stage_w(const T2* src0, T2* dst0, int N, int Ns, const T2* tw, int sigma, int nl,
-                                            int lstride) {
+__device__ __forceinline__ void fft_stage_w(const T2* src0, T2* dst0, int nb, int tstep, int Ns, const T2* tw,
+                                            int sigma, int nl, int lstride) {
   const int lane = threadIdx.x & (WAVE - 1);
-  const int nb = N / R;
-  const int tstep = N / (Ns * R);
-  const float rns = 1.0f / (float)Ns, rnb = 1.0f / (float)nb;
+  const float rns = rcp_small(Ns), rnb = rcp_small(nb);
   for (int u = lane; u < nl * nb; u += WAVE) {
     const int l = nl > 1 ? div_small(u, rnb) : 0;
     const int j = u - l * nb;
@@ -278,18 +280,20 @@ __device__ __forceinline__ void fft_stage_w(const T2* src0, T2* dst0, int N, int
 // the buffer holding the result.
 template <typename T2>
 __device__ T2* fft_line_w(T2* a, T2* b, const FFTPlan1D& p, const T2* tw, int sigma, int nl = 1, int lstride = 0) {
-  const int N = p.n;
   T2* src = a;
   T2* dst = b;
   int Ns = 1;
+  int next = p.stage[0];
   __builtin_amdgcn_wave_barrier();
   for (int f = 0; f < p.nfac; ++f) {
-    const int R = p.fac[f];
+    const int st = next;
+    next = p.stage[min(f + 1, MAX_FFT_FACTORS - 1)];        // read ahead of its use
+    const int R = st & 7, nb = (st >> 3) & 0x1fff, ts = st >> 16;
     switch (R) {
-      case 2: fft_stage_w<2>(src, dst, N, Ns, tw, sigma, nl, lstride); break;
-      case 3: fft_stage_w<3>(src, dst, N, Ns, tw, sigma, nl, lstride); break;
-      case 4: fft_stage_w<4>(src, dst, N, Ns, tw, sigma, nl, lstride); break;
-      default: fft_stage_w<5>(src, dst, N, Ns, tw, sigma, nl, lstride); break;
+      case 2: fft_stage_w<2>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
+      case 3: fft_stage_w<3>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
+      case 4: fft_stage_w<4>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
+      default: fft_stage_w<5>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
     }
     __builtin_amdgcn_wave_barrier();
     T2* t = src; src = dst; dst = t;
@@ -780,14 +784,14 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
   // one wavefront per lpw (x, y) columns of Kz points (lpw = 1 for one
   // frame; many frames put up to four short columns in a wavefront, so that
   // the stages fill its lanes), za.cpw wavefronts per workgroup; each
-  // wavefront has its own three LDS buffers of lpw lines and synchronises
+  // wavefront has its own za.lines LDS buffers of lpw lines and synchronises
   // only with itself.  Lane l always takes column l mod lpw, points
   // l / lpw + u 64 / lpw of it.
   const int Kx = za.Kx, Ky = za.Ky, Kz = za.Kz;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x >> 6;
   const int L = MULTI ? lpw : 1, zs = WAVE / L;            // lpw divides 64
   T2* twz = reinterpret_cast<T2*>(smem);
-  T2* A = twz + Kz + (size_t)wv * 3 * L * Kz;
+  T2* A = twz + Kz + (size_t)wv * za.lines * L * Kz;
   T2* B = A + L * Kz;
   T2* C = B + L * Kz;
   load_twiddles(pz, twz);
@@ -811,10 +815,11 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
     if (add_saved == 2) { const T2 b = data1[o]; a.x += b.x; a.y += b.y; }
     return a;
   };
-  T gk[ZPASS_PREFETCH];
-  T2 sv[ZPASS_PREFETCH];
+  constexpr int PF = MULTI ? ZPASS_PREFETCH : ZPASS_PREFETCH_ONE;
+  T gk[PF];
+  T2 sv[PF];
 #pragma unroll
-  for (int u = 0; u < ZPASS_PREFETCH; ++u) {
+  for (int u = 0; u < PF; ++u) {
     const int z = z0 + u * zs;
     gk[u] = (T)0;
     sv[u] = T2{(T)0, (T)0};
@@ -825,7 +830,7 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
     }
   }
   if (active)
-    for (int z = z0 + ZPASS_PREFETCH * zs; z < Kz; z += zs)
+    for (int z = z0 + PF * zs; z < Kz; z += zs)
       Al[z] = (!MASK || za.mode == 0 || zplane_on(zm, z)) ? load_in(z) : T2{(T)0, (T)0};
   __syncthreads();                                         // twiddles
   double e = 0.0;
@@ -844,47 +849,75 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
       };
       if (active) {
 #pragma unroll
-        for (int u = 0; u < ZPASS_PREFETCH; ++u)
+        for (int u = 0; u < PF; ++u)
           if (z0 + u * zs < Kz) mul(z0 + u * zs, gk[u]);
-        for (int z = z0 + ZPASS_PREFETCH * zs; z < Kz; z += zs) mul(z, G[z * plane + cxy]);
+        for (int z = z0 + PF * zs; z < Kz; z += zs) mul(z, G[z * plane + cxy]);
       }
       T2* Y = fft_line_w(X, F1, pz, twz, +1, L, Kz);
       if (active)
         for (int z = z0; z < Kz; z += zs)
           if (!MASK || zplane_on(zm, z)) data1[fo + z * plane + cxy] = Y[c * Kz + z];
     } else {
-      // C keeps G X; the first inverse transforms (-i kx + ky) G X (Ex + i Ey
-      // after the x-y inverse), the second -i kz G X (Ez)
+      // the inverse transforms of (-i kx + ky) G X (Ex + i Ey after the x-y
+      // inverse) and of -i kz G X (Ez)
       const T kx = mode_k<T>(x, Kx, (T)za.twopi_L[0]);
       const T ky = mode_k<T>(y, Ky, (T)za.twopi_L[1]);
-      T2* Cl = C + c * Kz;
-      auto mul = [&](int z, T g, T2 w) {
-        T2 v = Xl[z];
-        if (add_saved == 1) { v.x += w.x; v.y += w.y; }
-        v = T2{v.x * g, v.y * g};
-        Cl[z] = v;
-        F1l[z] = T2{kx * v.y + ky * v.x, -kx * v.x + ky * v.y};
-      };
-      if (active) {
+      if (!MULTI && za.lines == 4) {
+        // one column per wavefront: both transforms at once as two lines in
+        // (A, B) and (C, D), so that the second fills lanes the first leaves
+        // idle (a radix-4 stage of 128 points has 32 butterflies) instead of
+        // following it: the z chain of the field pass is two transforms long,
+        // not three.  A lane takes its points of X and puts both spectra of
+        // the same points in their place.
+        auto mul = [&](int z, T g, T2 w) {
+          T2 v = X[z];
+          if (add_saved == 1) { v.x += w.x; v.y += w.y; }
+          v = T2{v.x * g, v.y * g};
+          const T kz = mode_k<T>(z, Kz, (T)za.twopi_L[2]);
+          A[z] = T2{kx * v.y + ky * v.x, -kx * v.x + ky * v.y};
+          B[z] = T2{kz * v.y, -kz * v.x};
+        };
 #pragma unroll
-        for (int u = 0; u < ZPASS_PREFETCH; ++u)
+        for (int u = 0; u < PF; ++u)
           if (z0 + u * zs < Kz) mul(z0 + u * zs, gk[u], sv[u]);
-        for (int z = z0 + ZPASS_PREFETCH * zs; z < Kz; z += zs)
+        for (int z = z0 + PF * zs; z < Kz; z += zs)
           mul(z, G[z * plane + cxy], add_saved == 1 ? save[fo + z * plane + cxy] : T2{(T)0, (T)0});
+        T2* Y = fft_line_w(A, C, pz, twz, +1, 2, Kz);
+        for (int z = z0; z < Kz; z += zs) {
+          data1[fo + z * plane + cxy] = Y[z];
+          data2[fo + z * plane + cxy] = Y[Kz + z];
+        }
+      } else {
+        // C keeps G X
+        T2* Cl = C + c * Kz;
+        auto mul = [&](int z, T g, T2 w) {
+          T2 v = Xl[z];
+          if (add_saved == 1) { v.x += w.x; v.y += w.y; }
+          v = T2{v.x * g, v.y * g};
+          Cl[z] = v;
+          F1l[z] = T2{kx * v.y + ky * v.x, -kx * v.x + ky * v.y};
+        };
+        if (active) {
+#pragma unroll
+          for (int u = 0; u < PF; ++u)
+            if (z0 + u * zs < Kz) mul(z0 + u * zs, gk[u], sv[u]);
+          for (int z = z0 + PF * zs; z < Kz; z += zs)
+            mul(z, G[z * plane + cxy], add_saved == 1 ? save[fo + z * plane + cxy] : T2{(T)0, (T)0});
+        }
+        T2* Y = fft_line_w(F1, X, pz, twz, +1, L, Kz);
+        if (active)
+          for (int z = z0; z < Kz; z += zs) data1[fo + z * plane + cxy] = Y[c * Kz + z];
+        T2* W = (Y == F1) ? X : F1;                           // free after the store above
+        __builtin_amdgcn_wave_barrier();
+        for (int z = z0; z < Kz; z += zs) {
+          const T kz = mode_k<T>(z, Kz, (T)za.twopi_L[2]);
+          const T2 v = Cl[z];
+          Cl[z] = T2{kz * v.y, -kz * v.x};
+        }
+        T2* Z = fft_line_w(C, W, pz, twz, +1, L, Kz);
+        if (active)
+          for (int z = z0; z < Kz; z += zs) data2[fo + z * plane + cxy] = Z[c * Kz + z];
       }
-      T2* Y = fft_line_w(F1, X, pz, twz, +1, L, Kz);
-      if (active)
-        for (int z = z0; z < Kz; z += zs) data1[fo + z * plane + cxy] = Y[c * Kz + z];
-      T2* W = (Y == F1) ? X : F1;                           // free after the store above
-      __builtin_amdgcn_wave_barrier();
-      for (int z = z0; z < Kz; z += zs) {
-        const T kz = mode_k<T>(z, Kz, (T)za.twopi_L[2]);
-        const T2 v = Cl[z];
-        Cl[z] = T2{kz * v.y, -kz * v.x};
-      }
-      T2* Z = fft_line_w(C, W, pz, twz, +1, L, Kz);
-      if (active)
-        for (int z = z0; z < Kz; z += zs) data2[fo + z * plane + cxy] = Z[c * Kz + z];
     }
   }
   if (za.mode == 0 && energy_part) {
@@ -1076,7 +1109,13 @@ void launch_fft_z_t(hipStream_t s, int n_frames, const FFTPlan1D& pz, const ZPas
       lpw *= 2;
   const int per_block = za.cpw * lpw;
   const int nzb = z_pass ? (za.Kx * za.Ky + per_block - 1) / per_block : 0;
-  size_t lds = (3 * (size_t)za.cpw * lpw * za.Kz + za.Kz) * sizeof(T2);
+  // LDS lines per column: two for the potential's round trip; the field's
+  // two inverse transforms run side by side in four where one column per
+  // wavefront leaves lanes idle (and four fit), else one after the other in
+  // three
+  ZPassArgs zl = za;
+  zl.lines = za.mode == 0 ? 2 : lpw == 1 && (4 * (size_t)za.cpw + 1) * za.Kz * sizeof(T2) <= LDS_LIMIT ? 4 : 3;
+  size_t lds = (zl.lines * (size_t)za.cpw * lpw * za.Kz + za.Kz) * sizeof(T2);
   if (r.n_blocks + p.n_blocks > 0) lds = std::max(lds, pair_queue_lds<T>());
   if ((r.n_blocks > 0 && r.tiles) || (p.n_blocks > 0 && p.tsplit > 0)) {
     std::fprintf(stderr, "cpm: only the one-wavefront-per-target pair forms ride in the z pass\n");
@@ -1095,22 +1134,22 @@ void launch_fft_z_t(hipStream_t s, int n_frames, const FFTPlan1D& pz, const ZPas
     std::abort();
   }
   if (zm && lpw > 1)
-    hipLaunchKernelGGL((k_fft_z_masked<T, T2, true>), grid, dim3(256), lds, s, pz, za, G, data1, data2, save,
+    hipLaunchKernelGGL((k_fft_z_masked<T, T2, true>), grid, dim3(256), lds, s, pz, zl, G, data1, data2, save,
                        add_saved, energy_part, nzb, r, p, lpw, za.n_blocks, *zm);
   else if (zm)
-    hipLaunchKernelGGL((k_fft_z_masked<T, T2, false>), grid, dim3(256), lds, s, pz, za, G, data1, data2, save,
+    hipLaunchKernelGGL((k_fft_z_masked<T, T2, false>), grid, dim3(256), lds, s, pz, zl, G, data1, data2, save,
                        add_saved, energy_part, nzb, r, p, 1, za.n_blocks, *zm);
   else if (in1 != data1 && lpw > 1)
-    hipLaunchKernelGGL((k_fft_z_sep<T, T2, true>), grid, dim3(256), lds, s, pz, za, G, in1, data1, data2, save,
+    hipLaunchKernelGGL((k_fft_z_sep<T, T2, true>), grid, dim3(256), lds, s, pz, zl, G, in1, data1, data2, save,
                        add_saved, energy_part, nzb, r, p, lpw, za.n_blocks, lj ? *lj : MDArgs{});
   else if (in1 != data1)
-    hipLaunchKernelGGL((k_fft_z_sep<T, T2, false>), grid, dim3(256), lds, s, pz, za, G, in1, data1, data2, save,
+    hipLaunchKernelGGL((k_fft_z_sep<T, T2, false>), grid, dim3(256), lds, s, pz, zl, G, in1, data1, data2, save,
                        add_saved, energy_part, nzb, r, p, 1, za.n_blocks, lj ? *lj : MDArgs{});
   else if (lpw > 1)
-    hipLaunchKernelGGL((k_fft_z<T, T2, true>), grid, dim3(256), lds, s, pz, za, G, data1, data2, save, add_saved,
+    hipLaunchKernelGGL((k_fft_z<T, T2, true>), grid, dim3(256), lds, s, pz, zl, G, data1, data2, save, add_saved,
                        energy_part, nzb, r, p, lpw, za.n_blocks);
   else
-    hipLaunchKernelGGL((k_fft_z<T, T2, false>), grid, dim3(256), lds, s, pz, za, G, data1, data2, save, add_saved,
+    hipLaunchKernelGGL((k_fft_z<T, T2, false>), grid, dim3(256), lds, s, pz, zl, G, data1, data2, save, add_saved,
                        energy_part, nzb, r, p, 1, za.n_blocks);
 }
 
