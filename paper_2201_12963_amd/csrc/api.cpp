@@ -580,7 +580,7 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
                            slab_terms(c));
     });
   } else {
-    rec(c, CPM_KERNEL_BIN, s, [=](hipStream_t s) { launch_bin_sites(s, nf, ba); });
+    rec(c, CPM_KERNEL_BIN, s, [=](hipStream_t s) { launch_bin_sites(s, ba); });
     SiteSet<double> sd = Bufs<double>::sites(c);
     if (!need_b) {
       launch_ewald_sf(s, nf, c->nk, c->d_kv, c->d_ew, sd, c->d_rhok, c->d_ek);

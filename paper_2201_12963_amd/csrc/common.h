@@ -425,7 +425,7 @@ struct BinArgs {
   int* status;
   double* wrap_all;            // scratch [frame][3][n_site]: wrapped coordinates, original order
 };
-void launch_bin_sites(hipStream_t s, int n_frames, const BinArgs& a);
+void launch_bin_sites(hipStream_t s, const BinArgs& a);
 
 // real-space sums (k_realspace.hip)
 template <typename T>

@@ -565,7 +565,8 @@ __global__ __launch_bounds__(INTERP ? XY_THREADS_MANY : XY_THREADS, INTERP ? 5 :
 // B-spline stencil reaches the plane in per-wavefront lists, and each staged
 // site adds its P x P in-plane contributions with LDS atomics, its weights
 // computed on the spot.  The scan needs no cell list, so the binning of the
-// same frame runs as one more workgroup of this launch (index n_planes).
+// same frame runs as one more workgroup of this launch (index n_planes on;
+// one frame: several, by z layers).
 // The assembled plane is also written to rho_out (the charge mesh, for
 // inspection), then transformed as in k_fft_xy.  ONE: a one-frame launch
 // (1024 threads; the binning keeps its sites in registers, the planes use
@@ -582,9 +583,10 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
   extern __shared__ __align__(16) unsigned char smem[];
   if ((int)blockIdx.x >= n_planes) {
     if constexpr (ONE)
-      bin_block<SPREAD_THREADS_ONE, true, BIN_BATCH_KEEP>(ba, blockIdx.y, reinterpret_cast<int*>(smem));
+      bin_layers_block<SPREAD_THREADS_ONE>(ba, (int)blockIdx.x - n_planes, (int)gridDim.x - n_planes,
+                                           reinterpret_cast<int*>(smem));
     else
-      bin_block<SPREAD_THREADS, false, BIN_BATCH>(ba, blockIdx.y, reinterpret_cast<int*>(smem));
+      bin_block<SPREAD_THREADS, BIN_BATCH>(ba, blockIdx.y, reinterpret_cast<int*>(smem));
     return;
   }
   const int Kx = px.n, Ky = py.n, NP = Kx * Ky;
@@ -997,8 +999,10 @@ void launch_fft_xy_spread_t(hipStream_t s, int n_frames, const FFTPlan1D& px, co
   const int spl = multi ? S : 1;
   const int np = planes ? (Kz + spl - 1) / spl : 0;         // workgroups of planes
   size_t lds = fft_xy_spread_lds<T, T2>(px.n, py.n, spl);
-  if (bin) lds = std::max(lds, bin_lds_spread(ba.n_site, ba.cell.n_cells));
-  dim3 grid(np + (bin ? 1 : 0), n_frames);
+  if (bin)
+    lds = std::max(lds, n_frames == 1 ? bin_layers_lds<SPREAD_THREADS_ONE>(ba.n_site, ba.cell)
+                                      : bin_body_lds<SPREAD_THREADS>(ba.n_site, ba.cell.n_cells));
+  dim3 grid(np + (!bin ? 0 : n_frames == 1 ? bin_layer_wgs(ba.cell) : 1), n_frames);
   if (grid.x == 0) return;
   auto* k = n_frames == 1 ? (mi.order == 5 ? k_fft_xy_spread<T, T2, true, true, 1> : k_fft_xy_spread<T, T2, true, false, 1>)
             : multi       ? (mi.order == 5 ? k_fft_xy_spread<T, T2, false, true, S> : k_fft_xy_spread<T, T2, false, false, S>)

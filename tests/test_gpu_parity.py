@@ -191,6 +191,40 @@ def test_step_parity_odd_site_count(torch_dev):
     w = dataclasses.replace(w0, kspace="pppm", site_xyz=w0.site_xyz[:, :99].copy(), site_q=q)
     check_step(torch_dev, w, A, S)
 
+@pytest.mark.parametrize("lz,crowded", [(1.3, False), (2.5, False), (3.7, False), (9.7, False), (10.3, False),
+                                        (20.1, False), (20.1, True)])
+@pytest.mark.parametrize("n_site", [2, 1026, 4098])
+def test_binning_by_z_layers(torch_dev, lz, crowded, n_site):
+    """1, 2, 6, 16, 17 and 33 z layers over at most 16 workgroups; all sites in
+    one layer (more than a wavefront holds in registers), one site or less per
+    wavefront."""
+    import dataclasses
+    _say(f"[gpu] binning lz={lz} n_site={n_site} crowded={crowded}")
+    from paper_2201_12963_amd import binding
+    from workloads import make_workload
+    w = make_workload("tiny", "ff")
+    rng = np.random.default_rng(int(10 * lz) + n_site)
+    box = np.array([w.box[0], w.box[1], lz])
+    keep = [0, w.n_elec - 1]
+    elec = w.elec_xyz[:, keep].copy()
+    elec[2] = (0.2, 0.6 * lz)
+    xyz = rng.uniform(0.0, 1.0, (3, n_site)) * box[:, None]
+    if crowded:
+        xyz[2] = rng.uniform(8.0, 8.05, n_site)
+    w = dataclasses.replace(w, box=box, kspace="pppm", mesh=(16, 16, 32), elec_xyz=np.ascontiguousarray(elec),
+                            elec_side=w.elec_side[keep], site_xyz=xyz + box[:, None] * rng.integers(-1, 2, xyz.shape),
+                            site_q=np.tile([0.5, -0.5], n_site // 2))
+    ctx, stream = gpu_context(torch_dev, w)
+    x = torch_dev.tensor(w.site_xyz, dtype=torch_dev.float64, device="cuda")
+    with torch_dev.cuda.stream(stream):
+        ctx.solve(x, 1.0)
+    stream.synchronize()
+    _, start, order = cells.bin_sites(w.site_xyz, w.box, w.rcut)
+    assert np.array_equal(ctx.get_buffer(binding.BUF_NCELL), np.array(cells.cell_grid(w.box, w.rcut)))
+    assert np.array_equal(ctx.get_buffer(binding.BUF_CELL_START), start)
+    assert np.array_equal(ctx.get_buffer(binding.BUF_SITE_ORDER), order)
+    ctx.close()
+
 
 def check_step(torch, w, A, S):
     es = cpm.Electrostatics(w, oracle_method(w))
