@@ -669,50 +669,92 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
       }
     }
   };
-  // Staging, wavefront by wavefront, by the first SPREAD_THREADS threads
-  // (in a one-frame workgroup the others wait at the barrier: more
-  // wavefronts only thin out the lists): a thread reads the z of SB sites
-  // (the loads issued together); those whose stencil reaches the plane go to
-  // the wavefront's own list (ballot and prefix count: no atomics and no
-  // workgroup barrier), which the wavefront then works through with all its
-  // lanes, so that every wavefront shares the weights and the atomics.
+  // the plane slot of site z (P: not reached), and whether the workgroup's
+  // planes are reached (several planes: the stencil reaches the first one, or
+  // wraps past Kz into one of the others)
+  auto slot = [&](double zj) -> int {
+    if (!isfinite(zj)) zj = 0.0;
+    int fz = spline_first(wrap(zj, Lz, rLz) * ihz, P);
+    fz = ((fz % Kz) + Kz) % Kz;
+    const int tz = iz - fz;
+    return tz + ((tz < 0) ? Kz : 0);
+  };
+  auto reached = [&](int tz) { return tz < P || (SPL > 1 && tz > Kz - npl); };
   const int lane = threadIdx.x & (WAVE - 1);
-  constexpr int NT = SPREAD_THREADS;
+  constexpr int NT = ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS;
   constexpr int SB = SPREAD_LIST / NT;
-  int* wl = list + (threadIdx.x / WAVE) * (SB * WAVE);
   const unsigned long long lt = (1ull << lane) - 1ull;
-  if (threadIdx.x < NT)
-  for (int base = 0; base < n; base += SPREAD_LIST) {
-    double zv[SB];
+  // Staging, SPREAD_LIST sites at a time: a thread reads the z of SB sites
+  // (the loads issued together) and those whose stencil reaches the plane are
+  // listed (ballots and prefix counts).
+  if constexpr (ONE) {
+    // one frame: one list for the workgroup (an LDS counter update per
+    // wavefront), which all threads then work through, so that the 16
+    // wavefronts share the scan and full wavefronts the weights and atomics
+    // (four wavefronts with a list each: the launch 17.9 us at 5120 sites on
+    // 36 x 36 planes, 14.4 like this)
+    __shared__ int n_hit;
+    for (int base = 0; base < n; base += SPREAD_LIST) {
+      if (threadIdx.x == 0) n_hit = 0;
+      double zv[SB];
 #pragma unroll
-    for (int u = 0; u < SB; ++u) {
-      const int j = base + u * NT + (int)threadIdx.x;
-      zv[u] = j < n ? sz[j] : 0.0;
-    }
-    int cnt = 0;
-#pragma unroll
-    for (int u = 0; u < SB; ++u) {
-      const int j = base + u * NT + (int)threadIdx.x;
-      int tz = P;
-      if (j < n) {
-        double zj = zv[u];
-        if (!isfinite(zj)) zj = 0.0;
-        int fz = spline_first(wrap(zj, Lz, rLz) * ihz, P);
-        fz = ((fz % Kz) + Kz) % Kz;
-        tz = iz - fz;
-        tz += (tz < 0) ? Kz : 0;
+      for (int u = 0; u < SB; ++u) {
+        const int j = base + u * NT + (int)threadIdx.x;
+        zv[u] = j < n ? sz[j] : 0.0;
       }
-      // (several planes: the stencil reaches the first one, or wraps past
-      // Kz into one of the others)
-      const bool hit = j < n && (tz < P || (SPL > 1 && tz > Kz - npl));
-      const unsigned long long m = __ballot(hit);
-      if (hit) wl[cnt + __popcll(m & lt)] = SPL == 1 ? j * 8 + tz : j;   // site (and its z weight slot)
-      cnt += __popcll(m);
+      __syncthreads();                                     // counter cleared, earlier list worked through
+      int ent[SB];
+      unsigned long long hits[SB];
+      int cnt = 0;
+#pragma unroll
+      for (int u = 0; u < SB; ++u) {
+        const int j = base + u * NT + (int)threadIdx.x;
+        int tz = P;
+        if (j < n) tz = slot(zv[u]);                       // (skipped by wavefronts past the end)
+        ent[u] = j * 8 + tz;                               // site and its z weight slot
+        hits[u] = __ballot(j < n && reached(tz));
+        cnt += __popcll(hits[u]);
+      }
+      int at = 0;
+      if (cnt > 0) {
+        if (lane == 0) at = atomicAdd(&n_hit, cnt);
+        at = __builtin_amdgcn_readfirstlane(at);
+      }
+#pragma unroll
+      for (int u = 0; u < SB; ++u) {
+        if (hits[u] >> lane & 1) list[at + __popcll(hits[u] & lt)] = ent[u];
+        at += __popcll(hits[u]);
+      }
+      __syncthreads();
+      for (int e = threadIdx.x; e < n_hit; e += NT) add_site(list[e]);
     }
-    // a wavefront's LDS operations complete in order: its lanes see the list
-    __builtin_amdgcn_wave_barrier();
-    for (int e = lane; e < cnt; e += WAVE) add_site(wl[e]);
-    __builtin_amdgcn_wave_barrier();                      // list read before the next batch writes it
+  } else {
+    // many frames: a list per wavefront, which needs no workgroup barrier
+    // (a shared list measured 5% slower here, where workgroups overlap)
+    int* wl = list + (threadIdx.x / WAVE) * (SB * WAVE);
+    for (int base = 0; base < n; base += SPREAD_LIST) {
+      double zv[SB];
+#pragma unroll
+      for (int u = 0; u < SB; ++u) {
+        const int j = base + u * NT + (int)threadIdx.x;
+        zv[u] = j < n ? sz[j] : 0.0;
+      }
+      int cnt = 0;
+#pragma unroll
+      for (int u = 0; u < SB; ++u) {
+        const int j = base + u * NT + (int)threadIdx.x;
+        int tz = P;
+        if (j < n) tz = slot(zv[u]);
+        const bool hit = j < n && reached(tz);
+        const unsigned long long m = __ballot(hit);
+        if (hit) wl[cnt + __popcll(m & lt)] = SPL == 1 ? j * 8 + tz : j;   // site (and its z weight slot)
+        cnt += __popcll(m);
+      }
+      // a wavefront's LDS operations complete in order: its lanes see the list
+      __builtin_amdgcn_wave_barrier();
+      for (int e = lane; e < cnt; e += WAVE) add_site(wl[e]);
+      __builtin_amdgcn_wave_barrier();                    // list read before the next batch writes it
+    }
   }
   __syncthreads();
   const size_t off = ((size_t)frame * Kz + iz) * NP;        // the workgroup's planes are contiguous
