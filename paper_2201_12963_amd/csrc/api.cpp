@@ -128,6 +128,8 @@ struct cpm_ctx {
   // given charges with the kept spectrum: the field pass then transforms the
   // electrolyte and electrode spectra summed, and no b is needed)
   bool fold_pot = false;
+  // set by enqueue_b when its explicit-Ewald launch took the site-site sums
+  bool pairs_made = false;
   // the MD loop's Lennard-Jones sums to ride in its field pass (set by the
   // loop around its force enqueue), and whether they did
   const MDArgs* host_lj = nullptr;
@@ -148,7 +150,7 @@ struct cpm_ctx {
 
   // ---- explicit Ewald
   int nk = 0;
-  double *d_kv = nullptr, *d_ew = nullptr, *d_Esite = nullptr;
+  double *d_kv = nullptr, *d_ew = nullptr;
   double2 *d_eph = nullptr, *d_rhok = nullptr, *d_rhok_all = nullptr;
 
   // ---- most recent launch of each step kernel, for timing (cpm_replay_kernel)
@@ -442,7 +444,6 @@ int alloc_frames(cpm_ctx* c, int nf) {
     TRY(dalloc(c, &c->d_ek, (size_t)nf * c->nk));
     TRY(dalloc(c, &c->d_rhok, (size_t)nf * c->nk));
     TRY(dalloc(c, &c->d_rhok_all, (size_t)nf * c->nk));
-    TRY(dalloc(c, &c->d_Esite, (size_t)nf * 3 * ns));
   }
   HIP_TRY(c, hipDeviceSynchronize());
   c->cap_frames = nf;
@@ -503,6 +504,22 @@ template <> struct Bufs<float> {
   static const float* gw(cpm_ctx* c) { return c->d_gwf; }
   static const float* val(cpm_ctx* c) { return c->d_valf; }
 };
+
+// the site-site sums of nf frames: one frame, a wavefront per site (short
+// chains, all in flight at once); many frames, cell tiles
+template <typename T>
+PairArgs<T> pair_args(cpm_ctx* c, int nf) {
+  PairArgs<T> pa{};
+  pa.tsplit = nf == 1 ? 0 : c->pair_tsplit;
+  pa.n_blocks = c->n_site == 0 ? 0 : pa.tsplit > 0 ? c->cell.n_cells * pa.tsplit : (c->n_site + 3) / 4;
+  pa.cell = c->cell;
+  pa.st = Bufs<T>::sites(c);
+  pa.alpha = (T)c->alpha;
+  pa.rc2 = c->rcut * c->rcut;
+  pa.f_pair = c->d_fpair;
+  pa.u_site = c->d_usite;
+  return pa;
+}
 
 // Stage 1: positions -> binned sites -> b (frames 0..nf-1).  With PPPM the
 // binning runs as one more workgroup per frame of the first mesh launch (the
@@ -580,15 +597,19 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
                            slab_terms(c));
     });
   } else {
-    rec(c, CPM_KERNEL_BIN, s, [=](hipStream_t s) { launch_bin_sites(s, ba); });
-    SiteSet<double> sd = Bufs<double>::sites(c);
-    if (!need_b) {
-      launch_ewald_sf(s, nf, c->nk, c->d_kv, c->d_ew, sd, c->d_rhok, c->d_ek);
-      return CPM_OK;
+    // (one frame, FP64) the binning beside the structure factor, then b
+    // beside the site-site sums; each timed alone through the kernel of its own
+    rec(c, CPM_KERNEL_BIN, s, [=](hipStream_t s) {
+      launch_ewald_sf(s, ba, true, c->nk, c->d_kv, c->d_ew, c->d_rhok, c->d_ek);
+    });
+    keep(c, CPM_KERNEL_BIN, [=](hipStream_t s) { launch_bin_sites(s, ba); });
+    c->pairs_made = need_b && forces;
+    if (!need_b) return CPM_OK;
+    if constexpr (!std::is_same<T, float>::value) {
+      const PairArgs<double> pa = pair_args<double>(c, nf);
+      launch_ewald_b(s, c->nk, c->d_ew, c->d_eph, c->d_rhok, rb, c->d_b, slab_terms(c), forces ? &pa : nullptr);
     }
-    rec(c, CPM_KERNEL_REAL_B, s, [=](hipStream_t s) { launch_real_b_t<T>(s, nf, rb); });
-    launch_ewald_sf(s, nf, c->nk, c->d_kv, c->d_ew, sd, c->d_rhok, c->d_ek);
-    launch_ewald_phi(s, nf, c->nk, c->n_elec, c->d_ew, c->d_eph, c->d_rhok, c->d_phir, c->d_b, slab_terms(c));
+    keep(c, CPM_KERNEL_REAL_B, [=](hipStream_t s) { launch_real_b_t<T>(s, nf, rb); });
   }
   return CPM_OK;
 }
@@ -619,17 +640,7 @@ int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const
   // by a launch of its own (explicit Ewald)
   const SlabTerms sl = slab_terms(c);
   fa.field_frame = c->geometry == CPM_SLAB ? c->d_slabfield : nullptr;
-  PairArgs<T> pa{};
-  // one frame: a wavefront per site (short chains, all in flight at once);
-  // many frames: cell tiles
-  pa.tsplit = nf == 1 ? 0 : c->pair_tsplit;
-  pa.n_blocks = c->n_site == 0 ? 0 : pa.tsplit > 0 ? c->cell.n_cells * pa.tsplit : (c->n_site + 3) / 4;
-  pa.cell = c->cell;
-  pa.st = st;
-  pa.alpha = fa.alpha;
-  pa.rc2 = fa.rc2;
-  pa.f_pair = c->d_fpair;
-  pa.u_site = c->d_usite;
+  PairArgs<T> pa = pair_args<T>(c, nf);
   if (pa.tsplit > 0) {
     // tiles run after the charge solve: they take the site-electrode pairs
     // too, and the site-force kernel then skips its own electrode walk
@@ -694,7 +705,6 @@ int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const
     const size_t M = c->mi.M;
     fa.Ea = E;
     fa.Ea_frame_stride = 3 * M;
-    fa.Esite = nullptr;
     if (nf > 1 && fa.f_elec && c->mi.order == 5) {
       // many frames, with the site-electrode sums in the tiles (order 5):
       // the inverse pass interpolates the field at the sites plane by plane
@@ -719,13 +729,25 @@ int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const
       });
     }
   } else {
-    rec(c, CPM_KERNEL_SITE_PAIRS, s, [=](hipStream_t s) { launch_site_pairs_t<T>(s, nf, pa); });
+    if (c->pairs_made)       // (beside b; timed alone through the stand-alone kernel with the same body)
+      keep(c, CPM_KERNEL_SITE_PAIRS, [=](hipStream_t s) { launch_site_pairs_t<T>(s, nf, pa); });
+    else
+      rec(c, CPM_KERNEL_SITE_PAIRS, s, [=](hipStream_t s) { launch_site_pairs_t<T>(s, nf, pa); });
     if (fa.field_frame) launch_slab_field(s, nf, sl, qa, qa_stride, c->d_slabfield);
-    SiteSet<double> sd = Bufs<double>::sites(c);
-    launch_ewald_rho_all(s, nf, c->nk, c->n_elec, c->d_eph, qa, qa_stride, c->d_rhok, c->d_rhok_all);
-    launch_ewald_field(s, nf, c->nk, c->d_kv, c->d_ew, sd, c->d_rhok_all, c->d_Esite);
-    fa.Ea = nullptr;
-    fa.Esite = c->d_Esite;
+    launch_ewald_rho_all(s, c->nk, c->n_elec, c->d_eph, qa, c->d_rhok, c->d_rhok_all);
+    if constexpr (!std::is_same<T, float>::value) {
+      const EwaldField ef{c->nk, c->d_kv, c->d_ew, c->d_rhok_all};
+      const EnergyArgs e = ea ? *ea : EnergyArgs{};
+      const bool we = ea != nullptr;
+      rec(c, CPM_KERNEL_SITE_FORCES, s, [=](hipStream_t s) {
+        launch_site_forces_ewald(s, c->cell, B::elec(c), st, fa, ef, true, we ? &e : nullptr);
+      });
+      if (we)
+        keep(c, CPM_KERNEL_ENERGY, [=](hipStream_t s) {
+          launch_site_forces_ewald(s, c->cell, B::elec(c), st, fa, ef, false, &e);
+        });
+    }
+    return CPM_OK;
   }
   const bool with_e = ea != nullptr;
   const EnergyArgs e = with_e ? *ea : EnergyArgs{};

@@ -212,9 +212,6 @@ struct ForceArgs {
   const T* Ea; size_t Ea_frame_stride;
   const T* Eb;
   MeshInfo mi;
-  // explicit-Ewald path instead of a mesh: k-space field at the sites,
-  // [frame][3][n_site] in cell-sorted order (V/nm), or nullptr
-  const double* Esite;
   // electrode charges, original order: qa per frame (stride n_elec), qb shared;
   // the same in the electrodes' cell-sorted order (what the pair walk reads)
   const double* qa; size_t qa_frame_stride;
@@ -533,15 +530,21 @@ void launch_fft_xy_spread_t(hipStream_t s, int n_frames, const FFTPlan1D& px, co
                             const MeshInfo& mi, const BinArgs& ba, T* rho_out, T2* out_c, bool planes = true,
                             bool bin = false);
 
-// explicit Ewald (k_ewald.hip)
-void launch_ewald_sf(hipStream_t s, int n_frames, int nk, const double* kv, const double* ew,
-                     const SiteSet<double>& st, double2* rho, double* ek);
-void launch_ewald_phi(hipStream_t s, int n_frames, int nk, int n_elec, const double* ew, const double2* eph,
-                      const double2* rho, const double* phi_real, double* b, const SlabTerms& sl = SlabTerms{});
-void launch_ewald_rho_all(hipStream_t s, int n_frames, int nk, int n_elec, const double2* eph, const double* q,
-                          size_t q_stride, const double2* rho, double2* out);
-void launch_ewald_field(hipStream_t s, int n_frames, int nk, const double* kv, const double* ew,
-                        const SiteSet<double>& st, const double2* rho, double* E);
+// explicit Ewald (k_ewald.hip), one frame: the structure factor and (bin) the
+// binning of the same positions; b and (pa) the site-site sums
+void launch_ewald_sf(hipStream_t s, const BinArgs& ba, bool bin, int nk, const double* kv, const double* ew,
+                     double2* rho, double* ek);
+void launch_ewald_b(hipStream_t s, int nk, const double* ew, const double2* eph, const double2* rho,
+                    const RealBArgs<double>& rb, double* b, const SlabTerms& sl, const PairArgs<double>* pa);
+void launch_ewald_rho_all(hipStream_t s, int nk, int n_elec, const double2* eph, const double* q, const double2* rho,
+                          double2* out);
+struct EwaldField {            // the k-space field's sum over the k-vectors, at the sites
+  int nk;
+  const double *kv, *ew;
+  const double2* rho;          // of all charges
+};
+void launch_site_forces_ewald(hipStream_t s, const Cell& cell, const ElecSet<double>& el, const SiteSet<double>& st,
+                              const ForceArgs<double>& fa, const EwaldField& ef, bool forces, const EnergyArgs* ea);
 
 // dense linear algebra (k_linalg.hip)
 constexpr int GJ_BLOCK = 32;

@@ -72,20 +72,28 @@ size_t site_pairs_lds(int tsplit, bool n3) {
 }
 
 
+constexpr int EWALD_FORCE_THREADS = 512;
+
 // The rest of the force on every site, once the electrode charges are known
 // (one-frame launches; many-frame ones take k_site_forces_g16 below): pairs
 // with the electrode Gaussians (g1), walked here; the k-space field,
 // interpolated from the mesh with the site's B-spline weights (three lanes
 // build the weights of one axis each in LDS, then the lanes run over the P^3
-// points) or taken from the explicit Ewald sum; the site-site sum of
+// points) or summed over the k-vectors (explicit Ewald); the site-site sum of
 // k_site_pairs; the applied field.  One wavefront per site (or two, see
 // below).  Workgroups from n_force_blocks on reduce the energies of their
 // frame instead (they read nothing this kernel writes, so they run beside
 // the force workgroups).
-template <typename T, bool TWO>
-__global__ __launch_bounds__(256) void k_site_forces(Cell cell, ElecSet<T> el, SiteSet<T> st,
-                                                     ForceArgs<T> fa, int n_force_blocks, EnergyArgs en,
-                                                     int walk_parts) {
+//
+// EWALD (explicit Ewald, one frame): a workgroup per site, whose first
+// wavefront does all of the above but the field, while the others sum the
+// field over the k-vectors (a sincos each: 16 us for a wavefront per site
+// over 1327 of them).
+// (the body; k_site_forces and k_site_forces_ewald below are its launches)
+template <typename T, bool TWO, bool EWALD>
+__device__ __forceinline__ void site_forces_body(const Cell& cell, const ElecSet<T>& el, const SiteSet<T>& st,
+                                                 const ForceArgs<T>& fa, int n_force_blocks, const EnergyArgs& en,
+                                                 int walk_parts, const EwaldField* ef) {
   int bx = blockIdx.x, frame = blockIdx.y;
   if (gridDim.y > 1) {
     // many frames: each XCD takes a contiguous range of whole frames, so a
@@ -100,18 +108,37 @@ __global__ __launch_bounds__(256) void k_site_forces(Cell cell, ElecSet<T> el, S
     energy_block(en, frame);
     return;
   }
-  __shared__ __align__(16) unsigned char scratch[4 * wave_scratch_bytes<T>()];
-  __shared__ T wsp[4][3][MAX_ORDER];
-  __shared__ int fsp[4][3];
+  constexpr int WAVES = EWALD ? 1 : 4;         // wavefronts that walk
+  __shared__ __align__(16) unsigned char scratch[WAVES * wave_scratch_bytes<T>()];
+  __shared__ T wsp[WAVES][3][MAX_ORDER];
+  __shared__ int fsp[WAVES][3];
+  __shared__ double efld[EWALD ? EWALD_FORCE_THREADS / WAVE : 1][3];
   const int lane = threadIdx.x & (WAVE - 1);
   const int wv = threadIdx.x >> 6;
+  if (EWALD && wv > 0) {
+    const double x = st.x[bx], y = st.y[bx], z = st.z[bx];
+    const int nk = ef->nk;
+    double e0 = 0.0, e1 = 0.0, e2 = 0.0;
+    for (int k = (wv - 1) * WAVE + lane; k < nk; k += EWALD_FORCE_THREADS - WAVE) {
+      const double kx = ef->kv[k], ky = ef->kv[nk + k], kz = ef->kv[2 * nk + k], w = ef->ew[k];
+      const double2 r = ef->rho[k];
+      double s, c;
+      sincos(kx * x + ky * y + kz * z, &s, &c);
+      const double a = -w * (c * r.y - s * r.x);     // Im(e^{-i k.R} rho)
+      e0 += a * kx; e1 += a * ky; e2 += a * kz;
+    }
+    e0 = wave_sum(e0); e1 = wave_sum(e1); e2 = wave_sum(e2);
+    if (lane == 0) { efld[wv][0] = e0; efld[wv][1] = e1; efld[wv][2] = e2; }
+    __syncthreads();
+    return;
+  }
   // parts == 2: two wavefronts per site, each walking half of the site's
   // electrode candidates (the walk is the kernel's longest chain); the
   // second hands its sums to the first through LDS.  A wavefront past the
   // last site mirrors it, writes nothing and still meets the barrier.
-  const int parts = walk_parts;
+  const int parts = EWALD ? 1 : walk_parts;
   const int part = parts == 2 ? (wv & 1) : 0;
-  const int jw = parts == 2 ? bx * 2 + (wv >> 1) : bx * 4 + wv;
+  const int jw = EWALD ? bx : parts == 2 ? bx * 2 + (wv >> 1) : bx * 4 + wv;
   if (parts == 1 && jw >= st.n) return;
   const bool live = jw < st.n;
   const int j = live ? jw : st.n - 1;
@@ -169,11 +196,6 @@ __global__ __launch_bounds__(256) void k_site_forces(Cell cell, ElecSet<T> el, S
       if (TWO) { eb[0] += w * fa.Eb[m]; eb[1] += w * fa.Eb[M + m]; eb[2] += w * fa.Eb[2 * M + m]; }
     }
   }
-  if (fa.Esite && lane == 0 && part == 0) {
-    const double* E = fa.Esite + (size_t)frame * 3 * st.n;
-    ea[0] = (T)E[j]; ea[1] = (T)E[st.n + j]; ea[2] = (T)E[2 * st.n + j];
-  }
-
   // ---- real space: electrode Gaussians (g1)
   T fr[3] = {0, 0, 0};
   T frb[3] = {0, 0, 0};
@@ -204,6 +226,14 @@ __global__ __launch_bounds__(256) void k_site_forces(Cell cell, ElecSet<T> el, S
               });
             });
   if (lane < n) eval_g1<T, TWO>(Q, lane, fa.alpha, fa.eta, fr, frb);
+  }
+
+  if (EWALD) {
+    __syncthreads();
+    if (lane == 0)
+      for (int w = 1; w < EWALD_FORCE_THREADS / WAVE; ++w)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) ea[d] += (T)efld[w][d];
   }
 
   // ---- reduce and write
@@ -264,6 +294,30 @@ __global__ __launch_bounds__(256) void k_site_forces(Cell cell, ElecSet<T> el, S
     o[st.n + orig] = F[1] + dv * FB[1];
     o[2 * st.n + orig] = F[2] + dv * FB[2];
   }
+}
+
+// (the wavefronts per SIMD of the walking forms set which sites take two of
+// them, and so the order of their sums: held where they were)
+template <typename T, bool TWO>
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 3 : TWO ? 6 : 7) void k_site_forces(
+    Cell cell, ElecSet<T> el, SiteSet<T> st, ForceArgs<T> fa, int n_force_blocks, EnergyArgs en, int walk_parts) {
+  site_forces_body<T, TWO, false>(cell, el, st, fa, n_force_blocks, en, walk_parts, nullptr);
+}
+
+__global__ __launch_bounds__(EWALD_FORCE_THREADS) void k_site_forces_ewald(Cell cell, ElecSet<double> el,
+                                                                           SiteSet<double> st, ForceArgs<double> fa,
+                                                                           int n_force_blocks, EnergyArgs en,
+                                                                           EwaldField ef) {
+  site_forces_body<double, false, true>(cell, el, st, fa, n_force_blocks, en, 1, &ef);
+}
+
+void launch_site_forces_ewald(hipStream_t s, const Cell& cell, const ElecSet<double>& el, const SiteSet<double>& st,
+                              const ForceArgs<double>& fa, const EwaldField& ef, bool forces, const EnergyArgs* ea) {
+  const int nfb = forces ? st.n : 0;
+  const EnergyArgs e = ea ? *ea : EnergyArgs{};
+  if (nfb + (ea ? 1 : 0) == 0) return;
+  hipLaunchKernelGGL(k_site_forces_ewald, dim3(nfb + (ea ? 1 : 0)), dim3(EWALD_FORCE_THREADS), 0, s, cell, el, st, fa,
+                     nfb, e, ef);
 }
 
 // The same when the pair tiles have already made the site-electrode sums
@@ -341,9 +395,6 @@ __global__ __launch_bounds__(G16_THREADS) void k_site_forces_g16(SiteSet<T> st, 
       ea[0] += w * Ef[m]; ea[1] += w * Ef[M + m]; ea[2] += w * Ef[2 * M + m];
       if (TWO) { eb[0] += w * fa.Eb[m]; eb[1] += w * fa.Eb[M + m]; eb[2] += w * fa.Eb[2 * M + m]; }
     }
-  } else if (fa.Esite && sub == 0) {
-    const double* E = fa.Esite + (size_t)frame * 3 * st.n;
-    ea[0] = (T)E[j]; ea[1] = (T)E[st.n + j]; ea[2] = (T)E[2 * st.n + j];
   }
 #pragma unroll
   for (int off = 8; off > 0; off >>= 1) {

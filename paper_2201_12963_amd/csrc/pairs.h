@@ -348,11 +348,12 @@ __device__ __forceinline__ T g1_potential(T dx, T dy, T dz, T q, T alpha, T eta)
 
 // Real-space electrolyte potential at electrode atom g of a frame, one
 // wavefront: k_e sum_j Q_j g1(r) over the sites of the stencil cells.
-// scratch: this wavefront's LDS (wave_scratch_bytes<T>()).
+// scratch: this wavefront's LDS (wave_scratch_bytes<T>()).  Returns the value
+// (every lane) and the atom's original index.
 template <typename T>
-__device__ __forceinline__ void real_b_wave(const Cell& cell, T alpha, T eta, double rc2, const ElecSet<T>& el,
-                                            const SiteSet<T>& st, T* __restrict__ phi_out, int g, int frame,
-                                            T* scratch) {
+__device__ __forceinline__ T real_b_wave(const Cell& cell, T alpha, T eta, double rc2, const ElecSet<T>& el,
+                                         const SiteSet<T>& st, T* __restrict__ phi_out, int g, int frame,
+                                         T* scratch, int* orig = nullptr) {
   const int lane = threadIdx.x & (WAVE - 1);
   const size_t fo = (size_t)frame * st.n;
   const double* sx = st.x + fo; const double* sy = st.y + fo; const double* sz = st.z + fo;
@@ -388,6 +389,8 @@ __device__ __forceinline__ void real_b_wave(const Cell& cell, T alpha, T eta, do
   if (lane < n) acc += g1_potential(Q.x[lane], Q.y[lane], Q.z[lane], Q.a[lane], alpha, eta);
   acc = wave_sum(acc);
   if (lane == 0) phi_out[(size_t)frame * el.n + og] = (T)KE * acc;
+  if (orig) *orig = og;
+  return (T)KE * acc;
 }
 
 // ------------------------------------------------------------ site forces

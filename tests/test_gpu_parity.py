@@ -191,6 +191,17 @@ def test_step_parity_odd_site_count(torch_dev):
     w = dataclasses.replace(w0, kspace="pppm", site_xyz=w0.site_xyz[:, :99].copy(), site_q=q)
     check_step(torch_dev, w, A, S)
 
+@pytest.mark.parametrize("n_site,kcut", [(2, 24.0), (6, 7.0), (98, 11.3)])
+def test_step_parity_ewald_counts(torch_dev, n_site, kcut):
+    """Explicit Ewald with few sites (fewer than a workgroup of the site-site
+    sums) and k-vector counts that do not fill the last workgroups."""
+    import dataclasses
+    _say(f"[gpu] step tiny ff with Ewald, {n_site} sites, kcut {kcut}")
+    w0, A, S = built("tiny", "ff")
+    w = dataclasses.replace(w0, kcut=kcut, site_xyz=w0.site_xyz[:, :n_site].copy(), site_q=w0.site_q[:n_site].copy())
+    check_step(torch_dev, w, A, S)
+
+
 @pytest.mark.parametrize("lz,crowded", [(1.3, False), (2.5, False), (3.7, False), (9.7, False), (10.3, False),
                                         (20.1, False), (20.1, True)])
 @pytest.mark.parametrize("n_site", [2, 1026, 4098])
