@@ -395,7 +395,8 @@ int alloc_frames(cpm_ctx* c, int nf) {
   }
   TRY(dalloc(c, &c->d_phir, (size_t)nf * ne));
   TRY(dalloc(c, &c->d_zdip, (size_t)nf));
-  TRY(dalloc(c, &c->d_fpair, (size_t)nf * 3 * ns));
+  // (u_site follows f_pair: the pair tiles clear both in one launch)
+  TRY(dalloc(c, &c->d_fpair, (size_t)nf * 4 * ns));
   TRY(dalloc(c, &c->d_wrap, (size_t)nf * 3 * ns));
   TRY(dalloc(c, &c->d_b, (size_t)nf * ne));
   TRY(dalloc(c, &c->d_Q0, (size_t)nf * ne));
@@ -405,7 +406,7 @@ int alloc_frames(cpm_ctx* c, int nf) {
   TRY(dalloc(c, &c->d_qa, (size_t)nf * ne));
   TRY(dalloc(c, &c->d_qs, (size_t)nf * ne));
   if (mixed) TRY(dalloc(c, &c->d_bsplit, (size_t)3 * nf * c->n_pad));
-  TRY(dalloc(c, &c->d_usite, (size_t)nf * ns));
+  c->d_usite = c->d_fpair + (size_t)nf * 3 * ns;
   TRY(dalloc(c, &c->d_ftmp, (size_t)nf * 3 * ns));
   TRY(dalloc(c, &c->d_fcomp, (size_t)nf * 6 * ns));
   TRY(dalloc(c, &c->d_felec, (size_t)nf * 6 * ns));
@@ -881,13 +882,13 @@ int enqueue_batch(cpm_ctx* c, int nf, const double* xyz, int n_dv, double* q_out
     launch_reproject(s, nf, n, c->d_sub1, c->d_Q0);
   } else {
     rec(c, CPM_KERNEL_GEMM, s, [=](hipStream_t s) {
-      launch_gemm_nt(s, nf, n, n, 1.0, c->d_b, n, c->d_S, n, 0.0, c->d_Q0, n);
+      launch_gemm_nt(s, nf, n, n, c->d_b, n, c->d_S, n, c->d_Q0, n);
     });
   }
   rec(c, CPM_KERNEL_EXPAND_Q, s, [=](hipStream_t s) {
-    launch_expand_charges(s, nf, n, n_dv, c->d_dv, c->d_Q0, c->d_Sc, q_out);
+    launch_expand_charges(s, nf, n, n_dv, c->d_dv, c->d_Q0, c->d_Sc, q_out, c->d_epos,
+                          need_forces ? c->d_qs : nullptr);
   });
-  if (f_out || e_out) launch_permute(s, nf, n, c->d_epos, c->d_Q0, c->d_qs);
   if (need_forces) {
     ForceArgs<T> fa{};
     fa.out_scale = 1.0;

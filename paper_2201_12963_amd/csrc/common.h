@@ -552,8 +552,9 @@ void launch_elastance_real(hipStream_t s, int n, const double* ex, const double*
                            const Cell& cell, double alpha, double eta, double rcut, double self_term, double* A);
 void launch_phase_matrix(hipStream_t s, int n, int nkc, int k0, int nk, const double* kv, const double* sk,
                          const double* ex, const double* ey, const double* ez, double* C);
-void launch_gemm_nt(hipStream_t s, int M, int N, int K, double alpha, const double* A, int lda, const double* B,
-                    int ldb, double beta, double* D, int ldd);
+// D[M][N] = A[M][K] B[N][K]^T
+void launch_gemm_nt(hipStream_t s, int M, int N, int K, const double* A, int lda, const double* B, int ldb, double* D,
+                    int ldd);
 // D = beta D + alpha A A^T (D square), only half of the products formed
 void launch_syrk_nt(hipStream_t s, int M, int K, double alpha, const double* A, int lda, double beta, double* D,
                     int ldd);
@@ -577,8 +578,10 @@ void launch_charges(hipStream_t s, int n_frames, int n, const double* S, const d
                     double* Q0, double* q, const int* epos = nullptr, double* qs = nullptr);
 // dst[f][epos[i]] = src[f][i] for n values of n_frames frames
 void launch_permute(hipStream_t s, int n_frames, int n, const int* epos, const double* src, double* dst);
+// the charges of every (frame, dV); qs (or nullptr): the frames' charges at
+// dV = 0 in the electrodes' cell-sorted order (positions epos)
 void launch_expand_charges(hipStream_t s, int n_frames, int n_elec, int n_dv, const double* dv, const double* Q0,
-                           const double* Sc, double* q);
+                           const double* Sc, double* q, const int* epos, double* qs);
 // out[f][v][k] = comp[f][0][k] + dv[v] comp[f][1][k] over the 3 n_site
 // values k of every frame f and dV v
 void launch_expand_forces(hipStream_t s, int n_frames, int n_site, int n_dv, const double* dv, const double* comp,

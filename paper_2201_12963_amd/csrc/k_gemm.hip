@@ -139,6 +139,65 @@ __global__ __launch_bounds__(256) void k_gemm_f64_mfma(int M, int N, int K, doub
       }
 }
 
+// The same product where its 64 x 64 tiles would leave most of the chip idle
+// (few frames): a 16 x 16 tile per workgroup, whose GS_WAVES wavefronts take a
+// share of K each and join their blocks through LDS.  Operands come straight
+// from global memory, two consecutive k per lane and load (the two MFMAs of a
+// step take the even and the odd ones), GS_AHEAD steps in flight.  Bound by
+// the latency of one wavefront's K / GS_WAVES chain: 37 frames of 936 atoms
+// take 15 tiles of 64 x 64 and 57 us, or 177 small ones.
+constexpr int GS_TILE = 16, GS_WAVES = 8, GS_AHEAD = 4;
+constexpr int GS_MAX_TILES = 64;           // 64 x 64 tiles up to which this form is taken
+
+__global__ __launch_bounds__(GS_WAVES * 64) void k_gemm_f64_small(int M, int N, int K, const double* __restrict__ A,
+                                                                  int lda, const double* __restrict__ B, int ldb,
+                                                                  double* __restrict__ D, int ldd) {
+  __shared__ double red[GS_WAVES][GS_TILE * GS_TILE];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = blockIdx.y * GS_TILE, n0 = blockIdx.x * GS_TILE;
+  const int r = lane & 15, kq = lane >> 4;
+  // rows past the end repeat the last one (their results are not stored)
+  const double* a = A + (size_t)min(m0 + r, M - 1) * lda;
+  const double* b = B + (size_t)min(n0 + r, N - 1) * ldb;
+  const int steps = (K + 7) / 8;                       // of 8 k: lane quarter kq has k = 8 s + 2 kq and the next
+  const int s0 = steps * wave / GS_WAVES, s1 = steps * (wave + 1) / GS_WAVES;
+  const bool vec = ((lda | ldb) & 1) == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15) == 0;
+  double2 av[GS_AHEAD], bv[GS_AHEAD];
+  auto load = [&](int s, double2& x, double2& y) {
+    const int k = 8 * s + 2 * kq;
+    x = y = double2{0.0, 0.0};
+    if (s >= s1) return;
+    if (vec && k + 1 < K) {
+      x = *reinterpret_cast<const double2*>(a + k);
+      y = *reinterpret_cast<const double2*>(b + k);
+    } else {
+      if (k < K) { x.x = a[k]; y.x = b[k]; }
+      if (k + 1 < K) { x.y = a[k + 1]; y.y = b[k + 1]; }
+    }
+  };
+  double4_t acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int u = 0; u < GS_AHEAD; ++u) load(s0 + u, av[u], bv[u]);
+  for (int s = s0; s < s1; s += GS_AHEAD) {
+#pragma unroll
+    for (int u = 0; u < GS_AHEAD; ++u) {
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].x, bv[u].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u].y, bv[u].y, acc, 0, 0, 0);
+      load(s + u + GS_AHEAD, av[u], bv[u]);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) red[wave][(4 * t + kq) * GS_TILE + r] = acc[t];
+  __syncthreads();
+  for (int e = threadIdx.x; e < GS_TILE * GS_TILE; e += GS_WAVES * 64) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < GS_WAVES; ++w) v += red[w][e];
+    const int gm = m0 + e / GS_TILE, gn = n0 + e % GS_TILE;
+    if (gm < M && gn < N) D[(size_t)gm * ldd + gn] = v;
+  }
+}
+
 // ------------------------------------------------ elastance, k space by heights
 
 // For electrode atoms that share a few heights z_h (flat sheets) the k-space
@@ -352,11 +411,15 @@ __global__ __launch_bounds__(256) void k_gemm_bf16x6_mfma(int M, int N, int K, c
       }
 }
 
-void launch_gemm_nt(hipStream_t s, int M, int N, int K, double alpha, const double* A, int lda, const double* B,
-                    int ldb, double beta, double* D, int ldd) {
+void launch_gemm_nt(hipStream_t s, int M, int N, int K, const double* A, int lda, const double* B, int ldb, double* D,
+                    int ldd) {
   if (M <= 0 || N <= 0) return;
-  hipLaunchKernelGGL(k_gemm_f64_mfma<false>, dim3((N + G64_TILE - 1) / G64_TILE, (M + G64_TILE - 1) / G64_TILE), dim3(256), 0,
-                     s, M, N, K, alpha, A, lda, B, ldb, beta, D, ldd);
+  const dim3 grid((N + G64_TILE - 1) / G64_TILE, (M + G64_TILE - 1) / G64_TILE);
+  if (grid.x * grid.y <= GS_MAX_TILES)
+    hipLaunchKernelGGL(k_gemm_f64_small, dim3((N + GS_TILE - 1) / GS_TILE, (M + GS_TILE - 1) / GS_TILE),
+                       dim3(GS_WAVES * 64), 0, s, M, N, K, A, lda, B, ldb, D, ldd);
+  else
+    hipLaunchKernelGGL(k_gemm_f64_mfma<false>, grid, dim3(256), 0, s, M, N, K, 1.0, A, lda, B, ldb, 0.0, D, ldd);
 }
 
 void launch_syrk_nt(hipStream_t s, int M, int K, double alpha, const double* A, int lda, double beta, double* D,

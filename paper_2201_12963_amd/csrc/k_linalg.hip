@@ -377,16 +377,19 @@ __device__ double block_sum(double v, double* red) {
 }
 
 
-// q[f][v][i] = Q0[f][i] + dv[v] Sc[i]
+// q[f][v][i] = Q0[f][i] + dv[v] Sc[i], and qs[f][epos[i]] = Q0[f][i] (the
+// charges the force pass reads, in the electrodes' cell-sorted order)
 __global__ __launch_bounds__(256) void k_expand_charges(int n_elec, int n_dv, const double* __restrict__ dv,
                                                         const double* __restrict__ Q0, const double* __restrict__ Sc,
-                                                        double* __restrict__ q) {
+                                                        double* __restrict__ q, const int* __restrict__ epos,
+                                                        double* __restrict__ qs) {
   // a thread takes atom i of frame f over the whole sweep (its two inputs
   // read once, every store a run of consecutive atoms)
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int f = blockIdx.y;
   if (i >= n_elec) return;
   const double a = Q0[(size_t)f * n_elec + i], b = Sc[i];
+  if (qs) qs[(size_t)f * n_elec + epos[i]] = a;
   double* o = q + (size_t)f * n_dv * n_elec + i;
   for (int v = 0; v < n_dv; ++v) o[(size_t)v * n_elec] = a + dv[v] * b;
 }
@@ -508,9 +511,9 @@ void launch_expand_forces(hipStream_t s, int n_frames, int n_site, int n_dv, con
   hipLaunchKernelGGL(k_expand_forces, dim3((n3 + 255) / 256, n_frames), dim3(256), 0, s, n3, n_dv, dv, comp, out);
 }
 void launch_expand_charges(hipStream_t s, int n_frames, int n_elec, int n_dv, const double* dv, const double* Q0,
-                           const double* Sc, double* q) {
+                           const double* Sc, double* q, const int* epos, double* qs) {
   hipLaunchKernelGGL(k_expand_charges, dim3((n_elec + 255) / 256, n_frames), dim3(256), 0, s, n_elec, n_dv, dv, Q0, Sc,
-                     q);
+                     q, epos, qs);
 }
 
 }  // namespace cpm

@@ -11,6 +11,7 @@
 // mesh point, and the potential at an atom one reduced dot product over its
 // P^3 points.  Many frames share each table read: the spread stages the
 // charges of up to 8 frames in LDS, the gather gives every lane 8 frames.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -57,7 +58,11 @@ __global__ __launch_bounds__(256) void k_spread_elec(int n_touch, const int* __r
 constexpr int SPREAD_FRAMES_THREADS = 512;
 constexpr int SPREAD_FRAMES_LDS = 64 * 1024;     // staged charges of 8 frames at most, bytes
 constexpr int SPREAD_FRAMES_LDS_MAX = 128 * 1024;  // of 4 or 2 frames (one workgroup per CU)
-constexpr int SPREAD_FRAMES_CHUNKS = 4;          // point chunks (workgroups per frame group)
+// point chunks (workgroups per frame group): 4 where the groups fill the chip
+// (1, 8 and 16 were slower there); with fewer, as many as make two workgroups
+// per CU, each of at least one point per thread group (37 frames, 936 atoms:
+// 59 us with 4 chunks, 12 with 63)
+constexpr int SPREAD_FRAMES_CHUNKS = 4, SPREAD_FRAMES_WGS = 512;
 
 template <typename T, int F>
 __global__ __launch_bounds__(SPREAD_FRAMES_THREADS) void k_spread_elec_frames(
@@ -108,17 +113,18 @@ __global__ __launch_bounds__(256) void k_gather_b(int n_elec, int P3, const int*
 }
 
 // The same for many frames: 16 lanes per atom, four atoms per wavefront,
-// and GATHER_FRAMES frames per lane, so that every table entry a lane reads
-// serves that many frames (one table read per GATHER_FRAMES frames instead
-// of one per frame).  The sums are FP64 in either precision.
-constexpr int GATHER_FRAMES = 8;
+// and F frames per lane, so that every table entry a lane reads serves that
+// many frames (one table read per F frames instead of one per frame).  The
+// sums are FP64 in either precision.  GATHER_FRAMES per lane where that fills
+// the chip, GATHER_FRAMES_FEW below GATHER_FEW workgroups (37 frames, 936
+// atoms: 23 us with 8 frames a lane, 295 workgroups).
+constexpr int GATHER_FRAMES = 8, GATHER_FRAMES_FEW = 2, GATHER_FEW = 2048;
 
-template <typename T>
+template <typename T, int F>
 __global__ __launch_bounds__(256) void k_gather_b_frames(int n_elec, int P3, const int* __restrict__ gidx,
                                                          const T* __restrict__ gw, const T* __restrict__ phi_all,
                                                          int M, const T* __restrict__ phi_real_all,
                                                          double* __restrict__ b_all, SlabTerms sl, int n_frames) {
-  constexpr int F = GATHER_FRAMES;
   const int sub = threadIdx.x & 15;
   const int i = blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4);
   const int f0 = blockIdx.y * F;
@@ -166,7 +172,10 @@ void launch_spread_elec_t(hipStream_t s, int n_frames, int n_touch, const int* t
                 : 2 * row <= (size_t)SPREAD_FRAMES_LDS_MAX ? 2
                                                            : 0;
   if (F > 0) {
-    const dim3 grid(SPREAD_FRAMES_CHUNKS, (n_frames + F - 1) / F);
+    const int groups = (n_frames + F - 1) / F, rows = SPREAD_FRAMES_THREADS / F;
+    const int chunks = std::max(SPREAD_FRAMES_CHUNKS,
+                                std::min((n_touch + rows - 1) / rows, (SPREAD_FRAMES_WGS + groups - 1) / groups));
+    const dim3 grid(chunks, groups);
     const size_t lds = (size_t)F * n_elec * sizeof(double);
     auto go = [&](auto kern) {
       hipLaunchKernelGGL(kern, grid, dim3(SPREAD_FRAMES_THREADS), lds, s, n_touch, touch, rowptr, col, val, q,
@@ -202,9 +211,12 @@ void launch_gather_b_t(hipStream_t s, int n_frames, int n_elec, int P3, const in
     dim3 grid((n_elec + 3) / 4, 1);
     hipLaunchKernelGGL(k_gather_b<T>, grid, dim3(256), 0, s, n_elec, P3, gidx, gw, phi, M, phi_real, b, sl);
   } else {
-    dim3 grid((n_elec + 15) / 16, (n_frames + GATHER_FRAMES - 1) / GATHER_FRAMES);
-    hipLaunchKernelGGL(k_gather_b_frames<T>, grid, dim3(256), 0, s, n_elec, P3, gidx, gw, phi, M, phi_real, b, sl,
-                       n_frames);
+    const int gx = (n_elec + 15) / 16, gy = (n_frames + GATHER_FRAMES - 1) / GATHER_FRAMES;
+    auto go = [&](auto kern, int y) {
+      hipLaunchKernelGGL(kern, dim3(gx, y), dim3(256), 0, s, n_elec, P3, gidx, gw, phi, M, phi_real, b, sl, n_frames);
+    };
+    if (gx * gy >= GATHER_FEW) go(k_gather_b_frames<T, GATHER_FRAMES>, gy);
+    else go(k_gather_b_frames<T, GATHER_FRAMES_FEW>, (n_frames + GATHER_FRAMES_FEW - 1) / GATHER_FRAMES_FEW);
   }
 }
 

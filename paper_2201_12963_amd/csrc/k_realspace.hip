@@ -497,8 +497,13 @@ void launch_site_pairs_t(hipStream_t s, int n_frames, const PairArgs<T>& pa) {
   if (pa.tsplit > 0 && pa.fwd_n) {
     // site-site pairs once each (both ends take atomic adds), then the
     // site-electrode pairs
-    launch_zero(s, pa.f_pair, (size_t)n_frames * 3 * pa.st.n);
-    if (pa.u_site) launch_zero(s, pa.u_site, (size_t)n_frames * pa.st.n);
+    const size_t nv = (size_t)n_frames * pa.st.n;
+    if (pa.u_site == pa.f_pair + 3 * nv) {
+      launch_zero(s, pa.f_pair, 4 * nv);
+    } else {
+      launch_zero(s, pa.f_pair, 3 * nv);
+      if (pa.u_site) launch_zero(s, pa.u_site, nv);
+    }
     const size_t lds = site_pairs_lds<T>(pa.tsplit, true);
     if (pa.zshift)
       hipLaunchKernelGGL(HIP_KERNEL_NAME(k_site_pairs_n3<T, true>), grid, dim3(TILE_THREADS), lds, s, pa);
