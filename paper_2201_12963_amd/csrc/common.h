@@ -399,6 +399,16 @@ __device__ __forceinline__ int spline_triangle_d(double u, int P, T (&B)[MAX_ORD
   return (int)fl + 1;
 }
 
+// A stencil start in [-K, 2K) wrapped into [0, K) (a wrapped coordinate gives
+// -P/2 .. K; the integer remainders this replaces were ~60 instructions).  The
+// clamp keeps the index in range where a coordinate is too large for its
+// wrapping to mean anything.
+__device__ __forceinline__ int wrap_start(int f, int K) {
+  f += f < 0 ? K : 0;
+  f -= f >= K ? K : 0;
+  return max(0, min(f, K - 1));
+}
+
 // first mesh point of the stencil of scaled coordinate u, as spline_triangle_d
 template <typename T>
 __device__ __forceinline__ int spline_first(T u, int P) {

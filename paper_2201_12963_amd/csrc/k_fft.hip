@@ -392,7 +392,7 @@ __device__ void plane_interp(const InterpArgs<T>& ia, const InterpPre<T, T2>& pr
     // the stencil start as spline_triangle_d takes it (the weights only for
     // the sites kept)
     int fz = (int)floor(uz - 0.5 * P) + 1;
-    fz = ((fz % Kz) + Kz) % Kz;
+    fz = wrap_start(fz, Kz);
     int d0 = z0 - fz;
     d0 += d0 < 0 ? Kz : 0;               // slot of plane z0; plane z0 + p has slot d0 + p (mod Kz)
     int d1 = d0 + np - 1;
@@ -402,8 +402,8 @@ __device__ void plane_interp(const InterpArgs<T>& ia, const InterpPre<T, T2>& pr
     spline_triangle_d<T, 5>(uz, P, Bz);
     int fx = spline_triangle_d<T, 5>((first ? pre.x : ia.sx[fo + j]) * ia.mi.invh[0], P, Bx);
     int fy = spline_triangle_d<T, 5>((first ? pre.y : ia.sy[fo + j]) * ia.mi.invh[1], P, By);
-    fx = ((fx % Kx) + Kx) % Kx;
-    fy = ((fy % Ky) + Ky) % Ky;
+    fx = wrap_start(fx, Kx);
+    fy = wrap_start(fy, Ky);
     T* out = ia.part + (size_t)frame * 6 * P * ia.n + j;      // share (slot, component) at [(slot 6 + component) n]
 #pragma unroll 1
     for (int p = 0; p < np; ++p) {
@@ -634,9 +634,9 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
     int fx = spline_triangle_d<T, ORD>(wrap(xj, Lx, rLx) * ihx, P, Bx);
     int fy = spline_triangle_d<T, ORD>(wrap(yj, Ly, rLy) * ihy, P, By);
     int fz = spline_triangle_d<T, ORD>(wrap(zj, Lz, rLz) * ihz, P, Bz);
-    fx = ((fx % Kx) + Kx) % Kx;
-    fy = ((fy % Ky) + Ky) % Ky;
-    fz = ((fz % Kz) + Kz) % Kz;
+    fx = wrap_start(fx, Kx);
+    fy = wrap_start(fy, Ky);
+    fz = wrap_start(fz, Kz);
 #pragma unroll
     for (int p = 0; p < SPL; ++p) {
       int tz;
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
   auto slot = [&](double zj) -> int {
     if (!isfinite(zj)) zj = 0.0;
     int fz = spline_first(wrap(zj, Lz, rLz) * ihz, P);
-    fz = ((fz % Kz) + Kz) % Kz;
+    fz = wrap_start(fz, Kz);
     const int tz = iz - fz;
     return tz + ((tz < 0) ? Kz : 0);
   };
@@ -844,7 +844,7 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
   const int col = (blockIdx.x * za.cpw + wv) * L + c;
   const bool wave_on = wv < za.cpw && (blockIdx.x * za.cpw + wv) * L < Kx * Ky;
   const bool active = wave_on && col < Kx * Ky;            // this lane's column exists
-  const int y = active ? col / Kx : 0, x = active ? col - y * Kx : 0;
+  const int y = active ? div_small(col, rcp_small(Kx)) : 0, x = active ? col - y * Kx : 0;
   const size_t fo = (size_t)blockIdx.y * Kx * Ky * Kz;
   const size_t plane = (size_t)Kx * Ky;
   const size_t cxy = (size_t)y * Kx + x;                   // point z of the column: z * plane + cxy

@@ -171,7 +171,7 @@ __device__ __forceinline__ void site_forces_body(const Cell& cell, const ElecSet
       const int K = lane == 0 ? Kx : (lane == 1 ? Ky : Kz);
       T B[MAX_ORDER];
       int first = spline_triangle_d<T>(xa * ih, P, B);
-      fsp[wv][lane] = ((first % K) + K) % K;
+      fsp[wv][lane] = wrap_start(first, K);
 #pragma unroll
       for (int b = 0; b < MAX_ORDER; ++b)
         if (b < P) wsp[wv][lane][P - 1 - b] = B[b];
@@ -366,9 +366,9 @@ __global__ __launch_bounds__(G16_THREADS) void k_site_forces_g16(SiteSet<T> st, 
     int fx = spline_triangle_d<T>(xj * fa.mi.invh[0], P, Bx);
     int fy = spline_triangle_d<T>(yj * fa.mi.invh[1], P, By);
     int fz = spline_triangle_d<T>(zj * fa.mi.invh[2], P, Bz);
-    fx = ((fx % Kx) + Kx) % Kx;
-    fy = ((fy % Ky) + Ky) % Ky;
-    fz = ((fz % Kz) + Kz) % Kz;
+    fx = wrap_start(fx, Kx);
+    fy = wrap_start(fy, Ky);
+    fz = wrap_start(fz, Kz);
     const T* Ef = fa.Ea + (size_t)frame * fa.Ea_frame_stride;
     // point t = (tz P + ty) P + tx: quotients through a float reciprocal,
     // exact for t < 7^3 (the fractions stay >= 1/98 away from integers)
