@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <limits>
 #include <cmath>
 #include <cstdarg>
@@ -147,6 +148,10 @@ struct cpm_ctx {
   double *d_gw = nullptr, *d_val = nullptr;
   float *d_gwf = nullptr, *d_valf = nullptr;
   int n_touch = 0, P3 = 0;
+  // one-frame FP64 steps of order 5: the electrode stencils by plane, and
+  // whether the inverse x-y pass gathers b
+  ElecPlanes planes{};
+  bool elec_gather = false;
 
   // ---- explicit Ewald
   int nk = 0;
@@ -532,7 +537,8 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
   using T2 = typename B::T2;
   hipStream_t s = c->stream;
   c->elec_owner = nullptr;
-  const bool mixed = std::is_same<T, float>::value;
+  constexpr bool mixed = std::is_same<T, float>::value;
+  const bool gather = !mixed && nf == 1 && c->elec_gather;
   BinArgs ba{};
   ba.n_site = c->n_site;
   ba.xyz_all = xyz;
@@ -558,6 +564,8 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
   rb.rc2 = c->rcut * c->rcut;
   rb.el = B::elec(c);
   rb.phi_out = B::phir(c);
+  rb.b_out = gather ? c->d_b : nullptr;
+  rb.sl = slab_terms(c);
   rb.item_c = c->d_item_c;
   rb.item_lo = c->d_item_lo;
   rb.item_hi = c->d_item_hi;
@@ -588,6 +596,21 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
     if (!need_b) return CPM_OK;
     // timed alone through the stand-alone kernel with the same body
     if (!rb.tiles) keep(c, CPM_KERNEL_REAL_B, [=](hipStream_t s) { launch_real_b_t<T>(s, nf, rb); });
+    if constexpr (!mixed) {
+      if (gather) {
+        // b finished in the inverse pass (replayed on scratch: it adds to b);
+        // the gather timed alone through the stand-alone kernel
+        launch_fft_xy_gather(s, c->px, c->py, c->mi.K[2], c->d_c1, c->d_phi, c->planes, c->d_b);
+        keep(c, CPM_KERNEL_FFT_XY_INV, [=](hipStream_t s) {
+          launch_fft_xy_gather(s, c->px, c->py, c->mi.K[2], c->d_c1, c->d_phi, c->planes, c->d_g);
+        });
+        keep(c, CPM_KERNEL_GATHER_B, [=](hipStream_t s) {
+          launch_gather_b_t<T>(s, nf, c->n_elec, c->P3, c->d_gidx, B::gw(c), B::phi(c), c->mi.M, B::phir(c), c->d_b,
+                               slab_terms(c));
+        });
+        return CPM_OK;
+      }
+    }
     // (many frames: only the planes the electrode stencils read)
     rec(c, CPM_KERNEL_FFT_XY_INV, s, [=](hipStream_t s) {
       launch_fft_xy_t<T, T2>(s, nf, c->px, c->py, c->mi.K[2], 1, nullptr, B::c1(c), nullptr, B::phi(c), nullptr, 0,
@@ -1107,6 +1130,13 @@ int check_launch(cpm_ctx* c) {
 
 extern "C" {
 
+// One-frame steps gather b inside the inverse x-y pass while a plane holds at
+// most this many (atom, plane) entries: only the planes at the electrodes hold
+// any, so larger electrodes leave that work to a few workgroups (1760 entries
+// a plane: 10.3 us in the pass against 6.9 + 3.3 in two launches; 440: 5.9
+// against 4.6 + 2.5).
+constexpr int ELEC_PLANE_MOST = 1024;
+
 int cpm_create(const cpm_desc* d, void* hip_stream, cpm_ctx** out) {
   if (out) *out = nullptr;
   if (!d || !out) return fail(nullptr, CPM_EINVAL, "null descriptor or output pointer");
@@ -1515,6 +1545,45 @@ int cpm_create(const cpm_desc* d, void* hip_stream, cpm_ctx** out) {
     c->zmask_ok = mi.K[2] <= 256;
     if (c->zmask_ok)
       for (int z : zl) c->zmask_e.w[z >> 6] |= 1ull << (z & 63);
+    if (c->precision == CPM_FP64 && P == 5) {
+      std::vector<std::vector<std::array<int, 3>>> of(mi.K[2]);            // atom, z slot, start
+      std::vector<double> w3((size_t)ne * 15);
+      for (int i = 0; i < ne; ++i) {
+        int first[3];
+        for (int k = 0; k < 3; ++k) {
+          double u = wrap_host(pos[k][i], c->box[k]) * mi.invh[k];
+          first[k] = (int)std::floor(u - P / 2.0) + 1;
+          for (int t = 0; t < P; ++t) w3[(size_t)i * 15 + 5 * k + t] = bspline_host(P, u - (first[k] + t) + P / 2.0);
+          first[k] = (first[k] % mi.K[k] + mi.K[k]) % mi.K[k];
+        }
+        for (int t = 0; t < P; ++t) of[(first[2] + t) % mi.K[2]].push_back({i, t, first[0] | first[1] << 16});
+      }
+      std::vector<int> ptr(mi.K[2] + 1, 0), atom, start;
+      std::vector<double> wx((size_t)ne * 25), wy((size_t)ne * 25), wz((size_t)ne * 5);
+      int most = 0;
+      for (int z = 0; z < mi.K[2]; ++z) {
+        ptr[z] = (int)atom.size();
+        most = std::max(most, (int)of[z].size());
+        for (const auto& a : of[z]) {
+          const size_t e = atom.size();
+          for (int t = 0; t < P; ++t) {
+            wx[(size_t)t * 5 * ne + e] = w3[(size_t)a[0] * 15 + t];
+            wy[(size_t)t * 5 * ne + e] = w3[(size_t)a[0] * 15 + 5 + t];
+          }
+          wz[e] = w3[(size_t)a[0] * 15 + 10 + a[1]];
+          atom.push_back(a[0]);
+          start.push_back(a[2]);
+        }
+      }
+      ptr[mi.K[2]] = (int)atom.size();
+      int *dp, *da, *ds;
+      double *dx, *dy, *dz;
+      if ((r = upload(c, &dp, ptr)) || (r = upload(c, &da, atom)) || (r = upload(c, &ds, start)) ||
+          (r = upload(c, &dx, wx)) || (r = upload(c, &dy, wy)) || (r = upload(c, &dz, wz)))
+        return bad(r);
+      c->planes = ElecPlanes{dp, da, ds, dx, dy, dz, (int)atom.size()};
+      c->elec_gather = most <= ELEC_PLANE_MOST;
+    }
     if (bin_lds_spread(ns, cl.n_cells) > LDS_LIMIT) {
       fail(c, CPM_EINVAL, "%d sites in %d cells exceed the binning workgroup's LDS", ns, cl.n_cells);
       return bad(CPM_EINVAL);

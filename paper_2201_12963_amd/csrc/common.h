@@ -203,6 +203,19 @@ struct InterpArgs {
   MeshInfo mi;
 };
 
+// One frame, FP64, order 5: the electrode stencils by plane, for the inverse
+// x-y pass that gathers b while a plane is in LDS.  Entry e is one (atom, plane) pair; the entries of plane z are
+// plane_ptr[z] .. plane_ptr[z + 1] - 1.
+struct ElecPlanes {
+  const int* plane_ptr;         // [K_z + 1]
+  const int* atom;              // [n] original index
+  const int* start;             // [n] x start | y start << 16
+  const double* wx;             // [5][n] weights at x start + t
+  const double* wy;             // [5][n]
+  const double* wz;             // [n] weight of the plane
+  int n;
+};
+
 template <typename T>
 struct ForceArgs {
   T alpha, eta;
@@ -248,6 +261,22 @@ struct ForceArgs {
 template <typename T>
 constexpr size_t pair_queue_lds() { return 4 * (5 * 128 * sizeof(T) + 64 * sizeof(int)); }
 
+// particle-mesh steps (k_pppm.hip)
+// Slab geometry's dipole correction (charged-sheet correction of the
+// z-periodic box): kappa = k_e 4 pi / V, electrode heights ze (wrapped),
+// the electrolyte dipole zdip[frame] = sum_j Q_j Z_j; kappa == 0 means none
+struct SlabTerms {
+  double kappa;
+  const double* ze;
+  const double* zdip;
+  int n_elec;
+};
+
+// b_i -= kappa z_i zdip (the electrolyte-electrode block of the correction)
+__device__ __forceinline__ double slab_b_term(const SlabTerms& sl, int i, int frame) {
+  return sl.kappa != 0.0 ? sl.kappa * sl.ze[i] * sl.zdip[frame] : 0.0;
+}
+
 // real-space part of b: one wavefront per electrode atom, four per
 // workgroup (tiles == 0; hosted as extra workgroups of another launch for
 // one frame), or cell tiles over fixed work items of at most TILE_TGT atoms
@@ -261,6 +290,11 @@ struct RealBArgs {
   double rc2;
   ElecSet<T> el;
   T* phi_out;                  // [frame][n_elec] original order
+  // one frame: the atom's b starts as minus its real-space part (and the slab
+  // correction's), and the inverse x-y pass subtracts the mesh part plane by
+  // plane; nullptr: not
+  double* b_out;
+  SlabTerms sl;
   int tiles;
   const int* item_c;           // cell of item b
   const int* item_lo;          // its atoms [item_lo, item_hi) of the sorted electrode arrays
@@ -452,23 +486,6 @@ void launch_site_forces_t(hipStream_t s, int n_frames, const Cell& cell, const E
                           const SiteSet<T>& st, const ForceArgs<T>& fa, bool forces, const EnergyArgs* ea,
                           const T* epart = nullptr);
 size_t bin_lds_bytes(int n_site, int n_cells);
-
-// particle-mesh steps (k_pppm.hip)
-// Slab geometry's dipole correction (charged-sheet correction of the
-// z-periodic box): kappa = k_e 4 pi / V, electrode heights ze (wrapped),
-// the electrolyte dipole zdip[frame] = sum_j Q_j Z_j; kappa == 0 means none
-struct SlabTerms {
-  double kappa;
-  const double* ze;
-  const double* zdip;
-  int n_elec;
-};
-
-// b_i -= kappa z_i zdip (the electrolyte-electrode block of the correction)
-__device__ __forceinline__ double slab_b_term(const SlabTerms& sl, int i, int frame) {
-  return sl.kappa != 0.0 ? sl.kappa * sl.ze[i] * sl.zdip[frame] : 0.0;
-}
-
 // One workgroup: field[frame] = -kappa (zdip[frame] + z.q), q of that frame
 __device__ __forceinline__ void slab_field_block(const SlabTerms& sl, const double* q, double* field, int frame) {
   __shared__ double red[16];
@@ -505,6 +522,10 @@ void launch_fft_xy_t(hipStream_t s, int n_frames, const FFTPlan1D& px, const FFT
 // (zl: many frames only, the n_zl planes to transform, ascending; nullptr: all)
 // inverse x-y pass of the field: c1 -> E[0] (re), E[1] (im); c2 -> E[2];
 // both in one launch; E frames frame_stride apart, components M apart
+// one frame, FP64, order 5: the potential's inverse pass (phi the whole mesh)
+// with the gather of b, b[atom] -= the plane's share
+void launch_fft_xy_gather(hipStream_t s, const FFTPlan1D& px, const FFTPlan1D& py, int Kz, const double2* in,
+                          double* phi, const ElecPlanes& ep, double* b);
 template <typename T, typename T2>
 void launch_fft_xy_field_inv_t(hipStream_t s, int n_frames, const FFTPlan1D& px, const FFTPlan1D& py, int Kz,
                                const T2* c1, const T2* c2, T* E, size_t frame_stride,

@@ -557,6 +557,76 @@ __global__ __launch_bounds__(INTERP ? XY_THREADS_MANY : XY_THREADS, INTERP ? 5 :
                                         in_c2, out_re2, zl, n_zl, ia);
 }
 
+// --------------------------------------- gather of b in the inverse x-y pass
+
+// One frame, FP64, order 5.  The gather of b was a launch of its own (2.5 -
+// 3.5 us and a gap, of which ~3 are the launch, a round trip to memory and the
+// stores); here it is part of the pass that has the plane in LDS (+1.3 us).  A
+// thread takes an (atom, plane) entry: separable weights from coalesced tables
+// (88 bytes an entry, loaded before the transform so that their latency passes
+// under it), 25 points in LDS.  (The electrode spread does not gain likewise:
+// the few planes with charge serialise it, 8.1 - 10.9 us in the pass against
+// 2.7 + 4.5.)
+constexpr int EP = 5;
+struct PlaneEntry {
+  double wx[EP], wy[EP], wz;
+  int start, atom;
+};
+__device__ __forceinline__ void load_entry(const ElecPlanes& ep, int e, PlaneEntry& v) {
+#pragma unroll
+  for (int t = 0; t < EP; ++t) { v.wx[t] = ep.wx[(size_t)t * ep.n + e]; v.wy[t] = ep.wy[(size_t)t * ep.n + e]; }
+  v.wz = ep.wz[e];
+  v.start = ep.start[e];
+  v.atom = ep.atom[e];
+}
+
+// The potential's inverse pass of plane blockIdx.x, then b[atom] -= the
+// plane's share of its stencil (an atom's five planes are five workgroups, so
+// the shares meet in atomic adds on the b that the real-space part began).
+__global__ __launch_bounds__(XY_THREADS) void k_fft_xy_gather(FFTPlan1D px, FFTPlan1D py, const double2* __restrict__ in,
+                                                              double* __restrict__ phi, ElecPlanes ep,
+                                                              double* __restrict__ b) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int Kx = px.n, Ky = py.n, NP = Kx * Ky;
+  double2* A = reinterpret_cast<double2*>(smem);
+  double2* B = A + NP;
+  double2* twx = B + NP;
+  double2* twy = twx + Kx;
+  load_twiddles(px, twx);
+  load_twiddles(py, twy);
+  const size_t off = (size_t)blockIdx.x * NP;
+  const int e0 = ep.plane_ptr[blockIdx.x], e1 = ep.plane_ptr[blockIdx.x + 1];
+  for (int i = threadIdx.x; i < NP; i += blockDim.x) A[i] = in[off + i];
+  PlaneEntry v;
+  int e = e0 + threadIdx.x;
+  if (e < e1) load_entry(ep, e, v);
+  __syncthreads();
+  double2* r1 = plane_lines(A, B, px, twx, Ky, 1, Kx, +1, true);        // along x
+  double2* o1 = (r1 == A) ? B : A;
+  double2* r2 = plane_lines(r1, o1, py, twy, Kx, Kx, 1, +1, true);      // along y
+  for (int i = threadIdx.x; i < NP; i += blockDim.x) phi[off + i] = r2[i].x;
+  for (; e < e1; e += blockDim.x) {
+    if (e >= e0 + (int)blockDim.x) load_entry(ep, e, v);
+    const int x0 = v.start & 0xffff, y0 = v.start >> 16;
+    double acc = 0.0;
+#pragma unroll
+    for (int ty = 0; ty < EP; ++ty) {
+      int iy = y0 + ty;
+      iy -= iy >= Ky ? Ky : 0;
+      const double2* row = r2 + iy * Kx;
+      double s = 0.0;
+#pragma unroll
+      for (int tx = 0; tx < EP; ++tx) {
+        int ix = x0 + tx;
+        ix -= ix >= Kx ? Kx : 0;
+        s = fma(v.wx[tx], row[ix].x, s);
+      }
+      acc = fma(v.wy[ty], s, acc);
+    }
+    atomicAdd(b + v.atom, -(v.wz * acc));
+  }
+}
+
 // ------------------------------------------------- spread fused with x-y
 
 // Forward x-y transform of one z-plane of the electrolyte charge mesh, whose
@@ -816,7 +886,7 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
     T* qbuf = reinterpret_cast<T*>(smem + (threadIdx.x >> 6) * wave_scratch_bytes<T>());
     if (hb < rb.n_blocks) {
       const int g = xcd_block(hb, rb.n_blocks) * (blockDim.x / WAVE) + (threadIdx.x >> 6);
-      if (g < rb.el.n) real_b_wave(rb.cell, rb.alpha, rb.eta, rb.rc2, rb.el, rb.st, rb.phi_out, g, blockIdx.y, qbuf);
+      if (g < rb.el.n) real_b_wave(rb.cell, rb.alpha, rb.eta, rb.rc2, rb.el, rb.st, rb.phi_out, g, blockIdx.y, qbuf, nullptr, rb.b_out, &rb.sl);
     } else if (LJ && hb >= rb.n_blocks + pa.n_blocks) {
       lj_site<4>(*lj, hb - rb.n_blocks - pa.n_blocks);
     } else {
@@ -1117,6 +1187,12 @@ void launch_fft_xy_t(hipStream_t s, int n_frames, const FFTPlan1D& px, const FFT
   else
     launch_xy_many<T, T2>(s, px, py, Kz, n_frames, mode, in_re, in_c, out_c, out_re, out_im, out_re_stride, 0,
                           (const T2*)nullptr, (T*)nullptr, nullptr, zl, n_zl);
+}
+
+void launch_fft_xy_gather(hipStream_t s, const FFTPlan1D& px, const FFTPlan1D& py, int Kz, const double2* in,
+                          double* phi, const ElecPlanes& ep, double* b) {
+  hipLaunchKernelGGL(k_fft_xy_gather, dim3(Kz), dim3(XY_THREADS), fft_xy_lds<double2>(px, py, 1), s, px, py, in, phi,
+                     ep, b);
 }
 
 template <typename T, typename T2>

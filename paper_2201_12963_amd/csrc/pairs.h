@@ -353,7 +353,8 @@ __device__ __forceinline__ T g1_potential(T dx, T dy, T dz, T q, T alpha, T eta)
 template <typename T>
 __device__ __forceinline__ T real_b_wave(const Cell& cell, T alpha, T eta, double rc2, const ElecSet<T>& el,
                                          const SiteSet<T>& st, T* __restrict__ phi_out, int g, int frame,
-                                         T* scratch, int* orig = nullptr) {
+                                         T* scratch, int* orig = nullptr, double* b_out = nullptr,
+                                         const SlabTerms* sl = nullptr) {
   const int lane = threadIdx.x & (WAVE - 1);
   const size_t fo = (size_t)frame * st.n;
   const double* sx = st.x + fo; const double* sy = st.y + fo; const double* sz = st.z + fo;
@@ -388,7 +389,10 @@ __device__ __forceinline__ T real_b_wave(const Cell& cell, T alpha, T eta, doubl
             });
   if (lane < n) acc += g1_potential(Q.x[lane], Q.y[lane], Q.z[lane], Q.a[lane], alpha, eta);
   acc = wave_sum(acc);
-  if (lane == 0) phi_out[(size_t)frame * el.n + og] = (T)KE * acc;
+  if (lane == 0) {
+    phi_out[(size_t)frame * el.n + og] = (T)KE * acc;
+    if (b_out) b_out[og] = -(double)((T)KE * acc) - slab_b_term(*sl, og, 0);
+  }
   if (orig) *orig = og;
   return (T)KE * acc;
 }
