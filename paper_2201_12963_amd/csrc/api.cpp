@@ -645,7 +645,7 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
 // of the site-force launch.
 template <typename T>
 int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const double* qa_s, ForceArgs<T> fa,
-                   const EnergyArgs* ea) {
+                   const EnergyArgs* ea, const LossArgs* la = nullptr) {
   using B = Bufs<T>;
   using T2 = typename B::T2;
   hipStream_t s = c->stream;
@@ -762,21 +762,25 @@ int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const
     if constexpr (!std::is_same<T, float>::value) {
       const EwaldField ef{c->nk, c->d_kv, c->d_ew, c->d_rhok_all};
       const EnergyArgs e = ea ? *ea : EnergyArgs{};
-      const bool we = ea != nullptr;
+      const bool we = ea != nullptr, wl = la != nullptr;
+      const LossArgs l = la ? *la : LossArgs{};
       rec(c, CPM_KERNEL_SITE_FORCES, s, [=](hipStream_t s) {
-        launch_site_forces_ewald(s, c->cell, B::elec(c), st, fa, ef, true, we ? &e : nullptr);
+        launch_site_forces_ewald(s, c->cell, B::elec(c), st, fa, ef, true, we ? &e : nullptr, wl ? &l : nullptr);
       });
       if (we)
         keep(c, CPM_KERNEL_ENERGY, [=](hipStream_t s) {
-          launch_site_forces_ewald(s, c->cell, B::elec(c), st, fa, ef, false, &e);
+          launch_site_forces_ewald(s, c->cell, B::elec(c), st, fa, ef, false, &e, nullptr);
         });
     }
     return CPM_OK;
   }
   const bool with_e = ea != nullptr;
   const EnergyArgs e = with_e ? *ea : EnergyArgs{};
+  const bool with_l = la != nullptr;
+  const LossArgs l = la ? *la : LossArgs{};
   rec(c, CPM_KERNEL_SITE_FORCES, s, [=](hipStream_t s) {
-    launch_site_forces_t<T>(s, nf, c->cell, B::elec(c), st, fa, true, with_e ? &e : nullptr, epart);
+    launch_site_forces_t<T>(s, nf, c->cell, B::elec(c), st, fa, true, with_e ? &e : nullptr, epart,
+                            with_l ? &l : nullptr);
   });
   if (with_e)
     keep(c, CPM_KERNEL_ENERGY, [=](hipStream_t s) {
@@ -855,10 +859,13 @@ int enqueue_grad(cpm_ctx* c, const double* xyz, double dv, const double* t, doub
   const int n = c->n_elec;
   double* q = q_out ? q_out : c->d_qint;
   TRY(enqueue_b<T>(c, 1, xyz, true));
-  launch_charges(s, 1, n, c->d_S, c->d_b, c->d_Sc, dv, c->d_Q0, q);
-  launch_adjoint_rhs(s, n, q, t, c->d_c, dv, c->d_g);
-  launch_charges(s, 1, n, c->d_S, c->d_g, c->d_Sc, 0.0, c->d_lam, nullptr);    // lambda = S g
-  launch_sub(s, n, q, c->d_lam, c->d_qa, c->d_epos, c->d_qs);
+  // q = S b + dv S c with g = 2 (q - t) + dv c, then lambda = S g with
+  // qa = q - lambda, each in its solve's launch; the loss with the energies
+  ChargeTail rhs{}, sub{};
+  rhs.t = t; rhs.c = c->d_c; rhs.g = c->d_g;
+  launch_charges(s, 1, n, c->d_S, c->d_b, c->d_Sc, dv, c->d_Q0, q, nullptr, nullptr, &rhs);
+  sub.q_of = q; sub.qa = c->d_qa;
+  launch_charges(s, 1, n, c->d_S, c->d_g, c->d_Sc, 0.0, c->d_lam, nullptr, c->d_epos, c->d_qs, &sub);
   ForceArgs<T> fa{};
   fa.out_scale = -1.0;
   fa.field = 0.0;
@@ -867,8 +874,8 @@ int enqueue_grad(cpm_ctx* c, const double* xyz, double dv, const double* t, doub
   fa.n_dv = 1;
   fa.u_site = c->d_usite;
   const EnergyArgs ea = energy_args(c, 1, nullptr, dv, c->d_energy_tmp);
-  TRY(enqueue_forces<T>(c, 1, c->d_qa, n, c->d_qs, fa, &ea));
-  launch_grad_finish(s, n, q, t, c->d_lam, c->d_c, c->d_energy_tmp, loss, dldv);
+  const LossArgs la{q, t, c->d_lam, loss, dldv};
+  TRY(enqueue_forces<T>(c, 1, c->d_qa, n, c->d_qs, fa, &ea, &la));
   return CPM_OK;
 }
 

@@ -378,6 +378,14 @@ struct EnergyArgs {
   double* out;                                   // [frame][n_dv][2]
 };
 
+// the gradient's loss = sum (q - t)^2 + U_coul and dL/ddV = lambda . c, beside
+// the energies of one frame with one dV (kernel entries of their own: more
+// kernel arguments lengthen every launch that carries them)
+struct LossArgs {
+  const double *q, *t, *lam;
+  double *loss, *dldv;
+};
+
 // Centred cardinal B-spline weights along one axis.  A particle at scaled
 // coordinate u (mesh units) touches the P mesh points m = first + t,
 // t = 0..P-1, first = floor(u - P/2) + 1, with weight M_P(u - m + P/2).
@@ -484,7 +492,8 @@ template <typename T>
 // place of the gathers from fa.Ea and fa.Eb, or nullptr
 void launch_site_forces_t(hipStream_t s, int n_frames, const Cell& cell, const ElecSet<T>& el,
                           const SiteSet<T>& st, const ForceArgs<T>& fa, bool forces, const EnergyArgs* ea,
-                          const T* epart = nullptr);
+                          const T* epart = nullptr,
+                          const LossArgs* la = nullptr);
 size_t bin_lds_bytes(int n_site, int n_cells);
 // One workgroup: field[frame] = -kappa (zdip[frame] + z.q), q of that frame
 __device__ __forceinline__ void slab_field_block(const SlabTerms& sl, const double* q, double* field, int frame) {
@@ -575,7 +584,8 @@ struct EwaldField {            // the k-space field's sum over the k-vectors, at
   const double2* rho;          // of all charges
 };
 void launch_site_forces_ewald(hipStream_t s, const Cell& cell, const ElecSet<double>& el, const SiteSet<double>& st,
-                              const ForceArgs<double>& fa, const EwaldField& ef, bool forces, const EnergyArgs* ea);
+                              const ForceArgs<double>& fa, const EwaldField& ef, bool forces, const EnergyArgs* ea,
+                              const LossArgs* la);
 
 // dense linear algebra (k_linalg.hip)
 constexpr int GJ_BLOCK = 32;
@@ -605,8 +615,18 @@ void launch_gj_invert(hipStream_t s, int n, double* A, double* dinv, double* pc,
 void launch_matvec(hipStream_t s, int n, const double* Mx, const double* x, double* y);
 void launch_dot(hipStream_t s, int n, const double* a, const double* b, double* out);
 void launch_rank1(hipStream_t s, int n, double* S, const double* u, const double* sc);
+// What the gradient's two charge solves add to the rows they make: the first the adjoint right-hand side
+// g = 2 (q - t) + dv c, the second (Q0 = lambda) qa = q_of - lambda, whose
+// cell-sorted copy then goes to qs.
+struct ChargeTail {
+  const double *t, *c;
+  double* g;
+  const double* q_of;
+  double* qa;
+};
 void launch_charges(hipStream_t s, int n_frames, int n, const double* S, const double* b, const double* Sc, double dv,
-                    double* Q0, double* q, const int* epos = nullptr, double* qs = nullptr);
+                    double* Q0, double* q, const int* epos = nullptr, double* qs = nullptr,
+                    const ChargeTail* tail = nullptr);
 // dst[f][epos[i]] = src[f][i] for n values of n_frames frames
 void launch_permute(hipStream_t s, int n_frames, int n, const int* epos, const double* src, double* dst);
 // the charges of every (frame, dV); qs (or nullptr): the frames' charges at
@@ -617,12 +637,6 @@ void launch_expand_charges(hipStream_t s, int n_frames, int n_elec, int n_dv, co
 // values k of every frame f and dV v
 void launch_expand_forces(hipStream_t s, int n_frames, int n_site, int n_dv, const double* dv, const double* comp,
                           double* out);
-
-void launch_adjoint_rhs(hipStream_t s, int n, const double* q, const double* t, const double* c, double dv, double* g);
-void launch_sub(hipStream_t s, int n, const double* a, const double* b, double* out, const int* epos = nullptr,
-                double* out_s = nullptr);
-void launch_grad_finish(hipStream_t s, int n, const double* q, const double* t, const double* lam, const double* c,
-                        const double* energy, double* loss, double* dldv);
 
 // mixed precision (k_mixed.hip)
 void launch_split_matrix(hipStream_t s, int n, int n_pad, const double* S, float* Sf, unsigned short* split);

@@ -313,10 +313,12 @@ __global__ void k_rank1(int n, double* __restrict__ S, const double* __restrict_
 
 // Q0 = S b (per frame), q = Q0 + dv Sc; one wavefront per row, four
 // independent accumulators so that four row loads per lane are in flight
-__global__ __launch_bounds__(256) void k_charges(int n, const double* __restrict__ S, const double* __restrict__ b_all,
-                                                 const double* __restrict__ Sc, double dv,
-                                                 double* __restrict__ Q0_all, double* __restrict__ q_all,
-                                                 const int* __restrict__ epos, double* __restrict__ qs_all) {
+// (the body; k_charges and k_charges_tail below are its launches)
+template <bool TAIL>
+__device__ __forceinline__ void charges_body(int n, const double* __restrict__ S, const double* __restrict__ b_all,
+                                             const double* __restrict__ Sc, double dv, double* __restrict__ Q0_all,
+                                             double* __restrict__ q_all, const int* __restrict__ epos,
+                                             double* __restrict__ qs_all, const ChargeTail& tail) {
   const int lane = threadIdx.x & (WAVE - 1);
   const int i = blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x >> 6);
   const int frame = blockIdx.y;
@@ -348,11 +350,29 @@ __global__ __launch_bounds__(256) void k_charges(int n, const double* __restrict
   const double acc = wave_sum((a0 + a1) + (a2 + a3));
   if (lane == 0) {
     const size_t o = (size_t)frame * n + i;
-    const double qv = acc + dv * Sc[i];
+    double qv = acc + dv * Sc[i];
     if (Q0_all) Q0_all[o] = acc;
     if (q_all) q_all[o] = qv;
+    if (TAIL && tail.g) tail.g[i] = 2.0 * (qv - tail.t[i]) + dv * tail.c[i];
+    if (TAIL && tail.qa) {
+      qv = tail.q_of[i] - acc;
+      tail.qa[i] = qv;
+    }
     if (qs_all) qs_all[(size_t)frame * n + ep] = qv;      // cell-sorted copy
   }
+}
+
+__global__ __launch_bounds__(256) void k_charges(int n, const double* __restrict__ S, const double* __restrict__ b,
+                                                 const double* __restrict__ Sc, double dv, double* __restrict__ Q0,
+                                                 double* __restrict__ q, const int* __restrict__ epos,
+                                                 double* __restrict__ qs) {
+  charges_body<false>(n, S, b, Sc, dv, Q0, q, epos, qs, ChargeTail{});
+}
+__global__ __launch_bounds__(256) void k_charges_tail(int n, const double* __restrict__ S, const double* __restrict__ b,
+                                                      const double* __restrict__ Sc, double dv, double* __restrict__ Q0,
+                                                      double* __restrict__ q, const int* __restrict__ epos,
+                                                      double* __restrict__ qs, ChargeTail tail) {
+  charges_body<true>(n, S, b, Sc, dv, Q0, q, epos, qs, tail);
 }
 
 // dst[f][epos[i]] = src[f][i]: charges of every frame in the electrodes'
@@ -363,19 +383,6 @@ __global__ __launch_bounds__(256) void k_permute(int n, const int* __restrict__ 
   const size_t f = blockIdx.y;
   if (i < n) dst[f * n + epos[i]] = src[f * n + i];
 }
-
-// ------------------------------------------------------------ energies
-
-__device__ double block_sum(double v, double* red) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double s = 0.0;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
-  return s;
-}
-
 
 // q[f][v][i] = Q0[f][i] + dv[v] Sc[i], and qs[f][epos[i]] = Q0[f][i] (the
 // charges the force pass reads, in the electrodes' cell-sorted order)
@@ -408,60 +415,7 @@ __global__ __launch_bounds__(256) void k_expand_forces(int n3, int n_dv, const d
   for (int v = 0; v < n_dv; ++v) o[(size_t)v * n3] = a + dv[v] * b;
 }
 
-// ------------------------------------------------------------ adjoint
-
-// g = 2 (q - t) + dv c   (the right-hand side of lambda = S g)
-__global__ __launch_bounds__(256) void k_adjoint_rhs(int n, const double* __restrict__ q, const double* __restrict__ t,
-                                                     const double* __restrict__ c, double dv, double* __restrict__ g) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) g[i] = 2.0 * (q[i] - t[i]) + dv * c[i];
-}
-
-// qa = q - lambda  (electrode charges of the adjoint force pass)
-// (and its cell-sorted copy out_s[epos[i]])
-__global__ __launch_bounds__(256) void k_sub(int n, const double* __restrict__ a, const double* __restrict__ b,
-                                             double* __restrict__ out, const int* __restrict__ epos,
-                                             double* __restrict__ out_s) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    const double v = a[i] - b[i];
-    out[i] = v;
-    if (out_s) out_s[epos[i]] = v;
-  }
-}
-
-// loss = sum (q - t)^2 + U_coul;  dL/ddV = lambda . c   (one workgroup)
-__global__ __launch_bounds__(256) void k_grad_finish(int n, const double* __restrict__ q, const double* __restrict__ t,
-                                                     const double* __restrict__ lam, const double* __restrict__ c,
-                                                     const double* __restrict__ energy, double* __restrict__ loss,
-                                                     double* __restrict__ dldv) {
-  __shared__ double red[4];
-  double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    double d = q[i] - t[i];
-    a += d * d;
-    b += lam[i] * c[i];
-  }
-  double A = block_sum(a, red);
-  double B = block_sum(b, red);
-  if (threadIdx.x == 0) {
-    loss[0] = A + energy[0];
-    dldv[0] = B;
-  }
-}
-
 // ------------------------------------------------------------ launchers
-
-void launch_adjoint_rhs(hipStream_t s, int n, const double* q, const double* t, const double* c, double dv, double* g) {
-  hipLaunchKernelGGL(k_adjoint_rhs, dim3((n + 255) / 256), dim3(256), 0, s, n, q, t, c, dv, g);
-}
-void launch_sub(hipStream_t s, int n, const double* a, const double* b, double* out, const int* epos, double* out_s) {
-  hipLaunchKernelGGL(k_sub, dim3((n + 255) / 256), dim3(256), 0, s, n, a, b, out, epos, out_s);
-}
-void launch_grad_finish(hipStream_t s, int n, const double* q, const double* t, const double* lam, const double* c,
-                        const double* energy, double* loss, double* dldv) {
-  hipLaunchKernelGGL(k_grad_finish, dim3(1), dim3(256), 0, s, n, q, t, lam, c, energy, loss, dldv);
-}
 
 void launch_elastance_real(hipStream_t s, int n, const double* ex, const double* ey, const double* ez,
                            const Cell& cell, double alpha, double eta, double rcut, double self_term, double* A) {
@@ -497,8 +451,12 @@ void launch_rank1(hipStream_t s, int n, double* S, const double* u, const double
   hipLaunchKernelGGL(k_rank1, dim3((n + 15) / 16, (n + 15) / 16), dim3(256), 0, s, n, S, u, sc);
 }
 void launch_charges(hipStream_t s, int n_frames, int n, const double* S, const double* b, const double* Sc, double dv,
-                    double* Q0, double* q, const int* epos, double* qs) {
-  hipLaunchKernelGGL(k_charges, dim3((n + 3) / 4, n_frames), dim3(256), 0, s, n, S, b, Sc, dv, Q0, q, epos, qs);
+                    double* Q0, double* q, const int* epos, double* qs, const ChargeTail* tail) {
+  const dim3 grid((n + 3) / 4, n_frames);
+  if (tail)
+    hipLaunchKernelGGL(k_charges_tail, grid, dim3(256), 0, s, n, S, b, Sc, dv, Q0, q, epos, qs, *tail);
+  else
+    hipLaunchKernelGGL(k_charges, grid, dim3(256), 0, s, n, S, b, Sc, dv, Q0, q, epos, qs);
 }
 void launch_permute(hipStream_t s, int n_frames, int n, const int* epos, const double* src, double* dst) {
   if (n == 0 || n_frames == 0) return;

@@ -90,10 +90,10 @@ constexpr int EWALD_FORCE_THREADS = 512;
 // field over the k-vectors (a sincos each: 16 us for a wavefront per site
 // over 1327 of them).
 // (the body; k_site_forces and k_site_forces_ewald below are its launches)
-template <typename T, bool TWO, bool EWALD>
+template <typename T, bool TWO, bool EWALD, bool LOSS>
 __device__ __forceinline__ void site_forces_body(const Cell& cell, const ElecSet<T>& el, const SiteSet<T>& st,
                                                  const ForceArgs<T>& fa, int n_force_blocks, const EnergyArgs& en,
-                                                 int walk_parts, const EwaldField* ef) {
+                                                 int walk_parts, const EwaldField* ef, const LossArgs* la) {
   int bx = blockIdx.x, frame = blockIdx.y;
   if (gridDim.y > 1) {
     // many frames: each XCD takes a contiguous range of whole frames, so a
@@ -105,7 +105,7 @@ __device__ __forceinline__ void site_forces_body(const Cell& cell, const ElecSet
     bx = L - frame * gridDim.x;
   }
   if (bx >= n_force_blocks) {
-    energy_block(en, frame);
+    energy_block<LOSS>(en, frame, la);
     return;
   }
   constexpr int WAVES = EWALD ? 1 : 4;         // wavefronts that walk
@@ -301,23 +301,38 @@ __device__ __forceinline__ void site_forces_body(const Cell& cell, const ElecSet
 template <typename T, bool TWO>
 __global__ __launch_bounds__(256, sizeof(T) == 8 ? 3 : TWO ? 6 : 7) void k_site_forces(
     Cell cell, ElecSet<T> el, SiteSet<T> st, ForceArgs<T> fa, int n_force_blocks, EnergyArgs en, int walk_parts) {
-  site_forces_body<T, TWO, false>(cell, el, st, fa, n_force_blocks, en, walk_parts, nullptr);
+  site_forces_body<T, TWO, false, false>(cell, el, st, fa, n_force_blocks, en, walk_parts, nullptr, nullptr);
 }
 
+// with the gradient's loss beside the energies
+template <typename T>
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 3 : 7) void k_site_forces_loss(
+    Cell cell, ElecSet<T> el, SiteSet<T> st, ForceArgs<T> fa, int n_force_blocks, EnergyArgs en, int walk_parts,
+    LossArgs la) {
+  site_forces_body<T, false, false, true>(cell, el, st, fa, n_force_blocks, en, walk_parts, nullptr, &la);
+}
+
+template <bool LOSS>
 __global__ __launch_bounds__(EWALD_FORCE_THREADS) void k_site_forces_ewald(Cell cell, ElecSet<double> el,
                                                                            SiteSet<double> st, ForceArgs<double> fa,
                                                                            int n_force_blocks, EnergyArgs en,
-                                                                           EwaldField ef) {
-  site_forces_body<double, false, true>(cell, el, st, fa, n_force_blocks, en, 1, &ef);
+                                                                           EwaldField ef, LossArgs la) {
+  site_forces_body<double, false, true, LOSS>(cell, el, st, fa, n_force_blocks, en, 1, &ef, &la);
 }
 
 void launch_site_forces_ewald(hipStream_t s, const Cell& cell, const ElecSet<double>& el, const SiteSet<double>& st,
-                              const ForceArgs<double>& fa, const EwaldField& ef, bool forces, const EnergyArgs* ea) {
+                              const ForceArgs<double>& fa, const EwaldField& ef, bool forces, const EnergyArgs* ea,
+                              const LossArgs* la) {
   const int nfb = forces ? st.n : 0;
   const EnergyArgs e = ea ? *ea : EnergyArgs{};
   if (nfb + (ea ? 1 : 0) == 0) return;
-  hipLaunchKernelGGL(k_site_forces_ewald, dim3(nfb + (ea ? 1 : 0)), dim3(EWALD_FORCE_THREADS), 0, s, cell, el, st, fa,
-                     nfb, e, ef);
+  const dim3 grid(nfb + (ea ? 1 : 0));
+  if (la)
+    hipLaunchKernelGGL(k_site_forces_ewald<true>, grid, dim3(EWALD_FORCE_THREADS), 0, s, cell, el, st, fa, nfb, e, ef,
+                       *la);
+  else
+    hipLaunchKernelGGL(k_site_forces_ewald<false>, grid, dim3(EWALD_FORCE_THREADS), 0, s, cell, el, st, fa, nfb, e, ef,
+                       LossArgs{});
 }
 
 // The same when the pair tiles have already made the site-electrode sums
@@ -525,7 +540,7 @@ void launch_site_pairs_t(hipStream_t s, int n_frames, const PairArgs<T>& pa) {
 template <typename T>
 void launch_site_forces_t(hipStream_t s, int n_frames, const Cell& cell, const ElecSet<T>& el,
                           const SiteSet<T>& st, const ForceArgs<T>& fa, bool forces, const EnergyArgs* ea,
-                          const T* epart) {
+                          const T* epart, const LossArgs* la) {
   // TWO: a second charge set; walk: the kernel walks the electrode atoms
   // itself (no site-electrode sums from the pair tiles; else k_site_forces_g16)
   const bool two = fa.Eb || fa.qb, walk = fa.f_elec == nullptr;
@@ -582,7 +597,9 @@ void launch_site_forces_t(hipStream_t s, int n_frames, const Cell& cell, const E
   const int nfb = forces ? (parts == 2 ? (st.n + 1) / 2 : (st.n + 3) / 4) : 0;
   dim3 grid(nfb + (ea ? 1 : 0), n_frames);
   if (grid.x == 0) return;
-  if (two)
+  if (la)          // (the gradient: one frame, one charge set)
+    hipLaunchKernelGGL(k_site_forces_loss<T>, grid, dim3(256), 0, s, cell, el, st, fa, nfb, e, parts, *la);
+  else if (two)
     hipLaunchKernelGGL((k_site_forces<T, true>), grid, dim3(256), 0, s, cell, el, st, fa, nfb, e, parts);
   else
     hipLaunchKernelGGL((k_site_forces<T, false>), grid, dim3(256), 0, s, cell, el, st, fa, nfb, e, parts);
@@ -597,9 +614,9 @@ template size_t site_pairs_lds<double>(int, bool);
 template size_t site_pairs_lds<float>(int, bool);
 template void launch_site_forces_t<double>(hipStream_t, int, const Cell&, const ElecSet<double>&,
                                            const SiteSet<double>&, const ForceArgs<double>&, bool,
-                                           const EnergyArgs*, const double*);
+                                           const EnergyArgs*, const double*, const LossArgs*);
 template void launch_site_forces_t<float>(hipStream_t, int, const Cell&, const ElecSet<float>&,
                                           const SiteSet<float>&, const ForceArgs<float>&, bool,
-                                          const EnergyArgs*, const float*);
+                                          const EnergyArgs*, const float*, const LossArgs*);
 
 }  // namespace cpm
