@@ -133,7 +133,7 @@ struct cpm_ctx {
   bool pairs_made = false;
   // the MD loop's Lennard-Jones sums to ride in its field pass (set by the
   // loop around its force enqueue), and whether they did
-  const MDArgs* host_lj = nullptr;
+  const LJArgs* host_lj = nullptr;
   bool lj_hosted = false;
   const void* elec_owner = nullptr;
   bool zmask_ok = false;       // K_z <= 256: the field pass can take the mask
@@ -169,6 +169,7 @@ struct cpm_ctx {
 struct cpm_md {
   cpm_ctx* c = nullptr;
   MDArgs a{};
+  LJArgs lj{};
   int charge_every = 5;
   long long step = 0;
   bool started = false;
@@ -713,7 +714,7 @@ int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const
     const bool host_pairs = nf == 1;
     const bool fold = em != 0 && c->fold_pot;
     const bool with_lj = em != 0 && c->host_lj;
-    const MDArgs ljv = with_lj ? *c->host_lj : MDArgs{};
+    const LJArgs ljv = with_lj ? *c->host_lj : LJArgs{};
     c->lj_hosted = with_lj;
     rec(c, CPM_KERNEL_FFT_Z_FIELD, s, [=](hipStream_t s) {
       launch_fft_z_t<T, T2>(s, nf, c->pz, c->za_field, B::G(c), B::c1(c), B::c2(c), fold ? nullptr : B::save(c),
@@ -1968,23 +1969,26 @@ int cpm_md_create(cpm_ctx* c, const cpm_md_desc* d, cpm_md** out) {
     return CPM_OK;
   };
   MDArgs& a = md->a;
-  a.n_site = ns; a.n_mol = d->n_mol; a.n_groups = d->n_groups; a.n_lj_elec = d->n_lj_elec; a.thermostat = 1;
-  a.carbon_sigma = d->carbon_sigma; a.carbon_sqeps = std::sqrt(d->carbon_eps); a.lj_cut = d->lj_cut; a.bond = d->bond;
+  a.n_site = ns; a.n_mol = d->n_mol; a.n_groups = d->n_groups; a.thermostat = 1;
+  LJArgs& l = md->lj;
+  l.n_site = ns; l.n_lj_elec = d->n_lj_elec;
+  l.carbon_sigma = d->carbon_sigma; l.carbon_sqeps = std::sqrt(d->carbon_eps); l.rc2 = d->lj_cut * d->lj_cut; l.irc2 = 1.0 / l.rc2;
+  a.bond = d->bond;
   a.dt = d->dt; a.kt = 0.0083144626 * d->temperature;
-  for (int k = 0; k < 3; ++k) { a.box[k] = c->box[k]; a.inv_box[k] = 1.0 / c->box[k]; }
+  for (int k = 0; k < 3; ++k) { l.box[k] = a.box[k] = c->box[k]; l.inv_box[k] = a.inv_box[k] = 1.0 / c->box[k]; }
   for (int g = 0; g < d->n_groups; ++g) {
     a.nf[g] = 3.0 * nsite_g[g] - ncon_g[g];
     a.Q[g] = a.nf[g] * a.kt * d->tau * d->tau;
   }
-  const double* mass_c; const double* sig_c; const double* eps_c; const int *ms, *mz, *mg, *mo; const double* cx;
+  const double* mass_c; const double2* par; const int *ms, *mz, *mg, *mo; const double* cx;
   double *f_lj, *u_lj, *xi, *eta, *nh_in, *part, *q, *fc, *en;
   int r;
   std::vector<double> zeros(2 * MD_MAX_GROUPS, 0.0);
   std::vector<int> sizes(d->mol_size, d->mol_size + d->n_mol), groups(d->mol_group, d->mol_group + d->n_mol);
-  std::vector<double> sqeps(ns);
+  std::vector<double2> lj_par(ns);
   for (int j = 0; j < ns; ++j) {
     if (!(d->site_eps[j] >= 0.0)) { for (void* p : md->allocs) (void)hipFree(p); delete md; return fail(c, CPM_EINVAL, "epsilon must be >= 0"); }
-    sqeps[j] = std::sqrt(d->site_eps[j]);
+    lj_par[j] = double2{d->site_sigma[j], std::sqrt(d->site_eps[j])};
   }
   // z windows of the Lennard-Jones partners over the electrostatic cell grid:
   // the graphene atoms sorted by wrapped z, and per z layer the (at most
@@ -2018,7 +2022,7 @@ int cpm_md_create(cpm_ctx* c, const cpm_md_desc* d, cpm_md** out) {
   }
   const int reach = (int)std::ceil(pad / wz);                 // layers of sites within lj_cut, the same margin
   const int* crun_d;
-  if ((r = up(&mass_c, d->site_mass, ns)) || (r = up(&sig_c, d->site_sigma, ns)) || (r = up(&eps_c, sqeps.data(), ns)) ||
+  if ((r = up(&mass_c, d->site_mass, ns)) || (r = up(&par, lj_par.data(), ns)) ||
       (r = up(&ms, start.data(), d->n_mol)) || (r = up(&mz, sizes.data(), d->n_mol)) ||
       (r = up(&mg, groups.data(), d->n_mol)) || (r = up(&mo, mol_of.data(), ns)) ||
       (r = up(&cx, cxs.data(), 3 * (size_t)nlj)) || (r = up(&crun_d, crun.data(), 4 * (size_t)ncz)) ||
@@ -2028,10 +2032,9 @@ int cpm_md_create(cpm_ctx* c, const cpm_md_desc* d, cpm_md** out) {
       (r = up(&nh_in, zeros.data(), 2 * MD_MAX_GROUPS)) || (r = up(&part, (const double*)nullptr, (size_t)md_workgroups(d->n_mol) * MD_PART)) || (r = up(&q, (const double*)nullptr, c->n_elec)) ||
       (r = up(&fc, (const double*)nullptr, 3 * (size_t)ns)) || (r = up(&en, zeros.data(), 2)))
     return bad(r);
-  a.mass = mass_c; a.sigma = sig_c; a.sqeps = eps_c; a.mol_start = ms; a.mol_size = mz; a.mol_group = mg; a.mol_of = mo;
-  a.cx = cx; a.f_lj = f_lj; a.u_lj = u_lj; a.xi = xi; a.eta = eta; a.nh_in = nh_in; a.md_part = part; a.f_c = fc; a.energy = en;
-  a.cell_start = c->d_cell_start; a.order = c->d_order; a.carbon_run = crun_d;
-  a.nc_z = ncz; a.nxy = cl.nc[0] * cl.nc[1]; a.lj_reach = reach; a.Lz = Lz;
+  l.par = par; l.mol_of = mo; l.cx = cx; l.f_lj = f_lj; l.u_lj = u_lj; l.carbon_run = crun_d;
+  l.nc_z = ncz; l.nxy = cl.nc[0] * cl.nc[1]; l.lj_reach = reach;
+  a.mass = mass_c; a.mol_start = ms; a.mol_size = mz; a.mol_group = mg; a.f_lj = f_lj; a.u_lj = u_lj; a.xi = xi; a.eta = eta; a.nh_in = nh_in; a.md_part = part; a.f_c = fc; a.energy = en;
   md->d_q = q; md->d_fc = fc; md->d_energy = en;
   if (c->kspace == CPM_KSPACE_PPPM && !c->d_c1e && dalloc(c, &c->d_c1e, (size_t)c->mi.M) != CPM_OK)
     return bad(CPM_ENOMEM);
@@ -2051,9 +2054,10 @@ int md_forces(cpm_md* md, double* x, double dv, bool update) {
   // the sorted charges of the last update are reused, if nothing else has
   // run on the context since
   c->elec_mode = (!update && c->elec_owner == md) ? 2 : 1;
-  md->a.cell_start = c->d_cell_start;
-  md->a.order = c->d_order;
-  c->host_lj = &md->a;                 // the Lennard-Jones sums ride in the field pass (PPPM)
+  LJArgs& l = md->lj;
+  l.sx = c->d_sx; l.sy = c->d_sy; l.sz = c->d_sz;
+  l.cell_start = c->d_cell_start; l.order = c->d_order;
+  c->host_lj = &l;                     // the Lennard-Jones sums ride in the field pass (PPPM)
   c->lj_hosted = false;
   const int r = update ? enqueue_solve<double>(c, x, dv, md->d_q, md->d_fc, md->d_energy)
                        : enqueue_forces_at<double>(c, x, dv, md->d_q, md->d_fc);
@@ -2061,7 +2065,7 @@ int md_forces(cpm_md* md, double* x, double dv, bool update) {
   c->host_lj = nullptr;
   TRY(r);
   if (c->d_c1e) c->elec_owner = md;
-  if (!c->lj_hosted) launch_lj(c->stream, md->a);
+  if (!c->lj_hosted) launch_lj(c->stream, l);
   c->lj_hosted = false;
   return CPM_OK;
 }

@@ -98,6 +98,25 @@ __device__ __forceinline__ T wave_sum8(const T (&v)[8]) {
   return c;
 }
 
+// the same for four values: lane l holds the total of value l >> 4
+template <typename T>
+__device__ __forceinline__ T wave_sum4(const T (&v)[4]) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  T a[2];
+  const bool h32 = lane & 32, h16 = lane & 16;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const T keep = h32 ? v[i + 2] : v[i], send = h32 ? v[i] : v[i + 2];
+    a[i] = keep + __shfl_xor(send, 32, WAVE);
+  }
+  T c = (h16 ? a[1] : a[0]) + __shfl_xor(h16 ? a[0] : a[1], 16, WAVE);
+  c += __shfl_xor(c, 8, WAVE);
+  c += __shfl_xor(c, 4, WAVE);
+  c += __shfl_xor(c, 2, WAVE);
+  c += __shfl_xor(c, 1, WAVE);
+  return c;
+}
+
 // value of v in lane l (l uniform), for every lane
 __device__ __forceinline__ float read_lane(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
@@ -521,7 +540,7 @@ template <typename T>
 void launch_gather_b_t(hipStream_t s, int n_frames, int n_elec, int P3, const int* gidx, const T* gw,
                        const T* phi, int M, const T* phi_real, double* b, const SlabTerms& sl = SlabTerms{});
 
-struct MDArgs;   // the MD loop's arguments (below)
+struct LJArgs;   // the MD loop's Lennard-Jones arguments (below)
 
 // FFT passes (k_fft.hip)
 template <typename T, typename T2>
@@ -544,7 +563,7 @@ template <typename T, typename T2>
 void launch_fft_z_t(hipStream_t s, int n_frames, const FFTPlan1D& pz, const ZPassArgs& za, const T* G,
                     T2* data1, T2* data2, T2* save, int add_saved, double* energy_part, bool z_pass = true,
                     const RealBArgs<T>* rb = nullptr, const PairArgs<T>* pa = nullptr, const ZMask* zm = nullptr,
-                    const T2* in1 = nullptr, const MDArgs* lj = nullptr);
+                    const T2* in1 = nullptr, const LJArgs* lj = nullptr);
 // (in1: the input spectrum if not data1, which then only takes the result;
 // the masked many-frame launches work in place)
 template <typename T, typename T2>
@@ -693,16 +712,18 @@ constexpr int MD_THERMO = 4;          // per-step record: KE, U_LJ, E_cp (last u
 constexpr int MD_PART = MD_MAX_GROUPS + 1;   // per-workgroup partials: sum m v^2 per group, sum U_LJ
 inline int md_workgroups(int n_mol) { return (n_mol + WAVE - 1) / WAVE; }   // integrator: a wavefront per 64 molecules
 
-struct MDArgs {
-  int n_site, n_mol, n_groups, n_lj_elec, thermostat;
-  double* x; double* v;                 // [3][n_site] positions (nm), velocities (nm/ps)
-  double* f_lj;                         // [3][n_site] kJ/mol/nm (written by k_lj)
-  const double* f_c;                    // [3][n_site] Coulomb force, eV/nm
-  double* u_lj;                         // [n_site] Lennard-Jones energy share per site (written by k_lj)
-  const double* mass; const double* sigma; const double* sqeps;   // [n_site] (sqeps: sqrt(epsilon))
-  const int* mol_start; const int* mol_size; const int* mol_group; const int* mol_of;
+// the Lennard-Jones sums (lj.h); apart from the integrator's arguments, which
+// the field pass that hosts them would otherwise carry too
+constexpr int LJ_WAVES = 4;           // wavefronts of a site's workgroup
+struct LJArgs {
+  int n_site, n_lj_elec;
+  const double* sx; const double* sy; const double* sz;   // the binning's sorted wrapped positions
+  double* f_lj;                         // [3][n_site] kJ/mol/nm
+  double* u_lj;                         // [n_site] energy share per site
+  const double2* par;                   // [n_site] sigma, sqrt(epsilon)
+  const int* mol_of;
   const double* cx;                     // [3][n_lj_elec] graphene atoms, sorted by wrapped z
-  double carbon_sigma, carbon_sqeps, lj_cut, bond, dt, kt;
+  double carbon_sigma, carbon_sqeps, rc2, irc2;   // irc2 = 1 / rc2
   // partners by z window (the electrostatic binning of the same positions):
   // a site of z layer cz (of nc_z layers of the cell grid, nxy cells each)
   // meets the sites of layers cz - lj_reach .. cz + lj_reach (all of them when
@@ -712,7 +733,18 @@ struct MDArgs {
   // site indices
   const int* cell_start; const int* order; const int* carbon_run;
   int nc_z, nxy, lj_reach;
-  double Lz;
+  double box[3], inv_box[3];
+};
+
+struct MDArgs {
+  int n_site, n_mol, n_groups, thermostat;
+  double* x; double* v;                 // [3][n_site] positions (nm), velocities (nm/ps)
+  const double* f_lj;                   // [3][n_site] kJ/mol/nm (LJArgs)
+  const double* f_c;                    // [3][n_site] Coulomb force, eV/nm
+  const double* u_lj;                   // [n_site] Lennard-Jones energy share per site (LJArgs)
+  const double* mass;                   // [n_site]
+  const int* mol_start; const int* mol_size; const int* mol_group;
+  double bond, dt, kt;
   double box[3], inv_box[3];
   double nf[MD_MAX_GROUPS], Q[MD_MAX_GROUPS];
   double* xi; double* eta;              // [n_groups] thermostat state (device)
@@ -721,7 +753,7 @@ struct MDArgs {
   const double* energy;                 // [2] the last charge update's {U_coul, E_cp} (eV)
   double* thermo_out;                   // [step][MD_THERMO] or nullptr
 };
-void launch_lj(hipStream_t s, const MDArgs& a);
+void launch_lj(hipStream_t s, const LJArgs& a);
 void launch_md_integrate(hipStream_t s, const MDArgs& a, int mode, int rec_step);
 
 }  // namespace cpm

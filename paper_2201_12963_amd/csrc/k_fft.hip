@@ -874,7 +874,7 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
                                            T2* __restrict__ save, int add_saved,
                                            double* __restrict__ energy_part, int n_z_blocks,
                                            const RealBArgs<T>& rb, const PairArgs<T>& pa, int lpw, int ek_stride,
-                                           const ZMask& zm, const MDArgs* lj = nullptr) {
+                                           const ZMask& zm, const LJArgs* lj = nullptr) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double red[8];
   if (!MULTI && (int)blockIdx.x >= n_z_blocks) {
@@ -888,7 +888,7 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
       const int g = xcd_block(hb, rb.n_blocks) * (blockDim.x / WAVE) + (threadIdx.x >> 6);
       if (g < rb.el.n) real_b_wave(rb.cell, rb.alpha, rb.eta, rb.rc2, rb.el, rb.st, rb.phi_out, g, blockIdx.y, qbuf, nullptr, rb.b_out, &rb.sl);
     } else if (LJ && hb >= rb.n_blocks + pa.n_blocks) {
-      lj_site<4>(*lj, hb - rb.n_blocks - pa.n_blocks);
+      lj_site(*lj, hb - rb.n_blocks - pa.n_blocks);
     } else {
       const int j = xcd_block(hb - rb.n_blocks, pa.n_blocks) * (blockDim.x / WAVE) + (threadIdx.x >> 6);
       if (j < pa.st.n) site_pairs_wave(pa.cell, pa.st, pa.alpha, pa.rc2, pa.f_pair, pa.u_site, j, blockIdx.y, qbuf);
@@ -1070,7 +1070,7 @@ __global__ __launch_bounds__(256) void k_fft_z_sep(FFTPlan1D pz, ZPassArgs za, c
                                                    T2* __restrict__ data2, T2* __restrict__ save, int add_saved,
                                                    double* __restrict__ energy_part, int n_z_blocks,
                                                    RealBArgs<T> rb, PairArgs<T> pa, int lpw, int ek_stride,
-                                                   MDArgs lj) {
+                                                   LJArgs lj) {
   fft_z_body<T, T2, MULTI, false, true, true>(pz, za, G, in1, data1, data2, save, add_saved, energy_part,
                                               n_z_blocks, rb, pa, lpw, ek_stride, ZMask{}, &lj);
 }
@@ -1211,7 +1211,7 @@ template <typename T, typename T2>
 void launch_fft_z_t(hipStream_t s, int n_frames, const FFTPlan1D& pz, const ZPassArgs& za, const T* G,
                     T2* data1, T2* data2, T2* save, int add_saved, double* energy_part, bool z_pass,
                     const RealBArgs<T>* rb, const PairArgs<T>* pa, const ZMask* zm, const T2* in1,
-                    const MDArgs* lj) {
+                    const LJArgs* lj) {
   if (!in1) in1 = data1;
   if (lj && (in1 == data1 || n_frames != 1)) {
     std::fprintf(stderr, "cpm: the Lennard-Jones sums ride only in a one-frame field pass with a kept input\n");
@@ -1263,10 +1263,10 @@ void launch_fft_z_t(hipStream_t s, int n_frames, const FFTPlan1D& pz, const ZPas
                        add_saved, energy_part, nzb, r, p, 1, za.n_blocks, *zm);
   else if (in1 != data1 && lpw > 1)
     hipLaunchKernelGGL((k_fft_z_sep<T, T2, true>), grid, dim3(256), lds, s, pz, zl, G, in1, data1, data2, save,
-                       add_saved, energy_part, nzb, r, p, lpw, za.n_blocks, lj ? *lj : MDArgs{});
+                       add_saved, energy_part, nzb, r, p, lpw, za.n_blocks, lj ? *lj : LJArgs{});
   else if (in1 != data1)
     hipLaunchKernelGGL((k_fft_z_sep<T, T2, false>), grid, dim3(256), lds, s, pz, zl, G, in1, data1, data2, save,
-                       add_saved, energy_part, nzb, r, p, 1, za.n_blocks, lj ? *lj : MDArgs{});
+                       add_saved, energy_part, nzb, r, p, 1, za.n_blocks, lj ? *lj : LJArgs{});
   else if (lpw > 1)
     hipLaunchKernelGGL((k_fft_z<T, T2, true>), grid, dim3(256), lds, s, pz, zl, G, data1, data2, save, add_saved,
                        energy_part, nzb, r, p, lpw, za.n_blocks);
@@ -1284,11 +1284,11 @@ template void launch_fft_xy_t<float, float2>(hipStream_t, int, const FFTPlan1D&,
 template void launch_fft_z_t<double, double2>(hipStream_t, int, const FFTPlan1D&, const ZPassArgs&,
                                               const double*, double2*, double2*, double2*, int, double*, bool,
                                               const RealBArgs<double>*, const PairArgs<double>*, const ZMask*,
-                                              const double2*, const MDArgs*);
+                                              const double2*, const LJArgs*);
 template void launch_fft_z_t<float, float2>(hipStream_t, int, const FFTPlan1D&, const ZPassArgs&,
                                             const float*, float2*, float2*, float2*, int, double*, bool,
                                             const RealBArgs<float>*, const PairArgs<float>*, const ZMask*,
-                                            const float2*, const MDArgs*);
+                                            const float2*, const LJArgs*);
 template void launch_fft_xy_field_inv_t<double, double2>(hipStream_t, int, const FFTPlan1D&, const FFTPlan1D&,
                                                          int, const double2*, const double2*, double*, size_t,
                                                          const InterpArgs<double>*);

@@ -31,9 +31,8 @@ namespace cpm {
 constexpr double KB_KJ = 0.0083144626;      // kJ/mol/K
 constexpr double EV_KJ = 96.48533212;       // kJ/mol per eV
 
-template <int NW>
-__global__ __launch_bounds__(NW * WAVE) void k_lj(MDArgs a) {
-  lj_site<NW>(a, blockIdx.x);
+__global__ __launch_bounds__(LJ_WAVES * WAVE) void k_lj(LJArgs a) {
+  lj_site(a, blockIdx.x);
 }
 
 // minimum-image difference of two sites' coordinates along axis d
@@ -290,9 +289,8 @@ __global__ __launch_bounds__(WAVE) void k_md_start(MDArgs a, int mode, int rec_s
     for (int g = 0; g < a.n_groups; ++g) { a.xi[g] = xi[g]; a.eta[g] = eta[g]; }
 }
 
-constexpr int LJ_WAVES = 4;
-void launch_lj(hipStream_t s, const MDArgs& a) {
-  hipLaunchKernelGGL(k_lj<LJ_WAVES>, dim3(a.n_site), dim3(LJ_WAVES * WAVE), 0, s, a);
+void launch_lj(hipStream_t s, const LJArgs& a) {
+  hipLaunchKernelGGL(k_lj, dim3(a.n_site), dim3(LJ_WAVES * WAVE), 0, s, a);
 }
 void launch_md_integrate(hipStream_t s, const MDArgs& a, int mode, int rec_step) {
   const int nb = md_workgroups(a.n_mol);

@@ -1,5 +1,5 @@
 // Lennard-Jones forces and energy share of one electrolyte site, by one
-// workgroup of NW wavefronts whose threads share the partners: the sites and
+// workgroup of LJ_WAVES wavefronts whose threads share the partners: the sites and
 // graphene atoms of the z layers within the cutoff (the layers of the
 // electrostatic cell grid, whose binning of the same positions has run),
 // minimum image, pairs of one molecule excluded, energy shifted to zero at
@@ -9,35 +9,48 @@
 #pragma once
 #include "common.h"
 #include "bin.h"
+#include "pairs.h"
 
 namespace cpm {
 
-template <int NW>
-__device__ __forceinline__ void lj_site(const MDArgs& a, int i) {
-  __shared__ double red[NW][4];
-  const double xi = a.x[i], yi = a.x[a.n_site + i], zi = a.x[2 * a.n_site + i];
-  const double si = a.sigma[i], qi = a.sqeps[i];
+// Bound by latency and by the field pass's occupancy (its pair walk leaves 3
+// waves per SIMD): a chain of dependent reads per site, so the partners come
+// from the binning's sorted copies, coalesced, LJ_AHEAD per thread in flight
+// with their parameters (one by one through the sort's index, an MD step of
+// 1280 sites takes 57.7 us; so, 54.8).  Two wavefronts per site or one: 55.9,
+// 56.3, fewer reads in flight.  No FP64 divisions: 1 / r^2 is the hardware's
+// estimate with two Newton steps.
+constexpr int LJ_AHEAD = 4;
+
+__device__ __forceinline__ void lj_site(const LJArgs& a, int is) {
+  constexpr int NT = LJ_WAVES * WAVE;
+  __shared__ double red[LJ_WAVES][4];
+  const double xi = a.sx[is], yi = a.sy[is], zi = a.sz[is];
+  const int i = a.order[is];
+  const double2 pi = a.par[i];
   const int mi = a.mol_of[i];
-  const double rc2 = a.lj_cut * a.lj_cut;
-  double fx = 0.0, fy = 0.0, fz = 0.0, u = 0.0, uw = 0.5;   // a site-site pair's energy is shared by its sites
-  auto pair = [&](double dx, double dy, double dz, double sig, double eps) {
-    dx -= a.box[0] * rint(dx * a.inv_box[0]);
-    dy -= a.box[1] * rint(dy * a.inv_box[1]);
-    dz -= a.box[2] * rint(dz * a.inv_box[2]);
-    const double r2 = dx * dx + dy * dy + dz * dz;
-    if (r2 < rc2 && r2 > 0.0) {
-      const double ir2 = 1.0 / r2;
-      const double t = sig * sig * ir2, s6 = t * t * t;
-      const double tc = sig * sig / rc2, c6 = tc * tc * tc;
-      const double fr = 24.0 * eps * (2.0 * s6 * s6 - s6) * ir2;
-      fx += fr * dx; fy += fr * dy; fz += fr * dz;
-      u += uw * (4.0 * eps * (s6 * s6 - s6) - 4.0 * eps * (c6 * c6 - c6));
-    }
+  const double rc2 = a.rc2, irc2 = a.irc2;
+  double fx = 0.0, fy = 0.0, fz = 0.0, u = 0.0;
+  // squared minimum-image distance, the displacement in d
+  auto dist2 = [&](double (&d)[3]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) d[k] -= a.box[k] * rint(d[k] * a.inv_box[k]);
+    return d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
   };
-  // the z layer of the site, by the binning's arithmetic on the same
-  // coordinate, and the sorted-site ranges of the layers within lj_reach
+  // eps4: 4 epsilon; uw: the site's share of the pair's energy (half of a
+  // site-site pair's)
+  auto pair = [&](const double (&d)[3], double r2, double sig, double eps4, double uw) {
+    const double ir2 = recip_nr(r2), s2 = sig * sig;
+    const double t = s2 * ir2, s6 = t * t * t, tc = s2 * irc2, c6 = tc * tc * tc;
+    const double e = s6 * s6 - s6;
+    const double fr = 6.0 * eps4 * fma(s6, s6, e) * ir2;
+    fx = fma(fr, d[0], fx); fy = fma(fr, d[1], fy); fz = fma(fr, d[2], fz);
+    u = fma(uw * eps4, e - (c6 * c6 - c6), u);
+  };
+  // the z layer of the site and the sorted-site ranges of the layers within
+  // lj_reach (its margin covers a coordinate on a layer's face)
   int cz;
-  wrap_and_cell(zi, a.Lz, a.nc_z, cz);
+  wrap_and_cell(zi, a.box[2], a.nc_z, cz);
   const int* cs = a.cell_start;
   int lo0 = 0, hi0 = a.n_site, lo1 = 0, hi1 = 0;
   if (2 * a.lj_reach + 1 < a.nc_z) {
@@ -46,28 +59,52 @@ __device__ __forceinline__ void lj_site(const MDArgs& a, int i) {
     else if (lb >= a.nc_z) { lo0 = cs[la * a.nxy]; hi1 = cs[(lb + 1 - a.nc_z) * a.nxy]; }
     else { lo0 = cs[la * a.nxy]; hi0 = cs[(lb + 1) * a.nxy]; }
   }
-  auto site = [&](int s) {
-    const int j = a.order[s];
-    if (a.mol_of[j] == mi) return;
-    pair(xi - a.x[j], yi - a.x[a.n_site + j], zi - a.x[2 * a.n_site + j], 0.5 * (si + a.sigma[j]), qi * a.sqeps[j]);
-  };
-  for (int s = lo0 + threadIdx.x; s < hi0; s += blockDim.x) site(s);
-  for (int s = lo1 + threadIdx.x; s < hi1; s += blockDim.x) site(s);
-  uw = 1.0;
-  const double sc = 0.5 * (si + a.carbon_sigma), ec = qi * a.carbon_sqeps;
   const int* cr = a.carbon_run + 4 * cz;
+  const int c0 = cr[0], c1 = cr[2], m0 = cr[1] - c0, m = m0 + cr[3] - c1;
+  // the four ranges as one run of partners, LJ_AHEAD of them per thread
+  // loaded together, then their parameters together: two latencies a chunk
+  const int n0 = hi0 - lo0, n = n0 + hi1 - lo1;
+  for (int t0 = threadIdx.x; t0 < n + m; t0 += LJ_AHEAD * NT) {
+    double p[LJ_AHEAD][3];
+    int id[LJ_AHEAD];                          // the site's index, or -1
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
-    for (int j = cr[2 * h] + threadIdx.x; j < cr[2 * h + 1]; j += blockDim.x)
-      pair(xi - a.cx[j], yi - a.cx[a.n_lj_elec + j], zi - a.cx[2 * a.n_lj_elec + j], sc, ec);
-  fx = wave_sum(fx); fy = wave_sum(fy); fz = wave_sum(fz); u = wave_sum(u);
-  const int w = threadIdx.x / WAVE;
-  if ((threadIdx.x & (WAVE - 1)) == 0) { red[w][0] = fx; red[w][1] = fy; red[w][2] = fz; red[w][3] = u; }
+    for (int k = 0; k < LJ_AHEAD; ++k) {
+      const int t = t0 + k * NT;
+      id[k] = -1;
+      if (t < n) {
+        const int s = t < n0 ? lo0 + t : lo1 + t - n0;
+        p[k][0] = a.sx[s]; p[k][1] = a.sy[s]; p[k][2] = a.sz[s]; id[k] = a.order[s];
+      } else if (t < n + m) {
+        const int q = t - n, j = q < m0 ? c0 + q : c1 + q - m0;
+        p[k][0] = a.cx[j]; p[k][1] = a.cx[a.n_lj_elec + j]; p[k][2] = a.cx[2 * a.n_lj_elec + j];
+      }
+    }
+    double2 pj[LJ_AHEAD];
+    int mj[LJ_AHEAD];
+#pragma unroll
+    for (int k = 0; k < LJ_AHEAD; ++k) {
+      pj[k] = double2{a.carbon_sigma, a.carbon_sqeps};
+      mj[k] = -1;
+      if (id[k] >= 0) { pj[k] = a.par[id[k]]; mj[k] = a.mol_of[id[k]]; }
+    }
+#pragma unroll
+    for (int k = 0; k < LJ_AHEAD; ++k) {
+      if (t0 + k * NT >= n + m) break;
+      double d[3] = {xi - p[k][0], yi - p[k][1], zi - p[k][2]};
+      const double r2 = dist2(d);
+      if (r2 < rc2 && r2 > 0.0 && mj[k] != mi)
+        pair(d, r2, 0.5 * (pi.x + pj[k].x), 4.0 * pi.y * pj[k].y, mj[k] < 0 ? 1.0 : 0.5);
+    }
+  }
+  const double v[4] = {fx, fy, fz, u};
+  const double tot = wave_sum4(v);             // lane l: value l >> 4
+  const int w = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+  if ((lane & 15) == 0) red[w][lane >> 4] = tot;
   __syncthreads();
   if (threadIdx.x < 4) {
     double t = red[0][threadIdx.x];
 #pragma unroll
-    for (int k = 1; k < NW; ++k) t += red[k][threadIdx.x];
+    for (int k = 1; k < LJ_WAVES; ++k) t += red[k][threadIdx.x];
     if (threadIdx.x < 3) a.f_lj[threadIdx.x * a.n_site + i] = t;
     else a.u_lj[i] = t;
   }
