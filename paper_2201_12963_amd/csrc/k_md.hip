@@ -46,12 +46,14 @@ __device__ __forceinline__ double md_diff(const MDArgs& a, double p, double q, i
 // by g_c sigma_sc v_c / m_s for each c (sigma = +1 on the constraint's first
 // site, -1 on its second, v_c the constraint's vector), so the bond vector
 // of constraint a changes by sum_b K_ab g_b v_b with
-// K_ab = sigma(i_a, b) / m(i_a) - sigma(j_a, b) / m(j_a).
+// K_ab = sigma(i_a, b) / m(i_a) - sigma(j_a, b) / m(j_a).  The masses come in
+// as reciprocals w: a thread runs its molecule alone, so each FP64 division
+// (about fifteen dependent instructions) is time on the step's chain.
 
-__device__ __forceinline__ double md_kab(int a, int b, const double m[3]) {
+__device__ __forceinline__ double md_kab(int a, int b, const double w[3]) {
   const int ci[3] = {0, 0, 1}, cj[3] = {1, 2, 2};
   auto sig = [&](int s, int c) { return s == ci[c] ? 1.0 : (s == cj[c] ? -1.0 : 0.0); };
-  return sig(ci[a], b) / m[ci[a]] - sig(cj[a], b) / m[cj[a]];
+  return sig(ci[a], b) * w[ci[a]] - sig(cj[a], b) * w[cj[a]];
 }
 
 // x = M^-1 y for a 3 x 3 matrix (Cramer's rule; M is well conditioned here:
@@ -71,7 +73,7 @@ __device__ __forceinline__ void solve3(const double M[3][3], const double y[3], 
 // |p_i - p_j| = d for all three constraints, by Newton steps on the three
 // multipliers together (the same fixed point as one constraint at a time,
 // reached in a few steps)
-__device__ void shake3(const MDArgs& a, double p[3][3], const double o[3][3], const double m[3]) {
+__device__ void shake3(const MDArgs& a, double p[3][3], const double o[3][3], const double w[3]) {
   const int ci[3] = {0, 0, 1}, cj[3] = {1, 2, 2};
   const double d[3] = {a.bond, a.bond, a.bond * 1.7320508075688772};
   double ro[3][3];                                     // [constraint][axis], fixed during the solve
@@ -79,7 +81,7 @@ __device__ void shake3(const MDArgs& a, double p[3][3], const double o[3][3], co
     _Pragma("unroll") for (int k = 0; k < 3; ++k) ro[c][k] = md_diff(a, o[k][ci[c]], o[k][cj[c]], k);
   double K[3][3];
   _Pragma("unroll") for (int x = 0; x < 3; ++x)
-    _Pragma("unroll") for (int y = 0; y < 3; ++y) K[x][y] = md_kab(x, y, m);
+    _Pragma("unroll") for (int y = 0; y < 3; ++y) K[x][y] = md_kab(x, y, w);
   for (int it = 0; it < MD_MAX_ITER; ++it) {
     double r[3][3], f[3];
     bool done = true;
@@ -96,15 +98,15 @@ __device__ void shake3(const MDArgs& a, double p[3][3], const double o[3][3], co
     solve3(J, f, g);
     _Pragma("unroll") for (int c = 0; c < 3; ++c)
       _Pragma("unroll") for (int k = 0; k < 3; ++k) {
-        p[k][ci[c]] -= g[c] * ro[c][k] / m[ci[c]];
-        p[k][cj[c]] += g[c] * ro[c][k] / m[cj[c]];
+        p[k][ci[c]] -= g[c] * ro[c][k] * w[ci[c]];
+        p[k][cj[c]] += g[c] * ro[c][k] * w[cj[c]];
       }
   }
 }
 
 // RATTLE: remove the velocity components along the three constraints, a
 // linear 3 x 3 system for the multipliers solved at once
-__device__ void rattle3(const MDArgs& a, double v[3][3], const double p[3][3], const double m[3]) {
+__device__ void rattle3(const MDArgs& a, double v[3][3], const double p[3][3], const double w[3]) {
   const int ci[3] = {0, 0, 1}, cj[3] = {1, 2, 2};
   double r[3][3], vr[3];
   _Pragma("unroll") for (int c = 0; c < 3; ++c) {
@@ -115,25 +117,26 @@ __device__ void rattle3(const MDArgs& a, double v[3][3], const double p[3][3], c
   double M[3][3], kk[3];
   _Pragma("unroll") for (int x = 0; x < 3; ++x)
     _Pragma("unroll") for (int y = 0; y < 3; ++y)
-      M[x][y] = md_kab(x, y, m) * (r[x][0] * r[y][0] + r[x][1] * r[y][1] + r[x][2] * r[y][2]);
+      M[x][y] = md_kab(x, y, w) * (r[x][0] * r[y][0] + r[x][1] * r[y][1] + r[x][2] * r[y][2]);
   solve3(M, vr, kk);
   _Pragma("unroll") for (int c = 0; c < 3; ++c)
     _Pragma("unroll") for (int k = 0; k < 3; ++k) {
-      v[k][ci[c]] -= kk[c] * r[c][k] / m[ci[c]];
-      v[k][cj[c]] += kk[c] * r[c][k] / m[cj[c]];
+      v[k][ci[c]] -= kk[c] * r[c][k] * w[ci[c]];
+      v[k][cj[c]] += kk[c] * r[c][k] * w[cj[c]];
     }
 }
 
 // one molecule's sites (up to 3) between global memory and registers
 struct MolRegs {
   int s0, n, g;
-  double p[3][3], v[3][3], m[3];
+  double p[3][3], v[3][3], m[3], w[3];   // w: 1 / m
 };
 
 __device__ __forceinline__ void mol_load(const MDArgs& a, int mol, MolRegs& r) {
   r.s0 = a.mol_start[mol]; r.n = a.mol_size[mol]; r.g = a.mol_group[mol];
   _Pragma("unroll") for (int s = 0; s < 3; ++s) if (s < r.n) {
     r.m[s] = a.mass[r.s0 + s];
+    r.w[s] = 1.0 / r.m[s];
     _Pragma("unroll") for (int k = 0; k < 3; ++k) {
       r.p[k][s] = a.x[k * a.n_site + r.s0 + s];
       r.v[k][s] = a.v[k * a.n_site + r.s0 + s];
@@ -187,8 +190,8 @@ __global__ __launch_bounds__(WAVE) void k_md_end(MDArgs a, int mode) {
     mol_load(a, mol, r);
     if (mode & 1)
       _Pragma("unroll") for (int s = 0; s < 3; ++s) if (s < r.n)
-        _Pragma("unroll") for (int k = 0; k < 3; ++k) r.v[k][s] += 0.5 * a.dt * mol_force(a, r, k, s) / r.m[s];
-    if ((mode & 5) && r.n == 3) rattle3(a, r.v, r.p, r.m);
+        _Pragma("unroll") for (int k = 0; k < 3; ++k) r.v[k][s] += 0.5 * a.dt * mol_force(a, r, k, s) * r.w[s];
+    if ((mode & 5) && r.n == 3) rattle3(a, r.v, r.p, r.w);
     if (mode & 5)
       _Pragma("unroll") for (int s = 0; s < 3; ++s) if (s < r.n)
         _Pragma("unroll") for (int k = 0; k < 3; ++k) a.v[k * a.n_site + r.s0 + s] = r.v[k][s];
@@ -267,18 +270,19 @@ __global__ __launch_bounds__(WAVE) void k_md_start(MDArgs a, int mode, int rec_s
         if ((mode & 2) && nh) r.v[k][s] *= c2;
       }
     if (mode & 2) {
+      const double inv_dt = 1.0 / a.dt;
       double o[3][3];
       _Pragma("unroll") for (int s = 0; s < 3; ++s) if (s < r.n)
         _Pragma("unroll") for (int k = 0; k < 3; ++k) {
           o[k][s] = r.p[k][s];
-          r.v[k][s] += 0.5 * a.dt * fm[k][s] / r.m[s];
+          r.v[k][s] += 0.5 * a.dt * fm[k][s] * r.w[s];
           r.p[k][s] += a.dt * r.v[k][s];
         }
-      if (r.n == 3) shake3(a, r.p, o, r.m);
+      if (r.n == 3) shake3(a, r.p, o, r.w);
       _Pragma("unroll") for (int s = 0; s < 3; ++s) if (s < r.n)
         _Pragma("unroll") for (int k = 0; k < 3; ++k) {
           a.x[k * a.n_site + r.s0 + s] = r.p[k][s];
-          a.v[k * a.n_site + r.s0 + s] = (r.p[k][s] - o[k][s]) / a.dt;
+          a.v[k * a.n_site + r.s0 + s] = (r.p[k][s] - o[k][s]) * inv_dt;
         }
     } else {
       _Pragma("unroll") for (int s = 0; s < 3; ++s) if (s < r.n)
