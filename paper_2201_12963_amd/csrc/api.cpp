@@ -92,6 +92,8 @@ struct cpm_ctx {
   int batch_chunk = 0;                     // frames per batched launch chosen by the tuner (0: not yet)
   int pair_tsplit = 1;                     // batched site-pair tiles: workgroups per cell (tuned)
   int *d_fwd_n = nullptr, *d_fwd_lo = nullptr, *d_fwd_hi = nullptr;   // forward stencils (no images only)
+  int pair_grp = 1;                        // cells per item of the batched pair tiles
+  int *d_grun_n = nullptr, *d_grun_lo = nullptr, *d_grun_hi = nullptr;   // electrode runs per item (pair_grp > 1)
   // k-space field mesh of the electrode charges S c alone (batched dV sweep)
   double* d_ESc = nullptr;
   float* d_EScf = nullptr;
@@ -512,13 +514,24 @@ template <> struct Bufs<float> {
   static const float* val(cpm_ctx* c) { return c->d_valf; }
 };
 
+constexpr int PAIR_FILL = 1600;   // workgroups of a many-frame pair launch (about six per CU)
+
 // the site-site sums of nf frames: one frame, a wavefront per site (short
 // chains, all in flight at once); many frames, cell tiles
 template <typename T>
 PairArgs<T> pair_args(cpm_ctx* c, int nf) {
   PairArgs<T> pa{};
   pa.tsplit = nf == 1 ? 0 : c->pair_tsplit;
-  pa.n_blocks = c->n_site == 0 ? 0 : pa.tsplit > 0 ? c->cell.n_cells * pa.tsplit : (c->n_site + 3) / 4;
+  pa.grp = pa.tsplit > 0 ? c->pair_grp : 1;
+  // few frames: a layer's item in up to as many shares as it has cells, until
+  // there are PAIR_FILL workgroups (16 frames of 1280 sites: 1, 2, 4, 8 shares
+  // 255, 221, 213, 234 us a batch; 64 frames 414, 377, 407, 518; 256 frames
+  // 1095, 1105, 1268, 1742)
+  if (pa.grp > 1) {
+    const int items = nf * (c->cell.n_cells / pa.grp);
+    pa.tsplit = std::max(pa.tsplit, std::min(pa.grp, (PAIR_FILL + items - 1) / items));
+  }
+  pa.n_blocks = c->n_site == 0 ? 0 : pa.tsplit > 0 ? c->cell.n_cells / pa.grp * pa.tsplit : (c->n_site + 3) / 4;
   pa.cell = c->cell;
   pa.st = Bufs<T>::sites(c);
   pa.alpha = (T)c->alpha;
@@ -670,6 +683,7 @@ int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const
     // tiles run after the charge solve: they take the site-electrode pairs
     // too, and the site-force kernel then skips its own electrode walk
     pa.el = B::elec(c);
+    if (pa.grp > 1) { pa.el.run_n = c->d_grun_n; pa.el.run_lo = c->d_grun_lo; pa.el.run_hi = c->d_grun_hi; }
     pa.eta = fa.eta;
     pa.qa_s = qa_s;
     pa.qa_stride = qa_stride;
@@ -1423,6 +1437,33 @@ int cpm_create(const cpm_desc* d, void* hip_stream, cpm_ctx** out) {
         else { rlo[base + k] = lo; rhi[base + k] = hi; ++k; }
       }
     rn[cc2] = k;
+  }
+  // Items of the batched pair tiles.  With at most three cells along x and y
+  // the cells of a z layer share one stencil, so a layer is one item: its
+  // first cell's forward stencil holds the others' (a forward half holds the
+  // stencil cells of no smaller index), and its electrode runs are the union
+  // of theirs.  A quarter of the workgroups (2 x 2 cells) stage a quarter of
+  // the candidates.
+  if (no_img && cl.nc[0] <= 3 && cl.nc[1] <= 3 && cl.nc[0] * cl.nc[1] > 1) {
+    const int ng = cl.nc[0] * cl.nc[1];
+    c->pair_grp = ng;
+    std::vector<int> n2(cl.n_cells, 0), lo2(rlo.size(), 0), hi2(rhi.size(), 0);
+    for (int c0 = 0; c0 < cl.n_cells; c0 += ng) {
+      int k = 0;
+      const size_t base = (size_t)c0 * STENCIL_MAX;
+      for (int g = 0; g < gn[c0]; ++g)
+        for (int e = glo[base + g]; e < ghi[base + g]; ++e) {
+          const int lo = ecs[e], hi = ecs[e + 1];
+          bool any = false;
+          for (int u = 0; u < ng; ++u) any = any || in_reach(c0 + u, e);
+          if (hi <= lo || !any) continue;
+          if (k > 0 && hi2[base + k - 1] == lo) hi2[base + k - 1] = hi;
+          else { lo2[base + k] = lo; hi2[base + k] = hi; ++k; }
+        }
+      n2[c0] = k;
+    }
+    if ((r = upload(c, &c->d_grun_n, n2)) || (r = upload(c, &c->d_grun_lo, lo2)) || (r = upload(c, &c->d_grun_hi, hi2)))
+      return bad(r);
   }
   {
     double *x, *y, *z; int *o, *ce, *cs, *rp, *rl, *rh;

@@ -22,6 +22,7 @@ constexpr size_t LDS_LIMIT = 150 * 1024;
 constexpr int TILE_THREADS = 256;
 constexpr int TILE_CAND = 256;
 constexpr int TILE_TGT = 64;
+constexpr int TILE_TGT_MANY = 85;          // of the many-frame pair tiles (a third of the threads)
 
 // ---------------------------------------------------------------- geometry
 
@@ -321,13 +322,14 @@ struct RealBArgs {
 };
 
 // site-site forces hosted as extra workgroups of another launch: cell tiles
-// (tsplit > 0 workgroups per cell, each a contiguous share of its sites;
+// (tsplit > 0 workgroups per item, each a contiguous share of its sites;
 // for many frames) or one wavefront per site (tsplit == 0; for one frame,
 // where the shorter per-wavefront chains win)
 template <typename T>
 struct PairArgs {
-  int n_blocks;                // workgroups per frame (n_cells * tsplit, or ceil(n_site / 4)), 0: none
+  int n_blocks;                // workgroups per frame (n_cells / grp * tsplit, or ceil(n_site / 4)), 0: none
   int tsplit;
+  int grp;                     // cells per tile item: 1, or all those of a z layer (equal stencils; with fwd_n)
   Cell cell;
   SiteSet<T> st;
   T alpha;

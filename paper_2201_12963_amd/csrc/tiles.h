@@ -20,7 +20,13 @@
 //
 // Without periodic images the site-site pairs take a form of their own
 // (site_pairs_n3_tile below) that evaluates every pair once, and the
-// site-electrode pairs a launch of their own (site_elec_tile).
+// site-electrode pairs a launch of their own (site_elec_tile).  Their items
+// are whole z layers where the layer's cells share a stencil (at most three
+// cells along x and y), cut into even chunks of at most TILE_TGT_MANY: a
+// workgroup's time is mostly the chain before and after its pairs (runs,
+// staging, last partial queue, atomics), so fewer, fuller ones win (2048
+// frames of 1280 sites in 2 x 2 cells a layer: site pairs 2.32 -> 1.43 ms,
+// site-electrode 1.35 -> 0.62).
 #pragma once
 #include "pairs.h"
 
@@ -404,14 +410,14 @@ struct PairN3Lds {
   static constexpr size_t cq = rec + (size_t)TILE_CAND * 32;
   static constexpr size_t cacc = cq + ((size_t)TILE_CAND * sizeof(T) + 15) / 16 * 16;
   static constexpr size_t tacc = cacc + 4 * (size_t)TILE_CAND * sizeof(double);
-  static constexpr size_t tpos = tacc + 4 * (size_t)TILE_TGT * sizeof(double);     // x, y, z [TILE_TGT]
-  static constexpr size_t tq = tpos + 3 * (size_t)TILE_TGT * sizeof(double);
-  static constexpr size_t queue = tq + ((size_t)TILE_TGT * sizeof(T) + 15) / 16 * 16;
+  static constexpr size_t tpos = tacc + 4 * (size_t)TILE_TGT_MANY * sizeof(double);     // x, y, z [TILE_TGT_MANY]
+  static constexpr size_t tq = tpos + 3 * (size_t)TILE_TGT_MANY * sizeof(double);
+  static constexpr size_t queue = tq + ((size_t)TILE_TGT_MANY * sizeof(T) + 15) / 16 * 16;
   static constexpr size_t queue_bytes = (TileQI::bytes() + 15) / 16 * 16;
   static constexpr size_t total = queue + (TILE_THREADS / WAVE) * queue_bytes;
 };
 
-// Site-site sums of the targets [t_lo, t_hi) of cell c with every pair once
+// Site-site sums of the targets [t_lo, t_hi) of the item of cell c with every pair once
 // (no periodic images): the candidates are the sites of the forward half of
 // the stencil (pa.fwd_*) of larger sorted index than the target, so each
 // pair inside the cutoff is met by exactly one work item, which adds
@@ -432,9 +438,9 @@ __device__ __forceinline__ void site_pairs_n3_tile(const PairArgs<T>& pa, int c,
   double2* rzs = rxy + TILE_CAND;                                 // [TILE_CAND] z, sorted index
   T* cq = reinterpret_cast<T*>(lds + L::cq);                      // [TILE_CAND]
   double* cacc = reinterpret_cast<double*>(lds + L::cacc);       // [4][TILE_CAND]
-  double* tacc = reinterpret_cast<double*>(lds + L::tacc);       // [4][TILE_TGT]
-  double* tpx = reinterpret_cast<double*>(lds + L::tpos);        // [3][TILE_TGT]
-  T* tq = reinterpret_cast<T*>(lds + L::tq);                      // [TILE_TGT]
+  double* tacc = reinterpret_cast<double*>(lds + L::tacc);       // [4][TILE_TGT_MANY]
+  double* tpx = reinterpret_cast<double*>(lds + L::tpos);        // [3][TILE_TGT_MANY]
+  T* tq = reinterpret_cast<T*>(lds + L::tq);                      // [TILE_TGT_MANY]
   TileQI Q;
   Q.bind(lds + L::queue + (threadIdx.x >> 6) * L::queue_bytes);
   const int lane = threadIdx.x & (WAVE - 1);
@@ -461,7 +467,7 @@ __device__ __forceinline__ void site_pairs_n3_tile(const PairArgs<T>& pa, int c,
     const int tt = e & 255, kc = e >> 8;
     const double2 cxy = rxy[kc];
     const double cz = rzs[kc].x;
-    double ex = tpx[tt] - cxy.x, ey = tpx[TILE_TGT + tt] - cxy.y, ez = tpx[2 * TILE_TGT + tt] - cz;
+    double ex = tpx[tt] - cxy.x, ey = tpx[TILE_TGT_MANY + tt] - cxy.y, ez = tpx[2 * TILE_TGT_MANY + tt] - cz;
     ex = fma(-L0, rint(ex * iL0), ex);
     ey = fma(-L1, rint(ey * iL1), ey);
     if (!ZS) ez = fma(-L2, rint(ez * iL2), ez);
@@ -471,23 +477,25 @@ __device__ __forceinline__ void site_pairs_n3_tile(const PairArgs<T>& pa, int c,
     g0_terms(qx * qx + qy * qy + qz * qz, alpha, g, pot);
     const T wc = qc * g, wt = qt * g;
     atomicAdd(tacc + tt, (double)(wc * qx));
-    atomicAdd(tacc + TILE_TGT + tt, (double)(wc * qy));
-    atomicAdd(tacc + 2 * TILE_TGT + tt, (double)(wc * qz));
-    atomicAdd(tacc + 3 * TILE_TGT + tt, (double)(qc * pot));
+    atomicAdd(tacc + TILE_TGT_MANY + tt, (double)(wc * qy));
+    atomicAdd(tacc + 2 * TILE_TGT_MANY + tt, (double)(wc * qz));
+    atomicAdd(tacc + 3 * TILE_TGT_MANY + tt, (double)(qc * pot));
     atomicAdd(cacc + kc, (double)(-wt * qx));
     atomicAdd(cacc + TILE_CAND + kc, (double)(-wt * qy));
     atomicAdd(cacc + 2 * TILE_CAND + kc, (double)(-wt * qz));
     atomicAdd(cacc + 3 * TILE_CAND + kc, (double)(qt * pot));
   };
 
-  for (int t0 = t_lo; t0 < t_hi; t0 += TILE_TGT) {
-    const TileMap m(min(TILE_TGT, t_hi - t0));
+  const int nch = (t_hi - t_lo + TILE_TGT_MANY - 1) / TILE_TGT_MANY;
+  for (int ch = 0; ch < nch; ++ch) {
+    const int t0 = t_lo + (t_hi - t_lo) * ch / nch;
+    const TileMap m(t_lo + (t_hi - t_lo) * (ch + 1) / nch - t0);
     const int j = t0 + m.ti;
     const double xt = sx[j], yt = sy[j], zt = sz[j];
-    for (int i = threadIdx.x; i < 4 * TILE_TGT; i += TILE_THREADS) tacc[i] = 0.0;
+    for (int i = threadIdx.x; i < 4 * TILE_TGT_MANY; i += TILE_THREADS) tacc[i] = 0.0;
     if ((int)threadIdx.x < m.ntc) {
       tq[threadIdx.x] = (T)sq[t0 + threadIdx.x];
-      tpx[threadIdx.x] = xt; tpx[TILE_TGT + threadIdx.x] = yt; tpx[2 * TILE_TGT + threadIdx.x] = zt;
+      tpx[threadIdx.x] = xt; tpx[TILE_TGT_MANY + threadIdx.x] = yt; tpx[2 * TILE_TGT_MANY + threadIdx.x] = zt;
     }
     for (int c0 = 0;; c0 += TILE_CAND) {
       __syncthreads();
@@ -561,9 +569,9 @@ __device__ __forceinline__ void site_pairs_n3_tile(const PairArgs<T>& pa, int c,
     if ((int)threadIdx.x < m.ntc) {
       const int jj = t0 + threadIdx.x;
       atomicAdd(fp + jj, tacc[threadIdx.x]);
-      atomicAdd(fp + n + jj, tacc[TILE_TGT + threadIdx.x]);
-      atomicAdd(fp + 2 * (size_t)n + jj, tacc[2 * TILE_TGT + threadIdx.x]);
-      if (us) atomicAdd(us + jj, 0.5 * KE * sq[jj] * tacc[3 * TILE_TGT + threadIdx.x]);
+      atomicAdd(fp + n + jj, tacc[TILE_TGT_MANY + threadIdx.x]);
+      atomicAdd(fp + 2 * (size_t)n + jj, tacc[2 * TILE_TGT_MANY + threadIdx.x]);
+      if (us) atomicAdd(us + jj, 0.5 * KE * sq[jj] * tacc[3 * TILE_TGT_MANY + threadIdx.x]);
     }
     __syncthreads();
   }
@@ -580,8 +588,8 @@ struct ElecTileLds {
   static constexpr size_t pos = (sizeof(TileRuns) + 15) / 16 * 16;                  // x, y, z [TILE_CAND]
   static constexpr size_t qab = pos + 3 * (size_t)TILE_CAND * sizeof(double);       // qa, qb [TILE_CAND]
   static constexpr size_t tacc = qab + (2 * (size_t)TILE_CAND * sizeof(T) + 15) / 16 * 16;
-  static constexpr size_t tpos = tacc + 6 * (size_t)TILE_TGT * sizeof(double);      // x, y, z [TILE_TGT]
-  static constexpr size_t queue = tpos + 3 * (size_t)TILE_TGT * sizeof(double);
+  static constexpr size_t tpos = tacc + 6 * (size_t)TILE_TGT_MANY * sizeof(double);      // x, y, z [TILE_TGT_MANY]
+  static constexpr size_t queue = tpos + 3 * (size_t)TILE_TGT_MANY * sizeof(double);
   static constexpr size_t queue_bytes = (TileQI::bytes() + 15) / 16 * 16;
   static constexpr size_t total = queue + (TILE_THREADS / WAVE) * queue_bytes;
 };
@@ -611,8 +619,8 @@ __device__ __forceinline__ void site_elec_tile(const PairArgs<T>& pa, int c, int
   double* pz = py + TILE_CAND;
   T* qa = reinterpret_cast<T*>(lds + L::qab);
   T* qb = qa + TILE_CAND;
-  double* tacc = reinterpret_cast<double*>(lds + L::tacc);       // [6][TILE_TGT]
-  double* tpx = reinterpret_cast<double*>(lds + L::tpos);        // [3][TILE_TGT]
+  double* tacc = reinterpret_cast<double*>(lds + L::tacc);       // [6][TILE_TGT_MANY]
+  double* tpx = reinterpret_cast<double*>(lds + L::tpos);        // [3][TILE_TGT_MANY]
   TileQI Q;
   Q.bind(lds + L::queue + (threadIdx.x >> 6) * L::queue_bytes);
   const int lane = threadIdx.x & (WAVE - 1);
@@ -634,7 +642,7 @@ __device__ __forceinline__ void site_elec_tile(const PairArgs<T>& pa, int c, int
   auto eval = [&](int l) {
     const int e = Q.t[l];
     const int tt = e & 255, kc = e >> 8;
-    double ex = tpx[tt] - px[kc], ey = tpx[TILE_TGT + tt] - py[kc], ez = tpx[2 * TILE_TGT + tt] - pz[kc];
+    double ex = tpx[tt] - px[kc], ey = tpx[TILE_TGT_MANY + tt] - py[kc], ez = tpx[2 * TILE_TGT_MANY + tt] - pz[kc];
     ex = fma(-L0, rint(ex * iL0), ex);
     ey = fma(-L1, rint(ey * iL1), ey);
     if (!ZS) ez = fma(-L2, rint(ez * iL2), ez);
@@ -642,19 +650,21 @@ __device__ __forceinline__ void site_elec_tile(const PairArgs<T>& pa, int c, int
     const T g = g1_force(qx * qx + qy * qy + qz * qz, alpha, eta);
     const T wa = qa[kc] * g, wb = qb[kc] * g;
     atomicAdd(tacc + tt, (double)(wa * qx));
-    atomicAdd(tacc + TILE_TGT + tt, (double)(wa * qy));
-    atomicAdd(tacc + 2 * TILE_TGT + tt, (double)(wa * qz));
-    atomicAdd(tacc + 3 * TILE_TGT + tt, (double)(wb * qx));
-    atomicAdd(tacc + 4 * TILE_TGT + tt, (double)(wb * qy));
-    atomicAdd(tacc + 5 * TILE_TGT + tt, (double)(wb * qz));
+    atomicAdd(tacc + TILE_TGT_MANY + tt, (double)(wa * qy));
+    atomicAdd(tacc + 2 * TILE_TGT_MANY + tt, (double)(wa * qz));
+    atomicAdd(tacc + 3 * TILE_TGT_MANY + tt, (double)(wb * qx));
+    atomicAdd(tacc + 4 * TILE_TGT_MANY + tt, (double)(wb * qy));
+    atomicAdd(tacc + 5 * TILE_TGT_MANY + tt, (double)(wb * qz));
   };
 
-  for (int t0 = t_lo; t0 < t_hi; t0 += TILE_TGT) {
-    const TileMap m(min(TILE_TGT, t_hi - t0));
+  const int nch = (t_hi - t_lo + TILE_TGT_MANY - 1) / TILE_TGT_MANY;
+  for (int ch = 0; ch < nch; ++ch) {
+    const int t0 = t_lo + (t_hi - t_lo) * ch / nch;
+    const TileMap m(t_lo + (t_hi - t_lo) * (ch + 1) / nch - t0);
     const double xt = sx[t0 + m.ti], yt = sy[t0 + m.ti], zt = sz[t0 + m.ti];
-    for (int i = threadIdx.x; i < 6 * TILE_TGT; i += TILE_THREADS) tacc[i] = 0.0;
+    for (int i = threadIdx.x; i < 6 * TILE_TGT_MANY; i += TILE_THREADS) tacc[i] = 0.0;
     if ((int)threadIdx.x < m.ntc) {
-      tpx[threadIdx.x] = xt; tpx[TILE_TGT + threadIdx.x] = yt; tpx[2 * TILE_TGT + threadIdx.x] = zt;
+      tpx[threadIdx.x] = xt; tpx[TILE_TGT_MANY + threadIdx.x] = yt; tpx[2 * TILE_TGT_MANY + threadIdx.x] = zt;
     }
     for (int c0 = 0;; c0 += TILE_CAND) {
       __syncthreads();
@@ -706,7 +716,7 @@ __device__ __forceinline__ void site_elec_tile(const PairArgs<T>& pa, int c, int
     if ((int)threadIdx.x < m.ntc) {
       const int jj = t0 + threadIdx.x;
 #pragma unroll
-      for (int u = 0; u < 6; ++u) fe[(size_t)u * n + jj] = tacc[u * TILE_TGT + threadIdx.x];
+      for (int u = 0; u < 6; ++u) fe[(size_t)u * n + jj] = tacc[u * TILE_TGT_MANY + threadIdx.x];
     }
     __syncthreads();
   }
@@ -767,17 +777,17 @@ __device__ __forceinline__ void real_b_block(const RealBArgs<T>& rb, int b, int 
 }
 
 // work item b of a frame's tiles (tsplit > 0): share b mod tsplit of the
-// sorted sites [t_lo, t_hi) of cell b / tsplit
-__device__ __forceinline__ void tile_item(int b, int tsplit, const int* cs, int& c, int& t_lo, int& t_hi) {
-  c = b / tsplit;
-  const int s = b - c * tsplit;
-  const int lo = cs[c], n = cs[c + 1] - lo;
+// sorted sites [t_lo, t_hi) of the grp cells from c = grp (b / tsplit) on
+__device__ __forceinline__ void tile_item(int b, int tsplit, int grp, const int* cs, int& c, int& t_lo, int& t_hi) {
+  const int i = b / tsplit, s = b - i * tsplit;
+  c = i * grp;
+  const int lo = cs[c], n = cs[c + grp] - lo;
   t_lo = lo + (int)(((long long)n * s) / tsplit);
   t_hi = lo + (int)(((long long)n * (s + 1)) / tsplit);
 }
 
 // workgroup b of a frame's site-pair work: with tsplit > 0, share b mod
-// tsplit of the sites of cell b / tsplit (tiles; MODE 1: the site-electrode
+// tsplit of the sites of item b / tsplit (tiles; MODE 1: the site-electrode
 // sums alone, MODE 2: the site-site sums with every pair once; ZS: z images
 // fixed at staging, PairArgs::zshift); with tsplit == 0, sites 4b .. 4b+3
 // (one wavefront each)
@@ -792,7 +802,7 @@ __device__ __forceinline__ void site_pairs_block(const PairArgs<T>& pa, int b, i
     return;
   }
   int c, t_lo, t_hi;
-  tile_item(b, pa.tsplit, pa.st.cell_start + (size_t)frame * (pa.cell.n_cells + 1), c, t_lo, t_hi);
+  tile_item(b, pa.tsplit, pa.grp, pa.st.cell_start + (size_t)frame * (pa.cell.n_cells + 1), c, t_lo, t_hi);
   if (MODE == 2) site_pairs_n3_tile<T, ZS>(pa, c, t_lo, t_hi, frame, lds);
   else if (MODE == 1) site_elec_tile<T, ZS>(pa, c, t_lo, t_hi, frame, lds);
   else site_pairs_tile(pa, c, t_lo, t_hi, frame, lds);

@@ -302,3 +302,37 @@ def test_batch_launch_shapes(torch_dev, tiles_per_cell, xy_planes):
             assert rel_rms(Fb[fi, vi], f) < 1e-10
             assert np.abs(Eb[fi, vi] - e).max() < 1e-9 * np.abs(e).max()
     ctx.close()
+
+
+@pytest.mark.parametrize("rcut,frames", [(1.2, 2), (1.2, 17), (1.2, 65), (1.0, 3), (1.0, 33), (0.8, 16), (1.69, 5)])
+def test_batch_items_and_frame_counts(torch_dev, rcut, frames):
+    """Pair-tile items of a whole z layer (2 x 2 and 3 x 3 cells in x-y; 4 x 4
+    keeps one cell each; 1.69: two cells nearly half the box wide) and
+    batches whose launches are shaped by the frame count, against the
+    single-frame path with the tolerances of the launch-shape test."""
+    torch = torch_dev
+    from paper_2201_12963_amd import Context
+    from workloads import perturbed_frames
+    _say(f"[gpu] batch items: rcut {rcut}, {frames} frames")
+    w = dataclasses.replace(built("paper", "ff")[0], rcut=rcut)
+    X = perturbed_frames(w, frames, sigma=0.05, seed=23)
+    dvs = np.array([0.5, 3.0])
+    stream = torch.cuda.Stream()
+    ctx = Context.from_workload(w, stream=stream)
+    ctx.build_elastance()
+    with torch.cuda.stream(stream):
+        out = ctx.solve_batch(torch.tensor(X, dtype=torch.float64, device="cuda"), dvs)
+    stream.synchronize()
+    assert ctx.sync_status() == 0
+    Qb, Fb, Eb = (t.cpu().numpy() for t in out)
+    for fi in sorted({0, frames // 2, frames - 1}):
+        x = torch.tensor(X[fi], dtype=torch.float64, device="cuda")
+        for vi, dv in enumerate(dvs):
+            with torch.cuda.stream(stream):
+                one = ctx.solve(x, float(dv))
+            stream.synchronize()
+            q, f, e = (t.cpu().numpy() for t in one)
+            assert np.abs(Qb[fi, vi] - q).max() < 1e-11
+            assert rel_rms(Fb[fi, vi], f) < 1e-10
+            assert np.abs(Eb[fi, vi] - e).max() < 1e-9 * np.abs(e).max()
+    ctx.close()
