@@ -1151,6 +1151,8 @@ size_t fft_xy_lds_bytes(int Kx, int Ky, int elt_bytes, int planes) {
   return (2 * (size_t)planes * Kx * Ky + Kx + Ky) * (size_t)elt_bytes;
 }
 
+constexpr size_t XY_FILL = 512;
+
 // many-frame x-y launch with pl planes per workgroup; grid.y = ny (frames,
 // or frames x 2 parts for the split field transform)
 template <typename T, typename T2>
@@ -1162,6 +1164,9 @@ void launch_xy_many(hipStream_t s, const FFTPlan1D& px, const FFTPlan1D& py, int
   if (px.planes > 0 && px.planes < pl) pl = 1;          // the tuner's choice (one plane, or as many as fit)
   const int nz = zl ? n_zl : Kz;
   if (nz == 0) return;
+  // too few workgroups for two per CU: a plane each (8 frames of 36 x 36 x 135:
+  // 177 -> 163 us a batch; 37 frames equal, 120 frames 6% slower so)
+  if ((size_t)((nz + pl - 1) / pl) * ny < XY_FILL) pl = 1;
   const dim3 grid((nz + pl - 1) / pl, ny);
   const size_t lds = fft_xy_lds<T2>(px, py, pl);
   if (ia || zl) {
