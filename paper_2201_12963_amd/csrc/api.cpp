@@ -514,6 +514,22 @@ template <> struct Bufs<float> {
   static const float* val(cpm_ctx* c) { return c->d_valf; }
 };
 
+bool no_images(const Cell& cl) { return (cl.img[0] | cl.img[1] | cl.img[2]) == 0; }
+
+// cells per item of the batched tiles: a whole z layer where its cells share
+// one stencil, else one
+int layer_cells(const Cell& cl) {
+  return no_images(cl) && cl.nc[0] <= 3 && cl.nc[1] <= 3 ? cl.nc[0] * cl.nc[1] : 1;
+}
+
+// tiles may fix the z images at staging: |z_target - z_centre| <= w/2, so a
+// pair within rcut has the staged image's |dz| < rcut + w/2 < Lz/2 when
+// Lz > 2 rcut + w: the same image as the minimum image of the pair
+bool zshift_ok(const cpm_ctx* c) {
+  const Cell& cl = c->cell;
+  return no_images(cl) && cl.nc[2] >= 5 && cl.L[2] > 2.0 * c->rcut + cl.L[2] / cl.nc[2];
+}
+
 constexpr int PAIR_FILL = 1600;   // workgroups of a many-frame pair launch (about six per CU)
 
 // the site-site sums of nf frames: one frame, a wavefront per site (short
@@ -569,7 +585,7 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
   // real-space b: one frame, a wavefront per electrode atom (hosted in the
   // potential's z pass); many frames, cell tiles in a launch of their own
   RealBArgs<T> rb{};
-  rb.tiles = nf > 1;
+  rb.tiles = nf == 1 ? 0 : !no_images(c->cell) ? 1 : !mixed && zshift_ok(c) ? 3 : 2;
   rb.n_blocks = rb.tiles ? c->n_items : (c->n_elec + 3) / 4;
   rb.cell = c->cell;
   rb.st = st;
@@ -691,12 +707,7 @@ int enqueue_forces(cpm_ctx* c, int nf, const double* qa, size_t qa_stride, const
     pa.f_elec = c->d_felec;
     fa.f_elec = c->d_felec;
     pa.fwd_n = c->d_fwd_n; pa.fwd_lo = c->d_fwd_lo; pa.fwd_hi = c->d_fwd_hi;
-    // |z_target - z_centre| <= w/2, so a pair within rcut has the staged
-    // image's |dz| < rcut + w/2 < Lz/2 when Lz > 2 rcut + w: the same image
-    // as the minimum image of the pair
-    const Cell& cl = c->cell;
-    pa.zshift = (cl.img[0] | cl.img[1] | cl.img[2]) == 0 && cl.nc[2] >= 5 &&
-                cl.L[2] > 2.0 * c->rcut + cl.L[2] / cl.nc[2];
+    pa.zshift = zshift_ok(c);
   }
   const T* epart = nullptr;   // the interpolation's per-plane shares (many frames, order 5)
   if (c->kspace == CPM_KSPACE_PPPM) {
@@ -1361,11 +1372,13 @@ int cpm_create(const cpm_desc* d, void* hip_stream, cpm_ctx** out) {
   for (int k = 0; k < ne; ++k) epos[eorder[k]] = k;
   if ((r = upload(c, &c->d_epos, epos))) return bad(r);
   {
-    // each cell's atoms in equal chunks of at most TILE_TGT
+    // each cell's atoms in equal chunks of at most TILE_TGT, or a layer's
+    // where its cells share a stencil (below)
+    const int ng = layer_cells(cl), most = ng > 1 ? TILE_TGT_MANY : TILE_TGT;
     std::vector<int> ic, il, ih;
-    for (int cc2 = 0; cc2 < cl.n_cells; ++cc2) {
-      const int lo = ecs[cc2], n = ecs[cc2 + 1] - lo;
-      const int nch = (n + TILE_TGT - 1) / TILE_TGT;
+    for (int cc2 = 0; cc2 < cl.n_cells; cc2 += ng) {
+      const int lo = ecs[cc2], n = ecs[cc2 + ng] - lo;
+      const int nch = (n + most - 1) / most;
       for (int k = 0; k < nch; ++k) {
         ic.push_back(cc2);
         il.push_back(lo + (int)((long long)n * k / nch));
@@ -1444,9 +1457,9 @@ int cpm_create(const cpm_desc* d, void* hip_stream, cpm_ctx** out) {
   // stencil cells of no smaller index), and its electrode runs are the union
   // of theirs.  A quarter of the workgroups (2 x 2 cells) stage a quarter of
   // the candidates.
-  if (no_img && cl.nc[0] <= 3 && cl.nc[1] <= 3 && cl.nc[0] * cl.nc[1] > 1) {
-    const int ng = cl.nc[0] * cl.nc[1];
-    c->pair_grp = ng;
+  const int ng = layer_cells(cl);
+  c->pair_grp = ng;
+  if (ng > 1) {
     std::vector<int> n2(cl.n_cells, 0), lo2(rlo.size(), 0), hi2(rhi.size(), 0);
     for (int c0 = 0; c0 < cl.n_cells; c0 += ng) {
       int k = 0;

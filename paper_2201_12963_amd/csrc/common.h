@@ -299,8 +299,9 @@ __device__ __forceinline__ double slab_b_term(const SlabTerms& sl, int i, int fr
 
 // real-space part of b: one wavefront per electrode atom, four per
 // workgroup (tiles == 0; hosted as extra workgroups of another launch for
-// one frame), or cell tiles over fixed work items of at most TILE_TGT atoms
-// of one cell (tiles != 0; many frames)
+// one frame), or cell tiles over fixed work items of atoms of one cell (at
+// most TILE_TGT) or of a layer's (PairArgs::grp > 1; at most TILE_TGT_MANY)
+// (tiles != 0; many frames)
 template <typename T>
 struct RealBArgs {
   int n_blocks;                // workgroups per frame (ceil(n_elec / 4), or the item count), 0: none
@@ -315,7 +316,8 @@ struct RealBArgs {
   // plane; nullptr: not
   double* b_out;
   SlabTerms sl;
-  int tiles;
+  int tiles;                   // 0: wavefronts; tiles: 1 with periodic images, 2 without, 3 without and with the
+                               // z images fixed at staging (PairArgs::zshift)
   const int* item_c;           // cell of item b
   const int* item_lo;          // its atoms [item_lo, item_hi) of the sorted electrode arrays
   const int* item_hi;

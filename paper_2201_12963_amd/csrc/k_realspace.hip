@@ -14,9 +14,25 @@ __global__ __launch_bounds__(TILE_THREADS) void k_real_b(RealBArgs<T> rb) {
   real_b_block(rb, xcd_block(blockIdx.x, gridDim.x), blockIdx.y, lds);
 }
 
+template <typename T, bool ZS>
+__global__ __launch_bounds__(TILE_THREADS, sizeof(T) == 8 ? 5 : 8) void k_real_b_near(RealBArgs<T> rb) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  real_b_near_tile<T, ZS>(rb, rb.item_c[b], rb.item_lo[b], rb.item_hi[b], blockIdx.y, lds);
+}
+
 template <typename T>
 void launch_real_b_t(hipStream_t s, int n_frames, const RealBArgs<T>& rb) {
   if (rb.n_blocks == 0 || n_frames == 0) return;
+  if (rb.tiles > 1) {
+    // (FP32 takes each pair's own minimum image, so that the displacement it
+    // rounds has the same bits as one frame's)
+    auto* k = k_real_b_near<T, false>;
+    if constexpr (sizeof(T) == 8)
+      if (rb.tiles == 3) k = k_real_b_near<T, true>;
+    hipLaunchKernelGGL(k, dim3(rb.n_blocks, n_frames), dim3(TILE_THREADS), RealBLds<T>::total, s, rb);
+    return;
+  }
   const size_t lds = rb.tiles ? PairLds<T>::total : 4 * wave_scratch_bytes<T>();
   hipLaunchKernelGGL(k_real_b<T>, dim3(rb.n_blocks, n_frames), dim3(TILE_THREADS), lds, s, rb);
 }
