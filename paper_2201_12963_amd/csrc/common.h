@@ -46,7 +46,7 @@ struct Cell {          // periodic orthorhombic cell and its cell-list grid
 struct FFTPlan1D {     // mixed-radix Stockham plan for one axis
   int n;               // at most 8191 points
   int nfac;
-  // per stage: radix R (bits 0-2), butterflies n/R (bits 3-15) and twiddle
+  // per stage: radix R (bits 0-2; 2 to 6), butterflies n/R (bits 3-15) and twiddle
   // step n/(Ns R), Ns the product of the radices before it (from bit 16); the
   // integer divisions that gave these on the device were half of a stage's
   // latency

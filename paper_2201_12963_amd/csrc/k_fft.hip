@@ -41,7 +41,7 @@ template <typename T2> __device__ __forceinline__ T2 cmul_si(T2 a, int sigma) {
   return sigma > 0 ? T2{-a.y, a.x} : T2{a.y, -a.x};
 }
 
-// X[m] = sum_r v[r] exp(sigma 2 pi i r m / R), R in {2,3,4,5}; R is a
+// X[m] = sum_r v[r] exp(sigma 2 pi i r m / R), R in {2,3,4,5,6}; R is a
 // compile-time constant so v stays in registers
 template <int R, typename T2>
 __device__ __forceinline__ void small_dft(T2* v, int sigma) {
@@ -62,6 +62,15 @@ __device__ __forceinline__ void small_dft(T2* v, int sigma) {
     v[0] = cadd(v[0], s);
     v[1] = cadd(m, d);
     v[2] = csub(m, d);
+  } else if constexpr (R == 6) {
+    // by the prime factors 2 x 3: r = 3 r1 + 2 r2 and m = 3 m1 + 4 m2 (mod 6)
+    // need no twiddles between them
+    T2 a[3] = {v[0], v[2], v[4]}, b[3] = {v[3], v[5], v[1]};
+    small_dft<3>(a, sigma);
+    small_dft<3>(b, sigma);
+    v[0] = cadd(a[0], b[0]); v[3] = csub(a[0], b[0]);
+    v[4] = cadd(a[1], b[1]); v[1] = csub(a[1], b[1]);
+    v[2] = cadd(a[2], b[2]); v[5] = csub(a[2], b[2]);
   } else {  // R == 5
     const Rl c1 = (Rl)0.30901699437494742, c2 = (Rl)-0.80901699437494742;
     const Rl s1 = (Rl)0.95105651629515357, s2 = (Rl)0.58778525229247313;
@@ -152,6 +161,7 @@ __device__ T2* fft_lines(T2* a, T2* b, const FFTPlan1D& p, const T2* tw, int nli
       case 2: fft_stage<2>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
       case 3: fft_stage<3>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
       case 4: fft_stage<4>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
+      case 6: if constexpr (sizeof(T2) == 16) fft_stage<6>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
       default: fft_stage<5>(src, dst, nb, ts, Ns, nlines, es, ls, tw, sigma, nplanes, pstride); break;
     }
     __syncthreads();
@@ -293,6 +303,7 @@ __device__ T2* fft_line_w(T2* a, T2* b, const FFTPlan1D& p, const T2* tw, int si
       case 2: fft_stage_w<2>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
       case 3: fft_stage_w<3>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
       case 4: fft_stage_w<4>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
+      case 6: if constexpr (sizeof(T2) == 16) fft_stage_w<6>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
       default: fft_stage_w<5>(src, dst, nb, ts, Ns, tw, sigma, nl, lstride); break;
     }
     __builtin_amdgcn_wave_barrier();

@@ -167,6 +167,32 @@ def test_step_parity_plane_shapes(torch_dev, kx, ky):
     check_step(torch_dev, w, A, S)
 
 
+@pytest.mark.parametrize("mesh", [(36, 54, 64), (48, 30, 96), (36, 40, 90), (24, 36, 144)])
+def test_step_parity_radix_six(torch_dev, mesh):
+    """Meshes whose plans hold stages of radix 6, first and later, beside
+    radices 2 to 5, in planes and columns: one frame against the oracle, and
+    a batch against one frame."""
+    import dataclasses
+    torch = torch_dev
+    from paper_2201_12963_amd import Context
+    from workloads import perturbed_frames
+    _say(f"[gpu] step tiny ff with PPPM, mesh {mesh}")
+    w0, A, S = built("tiny", "ff")
+    w = dataclasses.replace(w0, kspace="pppm", mesh=mesh)
+    check_step(torch_dev, w, A, S)
+    stream = torch.cuda.Stream()
+    ctx = Context.from_workload(w, stream=stream)
+    ctx.build_elastance()
+    X = torch.tensor(perturbed_frames(w, 3, sigma=0.02, seed=4), dtype=torch.float64, device="cuda")
+    with torch.cuda.stream(stream):
+        q, f, _ = ctx.solve_batch(X, np.array([1.5]))
+        q1, f1, _ = ctx.solve(X[2].contiguous(), 1.5)
+    stream.synchronize()
+    assert (q[2, 0] - q1).abs().max().item() < 1e-11
+    assert (f[2, 0] - f1).pow(2).mean().sqrt().item() < 1e-10 * f1.pow(2).mean().sqrt().item()
+    ctx.close()
+
+
 @pytest.mark.parametrize("order", [3, 4, 6, 7])
 def test_step_parity_spline_orders(torch_dev, order):
     """B-spline orders other than 5: the kernels evaluate the weights by the
