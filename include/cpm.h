@@ -143,7 +143,8 @@ int cpm_solve(cpm_ctx* ctx, const double* site_xyz, double dv,
  * rank-one update.  Frames go through in launches of up to 4096: the first
  * call with at least 128 frames times launches of 64, 128, ... frames on its
  * own first frames and keeps the fastest size for the context, then at that
- * size times the site-pair tiles with 1, 2 and 4 workgroups per cell and the
+ * size (at most 512 frames) times the site-pair tiles with 1, 2 and 4
+ * workgroups per item (a cell, or a z layer whose cells share a stencil) and the
  * x-y passes with one plane or as many as fit per workgroup, and keeps the
  * fastest of each (it synchronises the stream; setting CPM_BATCH_CHUNK in the
  * environment fixes the size and skips all of it).  CPM_ENOMEM if the
@@ -154,7 +155,8 @@ int cpm_solve_batch(cpm_ctx* ctx, int n_frames, const double* site_xyz,
 
 /* Fix the batch launch shapes instead of tuning them (for callers that tune
  * themselves, and for tests): frames per launch (1..4096), site-pair tile
- * workgroups per cell (1..64) and x-y planes per many-frame workgroup (0: as
+ * workgroups per item (1..64; a cell, or a z layer whose cells share a stencil,
+ * which few frames split further) and x-y planes per many-frame workgroup (0: as
  * many as fit in LDS, 1: one).  CPM_EINVAL outside those ranges. */
 int cpm_set_batch_shape(cpm_ctx* ctx, int frames_per_launch, int tiles_per_cell, int xy_planes);
 

@@ -992,6 +992,7 @@ int enqueue_batch(cpm_ctx* c, int nf, const double* xyz, int n_dv, double* q_out
 // overwrites.
 constexpr int BATCH_CHUNK_MAX = 4096;
 constexpr int BATCH_TUNE_MIN = 64;
+constexpr int BATCH_TUNE_SHAPE = 512;
 
 template <typename Run>
 int tune_batch_chunk(cpm_ctx* c, int n_frames, Run run) {
@@ -1026,9 +1027,12 @@ int tune_batch_chunk(cpm_ctx* c, int n_frames, Run run) {
     const float per_frame = ms / (float)k;
     if (k == cand.front() || per_frame < best_t) { best_t = per_frame; best = k; }
   }
-  // then the launch shapes at that size: site-pair tiles per cell and x-y
-  // planes per workgroup, each the fastest of its candidates with the other
-  // at its current setting
+  // then the launch shapes at that size, or at BATCH_TUNE_SHAPE frames if it
+  // is larger (the chip is full there, and ten runs of 4096 frames were most of
+  // a new context's first batch): site-pair tiles per item and x-y planes per
+  // workgroup, each the fastest of its candidates with the other at its
+  // current setting
+  const int shape_frames = std::min(best, BATCH_TUNE_SHAPE);
   auto time_run = [&](int k, float& ms) -> int {
     ms = 0.0f;
     for (int rep = 0; rep < 2; ++rep) {
@@ -1047,7 +1051,7 @@ int tune_batch_chunk(cpm_ctx* c, int n_frames, Run run) {
     for (int ts : {1, 2, 4}) {
       c->pair_tsplit = ts;
       float ms;
-      if ((rc = time_run(best, ms))) break;
+      if ((rc = time_run(shape_frames, ms))) break;
       if (ts == 1 || ms < t_best) { t_best = ms; ts_best = ts; }
     }
     c->pair_tsplit = ts_best;
@@ -1058,7 +1062,7 @@ int tune_batch_chunk(cpm_ctx* c, int n_frames, Run run) {
     for (int pl : {0, 1}) {
       c->px.planes = pl;
       float ms;
-      if ((rc = time_run(best, ms))) break;
+      if ((rc = time_run(shape_frames, ms))) break;
       if (pl == 0 || ms < t_best) { t_best = ms; pl_best = pl; }
     }
     c->px.planes = pl_best;
