@@ -211,6 +211,22 @@ struct TileMap {
   }
 };
 
+// Staged sets filled up to whole steps of two candidates per thread (places
+// 0 .. nsl - 1 of a target), so that the tests need no bounds: the fill never
+// passes one, nor does a thread without a place.
+struct TileFill {
+  int nsl, sl, cap;            // cap: most candidates of a set
+  bool act;
+  __device__ __forceinline__ TileFill(const TileMap& m) {
+    nsl = min(m.nsl, TILE_CAND / 2);
+    act = m.sl < nsl;
+    sl = act ? m.sl : 0;
+    cap = TILE_CAND / (2 * nsl) * (2 * nsl);
+  }
+  // candidates per place for a set of nck <= cap (even; nsl times it <= cap)
+  __device__ __forceinline__ int steps(int nck) const { return 2 * ((nck + 2 * nsl - 1) / (2 * nsl)); }
+};
+
 // ------------------------------------------------------------ site pairs
 
 // queue entries: the displacement (3 values of T) and one int holding the
@@ -497,11 +513,19 @@ __device__ __forceinline__ void site_pairs_n3_tile(const PairArgs<T>& pa, int c,
       tq[threadIdx.x] = (T)sq[t0 + threadIdx.x];
       tpx[threadIdx.x] = xt; tpx[TILE_TGT_MANY + threadIdx.x] = yt; tpx[2 * TILE_TGT_MANY + threadIdx.x] = zt;
     }
-    for (int c0 = 0;; c0 += TILE_CAND) {
+    // (the fill has index -1; a thread without a place has no candidate of
+    // larger index than its own)
+    const TileFill fill(m);
+    const int jt = fill.act ? j : INT_MAX;
+    for (int c0 = 0;; c0 += fill.cap) {
       __syncthreads();
       const int total = R->total;
-      const int nck = min(TILE_CAND, total - c0);
-      for (int k = threadIdx.x; k < nck; k += TILE_THREADS) {
+      const int nck = min(fill.cap, total - c0), bs = fill.steps(nck);     // bs: block length
+      for (int k = threadIdx.x; k < bs * fill.nsl; k += TILE_THREADS) {
+        if (k >= nck) {
+          rzs[k].y = __longlong_as_double(-1ll);
+          continue;
+        }
         const int s = tile_src(R, c0 + k);
         double z = sz[s];
         if (ZS) z -= L2 * rint((z - zc) * iL2);
@@ -512,32 +536,29 @@ __device__ __forceinline__ void site_pairs_n3_tile(const PairArgs<T>& pa, int c,
         for (int u = 0; u < 4; ++u) cacc[u * TILE_CAND + k] = 0.0;
       }
       __syncthreads();
-      const int bs = nck > 0 ? (nck + m.nsl - 1) / m.nsl : 0;     // block length
-      const int b0 = m.sl * bs, bend = b0 + bs;
+      const int b0 = fill.sl * bs, bend = b0 + bs;
       int k = b0 + (bs > 0 ? m.ti % bs : 0);
       int nq = 0;
       // two candidates per step: both records are read before either is
       // tested (independent chains the compiler interleaves)
       for (int it = 0; it < bs; it += 2) {
-        int kk[2], kr[2];
+        int kk[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           kk[h] = k;
-          kr[h] = k < nck ? k : 0;
           if (++k == bend) k = b0;
         }
         double2 pxy[2], pzs[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) { pxy[h] = rxy[kr[h]]; pzs[h] = rzs[kr[h]]; }
+        for (int h = 0; h < 2; ++h) { pxy[h] = rxy[kk[h]]; pzs[h] = rzs[kk[h]]; }
         bool in[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const bool valid = m.act && it + h < bs && kk[h] < nck;
           double ex = xt - pxy[h].x, ey = yt - pxy[h].y, ez = zt - pzs[h].x;
           ex = fma(-L0, rint(ex * iL0), ex);
           ey = fma(-L1, rint(ey * iL1), ey);
           if (!ZS) ez = fma(-L2, rint(ez * iL2), ez);
-          in[h] = valid && (int)__double_as_longlong(pzs[h].y) > j && fma(ez, ez, fma(ey, ey, ex * ex)) < rc2;
+          in[h] = (int)__double_as_longlong(pzs[h].y) > jt && fma(ez, ez, fma(ey, ey, ex * ex)) < rc2;
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -562,7 +583,7 @@ __device__ __forceinline__ void site_pairs_n3_tile(const PairArgs<T>& pa, int c,
           if (us) atomicAdd(us + s, 0.5 * KE * sq[s] * u);
         }
       }
-      if (c0 + TILE_CAND >= total) break;
+      if (c0 + fill.cap >= total) break;
     }
     // the targets' sums (their staged sets are done: the last barrier above
     // follows every evaluation)
@@ -666,11 +687,17 @@ __device__ __forceinline__ void site_elec_tile(const PairArgs<T>& pa, int c, int
     if ((int)threadIdx.x < m.ntc) {
       tpx[threadIdx.x] = xt; tpx[TILE_TGT_MANY + threadIdx.x] = yt; tpx[2 * TILE_TGT_MANY + threadIdx.x] = zt;
     }
-    for (int c0 = 0;; c0 += TILE_CAND) {
+    const TileFill fill(m);
+    const double xa = fill.act ? xt : NAN;
+    for (int c0 = 0;; c0 += fill.cap) {
       __syncthreads();
       const int total = R->total;
-      const int nck = min(TILE_CAND, total - c0);
-      for (int k = threadIdx.x; k < nck; k += TILE_THREADS) {
+      const int nck = min(fill.cap, total - c0), n_iter = fill.steps(nck);
+      for (int k = threadIdx.x; k < n_iter * fill.nsl; k += TILE_THREADS) {
+        if (k >= nck) {
+          px[k] = NAN;
+          continue;
+        }
         const int s = tile_src(R, c0 + k);
         double z = pa.el.z[s];
         if (ZS) z -= L2 * rint((z - zc) * iL2);
@@ -679,26 +706,22 @@ __device__ __forceinline__ void site_elec_tile(const PairArgs<T>& pa, int c, int
         qb[k] = qb_e ? (T)qb_e[s] : (T)0;
       }
       __syncthreads();
-      const int n_iter = nck > 0 ? (nck + m.nsl - 1) / m.nsl : 0;
       int nq = 0;
       for (int it = 0; it < n_iter; it += 2) {
-        int kk[2], kr[2];
+        int kk[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          kk[h] = m.sl + (it + h) * m.nsl;
-          kr[h] = kk[h] < nck ? kk[h] : 0;
-        }
+        for (int h = 0; h < 2; ++h) kk[h] = fill.sl + (it + h) * fill.nsl;
         double ax[2], ay[2], az[2];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) { ax[h] = px[kr[h]]; ay[h] = py[kr[h]]; az[h] = pz[kr[h]]; }
+        for (int h = 0; h < 2; ++h) { ax[h] = px[kk[h]]; ay[h] = py[kk[h]]; az[h] = pz[kk[h]]; }
         bool in[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          double ex = xt - ax[h], ey = yt - ay[h], ez = zt - az[h];
+          double ex = xa - ax[h], ey = yt - ay[h], ez = zt - az[h];
           ex = fma(-L0, rint(ex * iL0), ex);
           ey = fma(-L1, rint(ey * iL1), ey);
           if (!ZS) ez = fma(-L2, rint(ez * iL2), ez);
-          in[h] = m.act && kk[h] < nck && fma(ez, ez, fma(ey, ey, ex * ex)) < rc2;
+          in[h] = fma(ez, ez, fma(ey, ey, ex * ex)) < rc2;
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -710,7 +733,7 @@ __device__ __forceinline__ void site_elec_tile(const PairArgs<T>& pa, int c, int
         }
       }
       if (lane < nq) eval(lane);
-      if (c0 + TILE_CAND >= total) break;
+      if (c0 + fill.cap >= total) break;
     }
     __syncthreads();
     if ((int)threadIdx.x < m.ntc) {
@@ -825,11 +848,17 @@ __device__ __forceinline__ void real_b_near_tile(const RealBArgs<T>& rb, int c, 
     if (!ZS) ez = fma(-L2, rint(ez * iL2), ez);
     atomicAdd(tacc + tt, (double)g1_potential((T)ex, (T)ey, (T)ez, cq[kc], alpha, eta));
   };
-  for (int c0 = 0;; c0 += TILE_CAND) {
+  const TileFill fill(m);
+  const double xa = fill.act ? xt : NAN;
+  for (int c0 = 0;; c0 += fill.cap) {
     __syncthreads();
     const int total = R->total;
-    const int nck = min(TILE_CAND, total - c0);
-    for (int k = threadIdx.x; k < nck; k += TILE_THREADS) {
+    const int nck = min(fill.cap, total - c0), n_iter = fill.steps(nck);
+    for (int k = threadIdx.x; k < n_iter * fill.nsl; k += TILE_THREADS) {
+      if (k >= nck) {
+        px[k] = NAN;
+        continue;
+      }
       const int s = tile_src(R, c0 + k);
       double z = sz[s];
       if (ZS) z -= L2 * rint((z - zc) * iL2);
@@ -837,26 +866,22 @@ __device__ __forceinline__ void real_b_near_tile(const RealBArgs<T>& rb, int c, 
       cq[k] = (T)sq[s];
     }
     __syncthreads();
-    const int n_iter = nck > 0 ? (nck + m.nsl - 1) / m.nsl : 0;
     int nq = 0;
     for (int it = 0; it < n_iter; it += 2) {
-      int kk[2], kr[2];
+      int kk[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        kk[h] = m.sl + (it + h) * m.nsl;
-        kr[h] = kk[h] < nck ? kk[h] : 0;
-      }
+      for (int h = 0; h < 2; ++h) kk[h] = fill.sl + (it + h) * fill.nsl;
       double ax[2], ay[2], az[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) { ax[h] = px[kr[h]]; ay[h] = py[kr[h]]; az[h] = pz[kr[h]]; }
+      for (int h = 0; h < 2; ++h) { ax[h] = px[kk[h]]; ay[h] = py[kk[h]]; az[h] = pz[kk[h]]; }
       bool in[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        double ex = xt - ax[h], ey = yt - ay[h], ez = zt - az[h];
+        double ex = xa - ax[h], ey = yt - ay[h], ez = zt - az[h];
         ex = fma(-L0, rint(ex * iL0), ex);
         ey = fma(-L1, rint(ey * iL1), ey);
         if (!ZS) ez = fma(-L2, rint(ez * iL2), ez);
-        in[h] = m.act && kk[h] < nck && fma(ez, ez, fma(ey, ey, ex * ex)) < rc2;
+        in[h] = fma(ez, ez, fma(ey, ey, ex * ex)) < rc2;
       }
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
@@ -868,7 +893,7 @@ __device__ __forceinline__ void real_b_near_tile(const RealBArgs<T>& rb, int c, 
       }
     }
     if (lane < nq) eval(lane);
-    if (c0 + TILE_CAND >= total) break;
+    if (c0 + fill.cap >= total) break;
   }
   __syncthreads();
   if ((int)threadIdx.x < m.ntc) {
