@@ -40,7 +40,7 @@ void launch_real_b_t(hipStream_t s, int n_frames, const RealBArgs<T>& rb) {
 template <typename T>
 __global__ __launch_bounds__(TILE_THREADS) void k_site_pairs(PairArgs<T> pa) {
   extern __shared__ __align__(16) unsigned char lds[];
-  site_pairs_block(pa, xcd_block(blockIdx.x, gridDim.x), blockIdx.y, lds);
+  site_pairs_block<T, 0>(pa, xcd_block(blockIdx.x, gridDim.x), blockIdx.y, lds);
 }
 
 // The cell-tile form (many frames) as a kernel of its own, held to five
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(TILE_THREADS) void k_site_pairs(PairArgs<T> pa) {
 template <typename T>
 __global__ __launch_bounds__(TILE_THREADS, 5) void k_site_pairs_tiles(PairArgs<T> pa) {
   extern __shared__ __align__(16) unsigned char lds[];
-  site_pairs_block<T, 0>(pa, xcd_block(blockIdx.x, gridDim.x), blockIdx.y, lds);
+  site_pairs_block<T, 3>(pa, xcd_block(blockIdx.x, gridDim.x), blockIdx.y, lds);
 }
 
 // The site-electrode sums of many frames beside k_site_pairs_n3 (~20 KB of
@@ -62,8 +62,9 @@ __global__ __launch_bounds__(TILE_THREADS, sizeof(T) == 8 ? 4 : 6) void k_site_e
 }
 
 // The site-site sums of many frames with every pair once (no periodic
-// images): ~25 KB of LDS in FP64; four workgroups per CU in FP64 (a fifth
-// would spill registers in the pair loop), six in FP32.
+// images): ~27 KB of LDS in FP64; four workgroups per CU in FP64 (a fifth
+// spills 28 registers in the pair loop: 4096 frames x 32 potentials 14.77 ms
+// against 14.48), six in FP32.
 template <typename T, bool ZS>
 __global__ __launch_bounds__(TILE_THREADS, sizeof(T) == 8 ? 4 : 6) void k_site_pairs_n3(PairArgs<T> pa) {
   extern __shared__ __align__(16) unsigned char lds[];

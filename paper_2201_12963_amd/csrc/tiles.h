@@ -925,26 +925,27 @@ __device__ __forceinline__ void tile_item(int b, int tsplit, int grp, const int*
   t_hi = lo + (int)(((long long)n * (s + 1)) / tsplit);
 }
 
-// workgroup b of a frame's site-pair work: with tsplit > 0, share b mod
-// tsplit of the sites of item b / tsplit (tiles; MODE 1: the site-electrode
-// sums alone, MODE 2: the site-site sums with every pair once; ZS: z images
-// fixed at staging, PairArgs::zshift); with tsplit == 0, sites 4b .. 4b+3
-// (one wavefront each)
-template <typename T, int MODE = 0, bool ZS = false>
+// workgroup b of a frame's site-pair work.  MODE 0: sites 4b .. 4b+3, one
+// wavefront each (tsplit == 0).  Tiles (tsplit > 0), share b mod tsplit of the
+// sites of item b / tsplit: MODE 1 the site-electrode sums alone, MODE 2 the
+// site-site sums with every pair once (ZS: z images fixed at staging,
+// PairArgs::zshift), MODE 3 both with periodic images.  (A kernel holds one
+// form: with the wavefront walk beside them the tiles spilled 26 to 242
+// registers.)
+template <typename T, int MODE, bool ZS = false>
 __device__ __forceinline__ void site_pairs_block(const PairArgs<T>& pa, int b, int frame, unsigned char* lds) {
-  if (pa.tsplit == 0) {
-    // one wavefront per site, four per workgroup
+  if constexpr (MODE == 0) {
     const int j = b * (TILE_THREADS / WAVE) + (threadIdx.x >> 6);
     if (j < pa.st.n)
       site_pairs_wave(pa.cell, pa.st, pa.alpha, pa.rc2, pa.f_pair, pa.u_site, j, frame,
                       reinterpret_cast<T*>(lds + (threadIdx.x >> 6) * wave_scratch_bytes<T>()));
-    return;
+  } else {
+    int c, t_lo, t_hi;
+    tile_item(b, pa.tsplit, pa.grp, pa.st.cell_start + (size_t)frame * (pa.cell.n_cells + 1), c, t_lo, t_hi);
+    if constexpr (MODE == 2) site_pairs_n3_tile<T, ZS>(pa, c, t_lo, t_hi, frame, lds);
+    else if constexpr (MODE == 1) site_elec_tile<T, ZS>(pa, c, t_lo, t_hi, frame, lds);
+    else site_pairs_tile(pa, c, t_lo, t_hi, frame, lds);
   }
-  int c, t_lo, t_hi;
-  tile_item(b, pa.tsplit, pa.grp, pa.st.cell_start + (size_t)frame * (pa.cell.n_cells + 1), c, t_lo, t_hi);
-  if (MODE == 2) site_pairs_n3_tile<T, ZS>(pa, c, t_lo, t_hi, frame, lds);
-  else if (MODE == 1) site_elec_tile<T, ZS>(pa, c, t_lo, t_hi, frame, lds);
-  else site_pairs_tile(pa, c, t_lo, t_hi, frame, lds);
 }
 
 }  // namespace cpm
