@@ -773,10 +773,14 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
     // wavefront), which all threads then work through, so that the 16
     // wavefronts share the scan and full wavefronts the weights and atomics
     // (four wavefronts with a list each: the launch 17.9 us at 5120 sites on
-    // 36 x 36 planes, 14.4 like this)
-    __shared__ int n_hit;
-    for (int base = 0; base < n; base += SPREAD_LIST) {
-      if (threadIdx.x == 0) n_hit = 0;
+    // 36 x 36 planes, 14.4 like this).  The counters of the even and odd rounds
+    // alternate: a round's is cleared between the two barriers of the round
+    // before it, where no wavefront reads or adds to it any more (one counter
+    // cleared at the top of a round could take the count from wavefronts still
+    // at the list of the last one).
+    __shared__ int n_hit[2];
+    if (threadIdx.x == 0) n_hit[0] = 0;
+    for (int base = 0, odd = 0; base < n; base += SPREAD_LIST, odd ^= 1) {
       double zv[SB];
 #pragma unroll
       for (int u = 0; u < SB; ++u) {
@@ -784,6 +788,7 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
         zv[u] = j < n ? sz[j] : 0.0;
       }
       __syncthreads();                                     // counter cleared, earlier list worked through
+      if (threadIdx.x == 0) n_hit[odd ^ 1] = 0;
       int ent[SB];
       unsigned long long hits[SB];
       int cnt = 0;
@@ -798,7 +803,7 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
       }
       int at = 0;
       if (cnt > 0) {
-        if (lane == 0) at = atomicAdd(&n_hit, cnt);
+        if (lane == 0) at = atomicAdd(&n_hit[odd], cnt);
         at = __builtin_amdgcn_readfirstlane(at);
       }
 #pragma unroll
@@ -807,7 +812,8 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
         at += __popcll(hits[u]);
       }
       __syncthreads();
-      for (int e = threadIdx.x; e < n_hit; e += NT) add_site(list[e]);
+      const int nh = n_hit[odd];
+      for (int e = threadIdx.x; e < nh; e += NT) add_site(list[e]);
     }
   } else {
     // many frames: a list per wavefront, which needs no workgroup barrier

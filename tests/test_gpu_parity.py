@@ -143,6 +143,30 @@ def test_step_parity_sites_crowded_into_one_layer(torch_dev):
     check_step(torch_dev, wc, A, S)
 
 
+def test_step_parity_sites_crowded_over_several_staging_rounds(torch_dev):
+    """10000 sites in a 0.2 nm slab.  The one-frame spread stages 4096 sites at
+    a time into one list per plane that 1024 threads work through; here each
+    of its three rounds leaves the planes beside the slab more entries than
+    threads, so that some wavefronts are still at the list of one round when
+    others reach the next.  A round's count must be the one its
+    wavefronts made: lost entries are charge missing from the mesh."""
+    import dataclasses
+    _say("[gpu] step paper ff, 10000 sites crowded into one slab")
+    w, A, S = built("paper", "ff")
+    n = 10000
+    rng = np.random.default_rng(12)
+    x = rng.uniform(0.0, 1.0, (3, n)) * w.box[:, None]
+    x[2] = rng.uniform(6.2, 6.4, n)
+    wc = dataclasses.replace(w, site_xyz=x, site_q=np.tile([0.5, -0.5], n // 2))
+    u = x[2] / (w.box[2] / w.mesh[2])
+    first = (np.floor(u - w.order / 2.0).astype(int) + 1) % w.mesh[2]
+    hits = np.zeros((w.mesh[2], (n + 4095) // 4096), int)
+    for t in range(w.order):
+        np.add.at(hits, ((first + t) % w.mesh[2], np.arange(n) // 4096), 1)
+    assert hits.shape[1] == 3 and (hits.max(axis=0) > 1024).all()
+    check_step(torch_dev, wc, A, S)
+
+
 @pytest.mark.parametrize("kz", [600, 2048])
 def test_step_parity_long_z_columns(torch_dev, kz):
     """Meshes with more points along z than the z pass prefetches per lane
