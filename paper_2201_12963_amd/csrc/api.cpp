@@ -611,6 +611,10 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
   rb.item_c = c->d_item_c;
   rb.item_lo = c->d_item_lo;
   rb.item_hi = c->d_item_hi;
+  // (timed alone, the launches that begin, finish or make b work on scratch,
+  // so that b stays the last step's)
+  RealBArgs<T> rb_timed = rb;
+  rb_timed.b_out = gather ? c->d_g : nullptr;
   if (c->kspace == CPM_KSPACE_PPPM) {
     // (the real charge mesh is kept for inspection after one frame only)
     rec(c, CPM_KERNEL_FFT_XY_FWD, s, [=](hipStream_t s) {
@@ -625,13 +629,15 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
     // no potential pass, the field pass folds the two spectra
     c->fold_pot = !need_b && nf == 1 && c->elec_mode != 0 && c->d_c1e && std::is_same<T, double>::value;
     if (!c->fold_pot) {
-      rec(c, CPM_KERNEL_FFT_Z_POT, s, [=](hipStream_t s) {
+      auto z_pot = [=](hipStream_t s, const RealBArgs<T>& r) {
         // (many frames: the result only on the planes the electrode stencils read)
         launch_fft_z_t<T, T2>(s, nf, c->pz, c->za_pot, B::G(c), B::c1(c), nullptr,
                               forces ? B::save(c) : nullptr, 0, c->d_ek, true,
-                              (rb.tiles || !need_b) ? nullptr : &rb, nullptr,
+                              (r.tiles || !need_b) ? nullptr : &r, nullptr,
                               nf > 1 && c->zmask_ok ? &c->zmask_e : nullptr);
-      });
+      };
+      z_pot(s, rb);
+      keep(c, CPM_KERNEL_FFT_Z_POT, [=](hipStream_t s) { z_pot(s, rb_timed); });
     }
     // forces at given charges (MD steps between charge updates): only the
     // saved site spectrum is needed, not b
@@ -640,14 +646,14 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
     if (!rb.tiles) keep(c, CPM_KERNEL_REAL_B, [=](hipStream_t s) { launch_real_b_t<T>(s, nf, rb); });
     if constexpr (!mixed) {
       if (gather) {
-        // b finished in the inverse pass (replayed on scratch: it adds to b);
-        // the gather timed alone through the stand-alone kernel
+        // b finished in the inverse pass; the gather timed alone through the
+        // stand-alone kernel
         launch_fft_xy_gather(s, c->px, c->py, c->mi.K[2], c->d_c1, c->d_phi, c->planes, c->d_b);
         keep(c, CPM_KERNEL_FFT_XY_INV, [=](hipStream_t s) {
           launch_fft_xy_gather(s, c->px, c->py, c->mi.K[2], c->d_c1, c->d_phi, c->planes, c->d_g);
         });
         keep(c, CPM_KERNEL_GATHER_B, [=](hipStream_t s) {
-          launch_gather_b_t<T>(s, nf, c->n_elec, c->P3, c->d_gidx, B::gw(c), B::phi(c), c->mi.M, B::phir(c), c->d_b,
+          launch_gather_b_t<T>(s, nf, c->n_elec, c->P3, c->d_gidx, B::gw(c), B::phi(c), c->mi.M, B::phir(c), c->d_g,
                                slab_terms(c));
         });
         return CPM_OK;

@@ -376,6 +376,31 @@ def test_graph_replay_matches_eager(torch_dev):
     ctx_g.close()
 
 
+@pytest.mark.parametrize("precision", [0, 1])
+def test_timing_one_kernel_keeps_the_last_steps_results(torch_dev, precision):
+    """Replaying a launch that begins, finishes or makes b leaves b as the last
+    step made it: the charge solve timed after it writes the same bits to the
+    caller's charges."""
+    torch = torch_dev
+    from paper_2201_12963_amd import binding
+    w, A, S = built("paper", "ff")
+    ctx, stream = gpu_context(torch, w, precision)
+    xyz = torch.tensor(w.site_xyz, dtype=torch.float64, device="cuda")
+    for name in ("real_b", "fft_z_pot", "fft_xy_inv", "gather_b"):
+        _say(f"[gpu] replay {name}, then charges, precision {precision}")
+        with torch.cuda.stream(stream):
+            q, f, e = ctx.solve(xyz, w.dv)
+        stream.synchronize()
+        q0, b0 = q.clone(), ctx.get_buffer(binding.BUF_B)
+        with torch.cuda.stream(stream):
+            ctx.replay_kernel(binding.KERNELS.index(name), 2)
+            ctx.replay_kernel(binding.KERNELS.index("charges"), 1)
+        stream.synchronize()
+        assert np.array_equal(ctx.get_buffer(binding.BUF_B), b0)
+        assert torch.equal(q, q0)
+    ctx.close()
+
+
 def test_set_matrix_restores_a_built_context(torch_dev):
     """A context given S from a host copy (checkpoint resume) steps like the one that built it.
 
