@@ -1092,6 +1092,7 @@ int tune_batch_chunk(cpm_ctx* c, int n_frames, Run run) {
 // do mixed contexts, whose FP32 and bf16 copies of S are roundings of it and
 // move by whole units in the last place where S moves by its own rounding.
 constexpr int ELAST_MIN_ATOMS = 16;
+constexpr size_t ELAST_SCRATCH = (size_t)256 << 20;      // bytes of either form's factors
 int enqueue_elastance_kspace(cpm_ctx* c, std::vector<void*>& temps) {
   const int n = c->n_elec;
   hipStream_t s = c->stream;
@@ -1119,7 +1120,7 @@ int enqueue_elastance_kspace(cpm_ctx* c, std::vector<void*>& temps) {
         kx.push_back(k0); ky.push_back(k1);
         nz.push_back(m);
       }
-    const int nk = (int)nz.size(), nkp = (nk + ELAST_SLAB - 1) / ELAST_SLAB * ELAST_SLAB, H = c->n_heights;
+    const int nk = (int)nz.size(), H = c->n_heights;
     kxy = kx;
     kxy.insert(kxy.end(), ky.begin(), ky.end());
     // the atoms height by height, each height padded to whole tiles
@@ -1133,13 +1134,21 @@ int enqueue_elastance_kspace(cpm_ctx* c, std::vector<void*>& temps) {
       }
       while (atoms.size() % ELAST_TILE) atoms.push_back(-1);
     }
+    // the x-y parts in chunks of ELAST_SCRATCH bytes, whole slabs (one slab is
+    // at most a sixteenth of A and 1280 bytes per atom)
+    const size_t per = ((size_t)H * H + 2 * atoms.size()) * sizeof(double);
+    const int slabs = (nk + ELAST_SLAB - 1) / ELAST_SLAB;
+    const int chunk = (int)std::min<size_t>(slabs, std::max<size_t>(1, ELAST_SCRATCH / (per * ELAST_SLAB))) * ELAST_SLAB;
     double *d_kxy, *d_W, *d_P;
     int *d_nz, *d_atoms, *d_th;
     TRY(up(&d_kxy, kxy)); TRY(up(&d_nz, nz)); TRY(up(&d_atoms, atoms)); TRY(up(&d_th, tile_h));
-    TRY(get(&d_W, (size_t)H * H * nkp)); TRY(get(&d_P, atoms.size() * 2 * nkp));
-    launch_elastance_kspace(s, n, (int)atoms.size(), d_atoms, d_th, H, c->d_heights, nk, nkp, d_kxy, d_nz, 2 * M_PI / c->box[2],
-                            1.0 / (4.0 * c->alpha_b * c->alpha_b), 2.0 * KE * 4.0 * M_PI / vol, c->d_ex, c->d_ey, d_W,
-                            d_P, c->d_A);
+    TRY(get(&d_W, (size_t)H * H * chunk)); TRY(get(&d_P, atoms.size() * 2 * chunk));
+    for (int c0 = 0; c0 < nk; c0 += chunk) {
+      const int nkp = std::min(chunk, slabs * ELAST_SLAB - c0);
+      launch_elastance_kspace(s, n, (int)atoms.size(), d_atoms, d_th, H, c->d_heights, c0, nk, nkp, d_kxy, d_nz,
+                              2 * M_PI / c->box[2], 1.0 / (4.0 * c->alpha_b * c->alpha_b), 2.0 * KE * 4.0 * M_PI / vol,
+                              c->d_ex, c->d_ey, d_W, d_P, c->d_A);
+    }
     return CPM_OK;
   }
   std::vector<double> kx, ky, kz;
@@ -1152,7 +1161,7 @@ int enqueue_elastance_kspace(cpm_ctx* c, std::vector<void*>& temps) {
     sk[k] = std::sqrt(2 * KE * kweight_host(k2, c->alpha_b, vol));
   }
   double *d_kv = nullptr, *d_sk = nullptr, *d_C = nullptr;
-  const int chunk = std::max(64, std::min(nk, (int)((size_t)(256u << 20) / (16 * (size_t)n))));
+  const int chunk = std::max(64, std::min(nk, (int)(ELAST_SCRATCH / (16 * (size_t)n))));
   TRY(up(&d_kv, kv)); TRY(up(&d_sk, sk)); TRY(get(&d_C, (size_t)n * 2 * chunk));
   for (int k0 = 0; k0 < nk; k0 += chunk) {
     int nkc = std::min(chunk, nk - k0);

@@ -626,13 +626,14 @@ void launch_syrk_nt(hipStream_t s, int M, int K, double alpha, const double* A, 
 // k_gemm.hip): atoms[n_list] lists the atoms height by height, each height
 // padded with -1 to whole tiles of ELAST_TILE, tile_h the height of each
 // tile; kxy[2][nk] the x-y parts of the k-vectors (the first one 0), nz their
-// largest |n_z|, nkp = nk rounded up to ELAST_SLAB; W[H][H][nkp] and
-// P[n_list][2 nkp] are scratch
+// largest |n_z|; a call takes the nkp (a multiple of ELAST_SLAB) of them from
+// c0 on, those past nk adding nothing; W[H][H][nkp] and P[n_list][2 nkp] are
+// scratch
 constexpr int ELAST_TILE = 64, ELAST_SLAB = 16;
 void launch_elastance_kspace(hipStream_t s, int n, int n_list, const int* atoms, const int* tile_h, int H,
-                             const double* heights, int nk, int nkp, const double* kxy, const int* nz, double dkz,
-                             double inv4a2, double scale, const double* ex, const double* ey, double* W, double* P,
-                             double* A);
+                             const double* heights, int c0, int nk, int nkp, const double* kxy, const int* nz,
+                             double dkz, double inv4a2, double scale, const double* ex, const double* ey, double* W,
+                             double* P, double* A);
 void launch_symmetrize(hipStream_t s, int n, double* A);
 void launch_gj_invert(hipStream_t s, int n, double* A, double* dinv, double* pc, double* rx, int* flag);
 void launch_matvec(hipStream_t s, int n, const double* Mx, const double* x, double* y);

@@ -210,17 +210,21 @@ __global__ __launch_bounds__(GS_WAVES * 64) void k_gemm_f64_small(int M, int N, 
 // the doubled paper cell (n = 1760) 2 x 36.6 k to 2 x 288, and the build's
 // k-space part from 12.4 ms of FP64 matrix products to ~0.1 ms.
 
-// W[h][h'][c]; kxy[2][nk], nz[c]: the largest |n_z| with |k| <= kcut of that
-// x-y part; entries nk .. nkp are zero.  The first x-y part is 0, whose
-// half space holds n_z > 0 only.
+// W[h][h'][c] of the x-y parts c0 .. c0 + nkp; kxy[2][nk], nz[c]: the largest
+// |n_z| with |k| <= kcut of that x-y part; entries past nk are zero.  The first
+// x-y part is 0, whose half space holds n_z > 0 only.
 // Sixteen lanes share an entry's k_z (an exp and a cos each, ~100 of them in
-// a chain cost 34 us at the doubled paper cell with one lane per entry).
-__global__ __launch_bounds__(256) void k_height_weights(int H, int nk, int nkp, const double* __restrict__ heights,
+// a chain cost 34 us at the doubled paper cell with one lane per entry).  The
+// workgroups are listed along x alone: H^2 pairs pass the grid's y limit of
+// 65535 from 256 heights on.
+__global__ __launch_bounds__(256) void k_height_weights(int H, int c0, int nk, int nkp,
+                                                        const double* __restrict__ heights,
                                                         const double* __restrict__ kxy, const int* __restrict__ nz,
                                                         double dkz, double inv4a2, double scale,
                                                         double* __restrict__ W) {
-  const int c = blockIdx.x * (blockDim.x / 16) + (threadIdx.x >> 4);     // nkp is a multiple of 16
-  const int pair = blockIdx.y;
+  const int per = nkp / 16;                              // workgroups of a pair (nkp is a multiple of 16)
+  const int pair = blockIdx.x / per;
+  const int cl = (blockIdx.x - pair * per) * 16 + (threadIdx.x >> 4), c = c0 + cl;
   double acc = 0.0, k2 = 0.0;
   if (c < nk) {
     const double dz = heights[pair / H] - heights[pair % H];
@@ -233,22 +237,22 @@ __global__ __launch_bounds__(256) void k_height_weights(int H, int nk, int nkp, 
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
   if (c > 0 && c < nk) acc = 2.0 * acc + exp(-k2 * inv4a2) / k2;
-  if ((threadIdx.x & 15) == 0) W[(size_t)pair * nkp + c] = scale * acc;
+  if ((threadIdx.x & 15) == 0) W[(size_t)pair * nkp + cl] = scale * acc;
 }
 
-// P[a][c] = cos(kxy_c . r_a), P[a][nkp + c] = sin, for the atoms listed by
-// height (atom < 0: padding, zeros)
-__global__ __launch_bounds__(256) void k_phase_xy(int nk, int nkp, const int* __restrict__ atoms,
+// P[a][c] = cos(kxy_c . r_a), P[a][nkp + c] = sin, of the same x-y parts, for
+// the atoms listed by height (atom < 0: padding, zeros)
+__global__ __launch_bounds__(256) void k_phase_xy(int c0, int nk, int nkp, const int* __restrict__ atoms,
                                                   const double* __restrict__ kxy, const double* __restrict__ ex,
                                                   const double* __restrict__ ey, double* __restrict__ P) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nkp) return;
-  const int a = atoms[blockIdx.y];
+  const int cl = blockIdx.y * blockDim.x + threadIdx.x, c = c0 + cl;
+  if (cl >= nkp) return;
+  const int a = atoms[blockIdx.x];
   double s = 0.0, co = 0.0;
   if (a >= 0 && c < nk) sincos(kxy[c] * ex[a] + kxy[nk + c] * ey[a], &s, &co);
-  double* row = P + (size_t)blockIdx.y * 2 * nkp;
-  row[c] = co;
-  row[nkp + c] = s;
+  double* row = P + (size_t)blockIdx.x * 2 * nkp;
+  row[cl] = co;
+  row[nkp + cl] = s;
 }
 
 // A[i][j] += sum_c W[h_i][h_j][c] (c_i c_j + s_i s_j) over the tiles of the
@@ -431,13 +435,13 @@ void launch_syrk_nt(hipStream_t s, int M, int K, double alpha, const double* A, 
 }
 
 void launch_elastance_kspace(hipStream_t s, int n, int n_list, const int* atoms, const int* tile_h, int H,
-                             const double* heights, int nk, int nkp, const double* kxy, const int* nz, double dkz,
-                             double inv4a2, double scale, const double* ex, const double* ey, double* W, double* P,
-                             double* A) {
+                             const double* heights, int c0, int nk, int nkp, const double* kxy, const int* nz,
+                             double dkz, double inv4a2, double scale, const double* ex, const double* ey, double* W,
+                             double* P, double* A) {
   const int t = n_list / ELAST_TILE;
-  hipLaunchKernelGGL(k_height_weights, dim3(nkp / 16, H * H), dim3(256), 0, s, H, nk, nkp, heights, kxy, nz,
-                     dkz, inv4a2, scale, W);
-  hipLaunchKernelGGL(k_phase_xy, dim3((nkp + 255) / 256, n_list), dim3(256), 0, s, nk, nkp, atoms, kxy, ex, ey, P);
+  hipLaunchKernelGGL(k_height_weights, dim3((size_t)H * H * (nkp / 16)), dim3(256), 0, s, H, c0, nk, nkp, heights, kxy,
+                     nz, dkz, inv4a2, scale, W);
+  hipLaunchKernelGGL(k_phase_xy, dim3(n_list, (nkp + 255) / 256), dim3(256), 0, s, c0, nk, nkp, atoms, kxy, ex, ey, P);
   hipLaunchKernelGGL(k_elastance_kspace, dim3(t * (t + 1) / 2), dim3(256), 0, s, n, H, nkp, atoms, tile_h, P, W, A);
 }
 

@@ -109,6 +109,32 @@ def test_elastance_atom_counts_and_heights(torch_dev, n_low, n_up, flat, geometr
     ctx.close()
 
 
+def test_elastance_of_many_heights(torch_dev):
+    """272 heights of 16 atoms: more pairs of heights than a launch's grid has
+    rows, and factors of the sum by heights that pass its scratch, so that the
+    k-vectors go through in three chunks.  Entries of A depend on the two atoms
+    alone: those of 150 atoms against the oracle's sum over these."""
+    import dataclasses
+    _say("[gpu] elastance, 272 heights")
+    w0 = workload("paper", "ff")
+    h = np.arange(136)
+    x, y = np.meshgrid(np.arange(4), np.arange(4), indexing="ij")
+    one = np.stack([(x.ravel()[None, :] + 0.25 * (h % 4)[:, None]) * 0.85,
+                    (y.ravel()[None, :] + 0.25 * (h // 4 % 4)[:, None]) * 0.85,
+                    np.repeat(0.012 * h[:, None], 16, axis=1)]).reshape(3, -1)
+    low, up = one + np.array([[0.0], [0.0], [0.5]]), one + np.array([[0.0], [0.0], [10.0]])
+    w = dataclasses.replace(w0, elec_xyz=np.ascontiguousarray(np.concatenate([low, up], axis=1)),
+                            elec_side=np.repeat(np.array([-1, 1], np.int8), low.shape[1]), kcut_exact=37.0)
+    assert np.unique(w.elec_xyz[2]).size == 272 and w.n_elec == 16 * 272
+    ctx, _ = gpu_context(torch_dev, w)
+    A = ctx.get_matrix(0)
+    ctx.close()
+    assert np.array_equal(A, A.T)
+    keep = np.sort(np.random.default_rng(3).choice(w.n_elec, 150, replace=False))
+    ref = ewald.elastance(w.elec_xyz[:, keep], w.box, w.eta, w.alpha_exact, w.rcut_exact, w.kcut_exact)
+    assert np.abs(A[np.ix_(keep, keep)] - ref).max() < TIGHT * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("name,geometry", CASES)
 def test_step_parity(torch_dev, name, geometry):
     _say(f"[gpu] step {name} {geometry}")
