@@ -140,8 +140,10 @@ def load_library():
 
 
 def _raw_stream(device_index: int) -> int:
-    """Handle of torch's current stream on a device."""
-    return torch._C._cuda_getCurrentRawStream(device_index)
+    """Handle of torch's current stream on a device: by torch's own shortcut
+    where it has one (the name is not a public one), else from the Stream."""
+    get = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return get(device_index) if get is not None else torch.cuda.current_stream(device_index).cuda_stream
 
 
 def _ptr(t: Optional[torch.Tensor]):

@@ -61,3 +61,18 @@ def test_create_rejects_bad_descriptors_without_gpu():
         with pytest.raises(binding.CpmError) as ei:
             binding.Context(**{**base, **over})
         assert ei.value.code == binding.CPM_EINVAL
+
+
+@pytest.mark.parametrize("shortcut", [True, False])
+def test_current_stream_handle_without_the_private_shortcut(monkeypatch, shortcut):
+    """The binding compares raw stream handles; a torch without the private
+    name it takes them from gives the handle of the current Stream instead."""
+    import types
+    import torch
+    from paper_2201_12963_amd import binding
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda dev=None: types.SimpleNamespace(cuda_stream=40 + dev))
+    if shortcut:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 70 + dev, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert binding._raw_stream(3) == (73 if shortcut else 43)
