@@ -106,8 +106,9 @@ int cpm_create(const cpm_desc* desc, void* hip_stream, cpm_ctx** out);
 int cpm_set_stream(cpm_ctx* ctx, void* hip_stream);
 
 /* Once per electrode geometry (Eq. 3, 8-9, 14-15; "precomputed" in
- * Sec. II.A): builds A in FP64 (Gaussian real-space pairs, k-space as
- * 2 C C^T with C the sqrt(w)-weighted cos/sin factors, self term, and in
+ * Sec. II.A): builds A in FP64 (Gaussian real-space pairs; k-space by pairs
+ * of electrode heights where few heights are shared by many atoms, else as
+ * 2 C C^T with C the sqrt(w)-weighted cos/sin factors; self term, and in
  * slab geometry the dipole correction's k_e 4 pi / V z z^T), inverts
  * it, projects S = O A^-1 (and O1 for the doubled cell) and forms S c.
  * Synchronises the stream.  CPM_ENOTSPD if A is not positive definite. */
@@ -290,7 +291,7 @@ int cpm_set_matrix(cpm_ctx* ctx, const double* host_S);
  *   CPM_BUF_FIELD_MESH double [3][Kz][Ky][Kx] field of all charges (V/nm)
  *   CPM_BUF_NCELL     int32 [3]  cells per axis
  *   CPM_BUF_BATCH_CHUNK int32 [3] the batch tuner's choices: frames per launch (0: not tuned yet),
- *                       site-pair tile workgroups per cell, x-y planes per workgroup (0: as many as fit)
+ *                       site-pair tile workgroups per item, x-y planes per workgroup (0: as many as fit)
  * The meshes are those of a cpm_solve: cpm_solve_batch does not store the
  * charge mesh, transforms the potential only on the planes the electrode
  * stencils reach and, at spline order 5, interpolates the field at the sites

@@ -90,7 +90,7 @@ struct cpm_ctx {
   double *d_g = nullptr, *d_qa = nullptr, *d_dv = nullptr;
   int cap_dv = 0;
   int batch_chunk = 0;                     // frames per batched launch chosen by the tuner (0: not yet)
-  int pair_tsplit = 1;                     // batched site-pair tiles: workgroups per cell (tuned)
+  int pair_tsplit = 1;                     // batched site-pair tiles: workgroups per item (tuned)
   int *d_fwd_n = nullptr, *d_fwd_lo = nullptr, *d_fwd_hi = nullptr;   // forward stencils (no images only)
   int pair_grp = 1;                        // cells per item of the batched pair tiles
   int *d_grun_n = nullptr, *d_grun_lo = nullptr, *d_grun_hi = nullptr;   // electrode runs per item (pair_grp > 1)
@@ -672,7 +672,7 @@ int enqueue_b(cpm_ctx* c, int nf, const double* xyz, bool forces, bool need_b = 
     // (one frame, FP64) the binning beside the structure factor, then b
     // beside the site-site sums; each timed alone through the kernel of its own
     rec(c, CPM_KERNEL_BIN, s, [=](hipStream_t s) {
-      launch_ewald_sf(s, ba, true, c->nk, c->d_kv, c->d_ew, c->d_rhok, c->d_ek);
+      launch_ewald_sf(s, ba, c->nk, c->d_kv, c->d_ew, c->d_rhok, c->d_ek);
     });
     keep(c, CPM_KERNEL_BIN, [=](hipStream_t s) { launch_bin_sites(s, ba); });
     c->pairs_made = need_b && forces;
@@ -1085,12 +1085,15 @@ int tune_batch_chunk(cpm_ctx* c, int n_frames, Run run) {
 // Two forms of the same sum.  Flat electrodes (few distinct heights) take the
 // separable one (k_gemm.hip), whose inner dimension is the x-y parts of the
 // k-vectors, ~130 times fewer than the k-vectors of the paper cells: it pays
-// while a height has ELAST_MIN_ATOMS atoms or more on average (its lists are
-// padded to 64 atoms per height, at most 4 times the atoms; the product form
-// costs more than that in every cell whose z mesh the method uses).  Other
-// electrodes take the product form, A += C C^T over chunks of k-vectors; so
-// do mixed contexts, whose FP32 and bf16 copies of S are roundings of it and
-// move by whole units in the last place where S moves by its own rounding.
+// while a height has ELAST_MIN_ATOMS atoms or more on average, since its lists
+// are padded to 64 atoms per height and its weights go with the pairs of heights
+// (a build by the product form and by heights, ms, at |k| <= 24.5 / nm: 32
+// atoms a height, n = 1728 5.8 / 2.0, 4352 29.6 / 16.1; 16 atoms, n = 864
+// 3.9 / 1.2, 1760 5.9 / 2.9, 4352 29.3 / 21.4; 8 atoms, n = 880 4.0 / 2.1,
+// 2176 7.7 / 10.0, 4352 29.6 / 42.4).  Other electrodes take the product form,
+// A += C C^T over chunks of k-vectors; so do mixed contexts, whose FP32 and
+// bf16 copies of S are roundings of it and move by whole units in the last
+// place where S moves by its own rounding.
 constexpr int ELAST_MIN_ATOMS = 16;
 constexpr size_t ELAST_SCRATCH = (size_t)256 << 20;      // bytes of either form's factors
 int enqueue_elastance_kspace(cpm_ctx* c, std::vector<void*>& temps) {
@@ -1166,7 +1169,7 @@ int enqueue_elastance_kspace(cpm_ctx* c, std::vector<void*>& temps) {
   for (int k0 = 0; k0 < nk; k0 += chunk) {
     int nkc = std::min(chunk, nk - k0);
     launch_phase_matrix(s, n, nkc, k0, nk, d_kv, d_sk, c->d_ex, c->d_ey, c->d_ez, d_C);
-    launch_syrk_nt(s, n, 2 * nkc, 1.0, d_C, 2 * nkc, 1.0, c->d_A, n);
+    launch_syrk_nt(s, n, 2 * nkc, d_C, 2 * nkc, c->d_A, n);
   }
   return CPM_OK;
 }
@@ -1196,9 +1199,12 @@ extern "C" {
 
 // One-frame steps gather b inside the inverse x-y pass while a plane holds at
 // most this many (atom, plane) entries: only the planes at the electrodes hold
-// any, so larger electrodes leave that work to a few workgroups (1760 entries
-// a plane: 10.3 us in the pass against 6.9 + 3.3 in two launches; 440: 5.9
-// against 4.6 + 2.5).
+// any, so larger electrodes leave that work to a few workgroups.  A whole solve
+// with the gather in two launches and in the pass, us: 36 x 36 planes, 440
+// entries 69.6 / 67.4, 700 71.8 / 70.7, 880 74.4 / 72.7, 1000 77.5 / 76.8,
+// 1300 82.4 / 81.7, 1760 91.4 / 90.8; three sheets on 18 x 18 planes, 960
+// entries 66.6 / 65.3, 1140 69.9 / 69.2, 1320 72.6 / 72.2.  Past the line the
+// pass gains less than 1%.
 constexpr int ELEC_PLANE_MOST = 1024;
 
 int cpm_create(const cpm_desc* d, void* hip_stream, cpm_ctx** out) {

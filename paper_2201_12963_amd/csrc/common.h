@@ -517,6 +517,9 @@ void launch_site_forces_t(hipStream_t s, int n_frames, const Cell& cell, const E
                           const SiteSet<T>& st, const ForceArgs<T>& fa, bool forces, const EnergyArgs* ea,
                           const T* epart = nullptr,
                           const LossArgs* la = nullptr);
+// the limit on the sites and cells of any context: the LDS of the counting sort
+// over all cells in one workgroup of 1024 threads (one frame sorts by z layers
+// and needs less; the limit also keeps a site index within BIN_SITE_BITS)
 size_t bin_lds_bytes(int n_site, int n_cells);
 // One workgroup: field[frame] = -kappa (zdip[frame] + z.q), q of that frame
 __device__ __forceinline__ void slab_field_block(const SlabTerms& sl, const double* q, double* field, int frame) {
@@ -577,26 +580,26 @@ size_t fft_xy_lds_bytes(int Kx, int Ky, int elt_bytes, int planes);
 // threads of the spread + x-y transform workgroups (which also run the
 // binning): many-frame launches SPREAD_THREADS (256 measured faster than
 // 512 there: 3.7 -> 2.5 ms per 4096 frames), one-frame launches
-// SPREAD_THREADS_ONE (four wavefronts per SIMD for the binning workgroup,
-// which is then on the step's critical path); the planes' staging is done
-// by the first SPREAD_THREADS threads in either case
+// SPREAD_THREADS_ONE (16 wavefronts for the latency of a plane's scan and list
+// and of the binning, all on the step's critical path)
 constexpr int SPREAD_THREADS = 256;
 constexpr int SPREAD_THREADS_ONE = 1024;
-// sites per thread whose z is read together by the spread's staging (the
-// per-wavefront lists hold SPREAD_LIST / 64 entries per wavefront, SPREAD_LIST
-// entries per workgroup in either configuration)
+// sites staged in a round of the spread: their z are read together, and the
+// list holds as many entries (one list for a one-frame workgroup, an equal
+// share per wavefront in the many-frame form)
 constexpr int SPREAD_LIST = 4096;
-// LDS of such a workgroup running the binning body
+// the limit on the sites and cells of a mesh context: the binning body's LDS
+// in either width (one-frame launches split it by z layers and need less)
 size_t bin_lds_spread(int n_site, int n_cells);
 template <typename T, typename T2>
 void launch_fft_xy_spread_t(hipStream_t s, int n_frames, const FFTPlan1D& px, const FFTPlan1D& py, int Kz,
                             const MeshInfo& mi, const BinArgs& ba, T* rho_out, T2* out_c, bool planes = true,
                             bool bin = false);
 
-// explicit Ewald (k_ewald.hip), one frame: the structure factor and (bin) the
+// explicit Ewald (k_ewald.hip), one frame: the structure factor and the
 // binning of the same positions; b and (pa) the site-site sums
-void launch_ewald_sf(hipStream_t s, const BinArgs& ba, bool bin, int nk, const double* kv, const double* ew,
-                     double2* rho, double* ek);
+void launch_ewald_sf(hipStream_t s, const BinArgs& ba, int nk, const double* kv, const double* ew, double2* rho,
+                     double* ek);
 void launch_ewald_b(hipStream_t s, int nk, const double* ew, const double2* eph, const double2* rho,
                     const RealBArgs<double>& rb, double* b, const SlabTerms& sl, const PairArgs<double>* pa);
 void launch_ewald_rho_all(hipStream_t s, int nk, int n_elec, const double2* eph, const double* q, const double2* rho,
@@ -619,9 +622,8 @@ void launch_phase_matrix(hipStream_t s, int n, int nkc, int k0, int nk, const do
 // D[M][N] = A[M][K] B[N][K]^T
 void launch_gemm_nt(hipStream_t s, int M, int N, int K, const double* A, int lda, const double* B, int ldb, double* D,
                     int ldd);
-// D = beta D + alpha A A^T (D square), only half of the products formed
-void launch_syrk_nt(hipStream_t s, int M, int K, double alpha, const double* A, int lda, double beta, double* D,
-                    int ldd);
+// D += A A^T (D square), only half of the products formed
+void launch_syrk_nt(hipStream_t s, int M, int K, const double* A, int lda, double* D, int ldd);
 // k-space part of A for atoms of H distinct heights, added to A (see
 // k_gemm.hip): atoms[n_list] lists the atoms height by height, each height
 // padded with -1 to whole tiles of ELAST_TILE, tile_h the height of each

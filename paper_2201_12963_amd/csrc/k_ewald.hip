@@ -118,10 +118,10 @@ __global__ __launch_bounds__(256) void k_ewald_rho_all(int nk, int n_elec, const
   if (lane == 0) out[k] = double2{r.x + re, r.y + im};
 }
 
-void launch_ewald_sf(hipStream_t s, const BinArgs& ba, bool bin, int nk, const double* kv, const double* ew,
-                     double2* rho, double* ek) {
-  const int nb = bin ? bin_layer_wgs(ba.cell) : 0, per = EWALD_SF_THREADS / WAVE;
-  const size_t lds = bin ? bin_layers_lds<EWALD_SF_THREADS>(ba.n_site, ba.cell) : 0;
+void launch_ewald_sf(hipStream_t s, const BinArgs& ba, int nk, const double* kv, const double* ew, double2* rho,
+                     double* ek) {
+  const int nb = bin_layer_wgs(ba.cell), per = EWALD_SF_THREADS / WAVE;
+  const size_t lds = bin_layers_lds<EWALD_SF_THREADS>(ba.n_site, ba.cell);
   hipLaunchKernelGGL(k_ewald_sf, dim3(nb + (nk + per - 1) / per), dim3(EWALD_SF_THREADS), lds, s, ba, nb, nk, kv, ew,
                      rho, ek);
 }

@@ -642,16 +642,16 @@ __global__ __launch_bounds__(XY_THREADS) void k_fft_xy_gather(FFTPlan1D px, FFTP
 
 // Forward x-y transform of one z-plane of the electrolyte charge mesh, whose
 // real values are first assembled in LDS.  The plane's workgroup scans every
-// site (wrapped into the box as the binning does), stages those whose
-// B-spline stencil reaches the plane in per-wavefront lists, and each staged
-// site adds its P x P in-plane contributions with LDS atomics, its weights
-// computed on the spot.  The scan needs no cell list, so the binning of the
-// same frame runs as one more workgroup of this launch (index n_planes on;
-// one frame: several, by z layers).
+// site (wrapped into the box as the binning does), lists those whose B-spline
+// stencil reaches the plane (one list for a one-frame workgroup, a list per
+// wavefront in the many-frame form), and each listed site adds its P x P
+// in-plane contributions with LDS atomics, its weights computed on the spot.
+// The scan needs no cell list, so the binning of the same frame runs as one
+// more workgroup of this launch (index n_planes on; one frame: several, by z
+// layers).
 // The assembled plane is also written to rho_out (the charge mesh, for
 // inspection), then transformed as in k_fft_xy.  ONE: a one-frame launch
-// (1024 threads; the binning keeps its sites in registers, the planes use
-// the direct sum).  P5: B-splines of order 5 (else any other order).  SPL:
+// (1024 threads; the planes use the direct sum).  P5: B-splines of order 5 (else any other order).  SPL:
 // consecutive planes per workgroup (many frames), which share the scan of
 // the sites and every staged site's weights; n_planes counts the workgroups
 // of planes.
@@ -678,7 +678,7 @@ __global__ __launch_bounds__(ONE ? SPREAD_THREADS_ONE : SPREAD_THREADS) void k_f
   // the real planes accumulate in FP64 in every precision (FP32 LDS atomics
   // measured slower than FP64 ones: 6.6 against 3.5 ms for a 4096-frame spread)
   double* acc = reinterpret_cast<double*>(twy + Ky);       // SPL * NP values
-  int* list = reinterpret_cast<int*>(acc + SPL * NP);      // staged (site, z slot) entries, or sites (SPL > 1)
+  int* list = reinterpret_cast<int*>(acc + SPL * NP);      // listed (site, z slot) entries, or sites (SPL > 1)
   load_twiddles(px, twx);
   load_twiddles(py, twy);
   const int iz = blockIdx.x * SPL;                         // first plane of the workgroup
@@ -903,7 +903,8 @@ __device__ __forceinline__ void fft_z_body(const FFTPlan1D& pz, const ZPassArgs&
     T* qbuf = reinterpret_cast<T*>(smem + (threadIdx.x >> 6) * wave_scratch_bytes<T>());
     if (hb < rb.n_blocks) {
       const int g = xcd_block(hb, rb.n_blocks) * (blockDim.x / WAVE) + (threadIdx.x >> 6);
-      if (g < rb.el.n) real_b_wave(rb.cell, rb.alpha, rb.eta, rb.rc2, rb.el, rb.st, rb.phi_out, g, blockIdx.y, qbuf, nullptr, rb.b_out, &rb.sl);
+      if (g < rb.el.n)
+        real_b_wave(rb.cell, rb.alpha, rb.eta, rb.rc2, rb.el, rb.st, rb.phi_out, g, blockIdx.y, qbuf, rb.b_out, &rb.sl);
     } else if (LJ && hb >= rb.n_blocks + pa.n_blocks) {
       lj_site(*lj, hb - rb.n_blocks - pa.n_blocks);
     } else {

@@ -41,13 +41,13 @@ __device__ __forceinline__ void tri_tile(int t, int& row, int& col) {
   col = t - row * (row + 1) / 2;
 }
 
-// SYM: A and B are the same matrix, so D's product part is symmetric: only
-// the tiles of the lower triangle are computed (blockIdx.x lists them) and
-// each is added at both places, half the matrix work.
+// D = A B^T.  SYM: A and B are the same matrix, D += A A^T, whose product part
+// is symmetric: only the tiles of the lower triangle are computed (blockIdx.x
+// lists them) and each is added at both places, half the matrix work.
 template <bool SYM>
-__global__ __launch_bounds__(256) void k_gemm_f64_mfma(int M, int N, int K, double alpha, const double* __restrict__ A,
-                                                       int lda, const double* __restrict__ B, int ldb, double beta,
-                                                       double* __restrict__ D, int ldd) {
+__global__ __launch_bounds__(256) void k_gemm_f64_mfma(int M, int N, int K, const double* __restrict__ A, int lda,
+                                                       const double* __restrict__ B, int ldb, double* __restrict__ D,
+                                                       int ldd) {
   __shared__ double sA[2][G64_TILE * G64_LD], sB[2][G64_TILE * G64_LD];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int tm = blockIdx.y, tn = blockIdx.x;
@@ -130,10 +130,10 @@ __global__ __launch_bounds__(256) void k_gemm_f64_mfma(int M, int N, int K, doub
         const int gm = m0 + wm + 16 * a + 4 * t + kq, gn = n0 + wn + 16 * b + r;
         if (gm < M && gn < N) {
           double* d = D + (size_t)gm * ldd + gn;
-          *d = (beta == 0.0 ? 0.0 : beta * *d) + alpha * acc[a][b][t];
+          *d = (SYM ? *d : 0.0) + acc[a][b][t];
           if (SYM && tm != tn) {
             d = D + (size_t)gn * ldd + gm;
-            *d = (beta == 0.0 ? 0.0 : beta * *d) + alpha * acc[a][b][t];
+            *d += acc[a][b][t];
           }
         }
       }
@@ -423,15 +423,14 @@ void launch_gemm_nt(hipStream_t s, int M, int N, int K, const double* A, int lda
     hipLaunchKernelGGL(k_gemm_f64_small, dim3((N + GS_TILE - 1) / GS_TILE, (M + GS_TILE - 1) / GS_TILE),
                        dim3(GS_WAVES * 64), 0, s, M, N, K, A, lda, B, ldb, D, ldd);
   else
-    hipLaunchKernelGGL(k_gemm_f64_mfma<false>, grid, dim3(256), 0, s, M, N, K, 1.0, A, lda, B, ldb, 0.0, D, ldd);
+    hipLaunchKernelGGL(k_gemm_f64_mfma<false>, grid, dim3(256), 0, s, M, N, K, A, lda, B, ldb, D, ldd);
 }
 
-void launch_syrk_nt(hipStream_t s, int M, int K, double alpha, const double* A, int lda, double beta, double* D,
-                    int ldd) {
+void launch_syrk_nt(hipStream_t s, int M, int K, const double* A, int lda, double* D, int ldd) {
   if (M <= 0) return;
   const int t = (M + G64_TILE - 1) / G64_TILE;
-  hipLaunchKernelGGL(k_gemm_f64_mfma<true>, dim3(t * (t + 1) / 2), dim3(256), 0, s, M, M, K, alpha, A, lda, A, lda,
-                     beta, D, ldd);
+  hipLaunchKernelGGL(k_gemm_f64_mfma<true>, dim3(t * (t + 1) / 2), dim3(256), 0, s, M, M, K, A, lda, A, lda, D,
+                     ldd);
 }
 
 void launch_elastance_kspace(hipStream_t s, int n, int n_list, const int* atoms, const int* tile_h, int H,

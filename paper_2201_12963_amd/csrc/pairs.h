@@ -21,9 +21,9 @@
 
 namespace cpm {
 
-// 1/d for d >= 1: the hardware reciprocal estimate refined by two Newton
-// steps y <- y + y (1 - d y) (each squares the relative error, so the
-// estimate's ~1e-7 falls below FP64 rounding)
+// 1/d for d whose reciprocal is a normal number: the hardware reciprocal
+// estimate refined by two Newton steps y <- y + y (1 - d y) (each squares the
+// relative error, so the estimate's ~1e-7 falls below FP64 rounding)
 __device__ __forceinline__ double recip_nr(double d) {
   double y = __builtin_amdgcn_rcp(d);
   y = fma(y, fma(-d, y, 1.0), y);
@@ -349,12 +349,11 @@ __device__ __forceinline__ T g1_potential(T dx, T dy, T dz, T q, T alpha, T eta)
 // Real-space electrolyte potential at electrode atom g of a frame, one
 // wavefront: k_e sum_j Q_j g1(r) over the sites of the stencil cells.
 // scratch: this wavefront's LDS (wave_scratch_bytes<T>()).  Returns the value
-// (every lane) and the atom's original index.
+// (every lane).
 template <typename T>
 __device__ __forceinline__ T real_b_wave(const Cell& cell, T alpha, T eta, double rc2, const ElecSet<T>& el,
                                          const SiteSet<T>& st, T* __restrict__ phi_out, int g, int frame,
-                                         T* scratch, int* orig = nullptr, double* b_out = nullptr,
-                                         const SlabTerms* sl = nullptr) {
+                                         T* scratch, double* b_out = nullptr, const SlabTerms* sl = nullptr) {
   const int lane = threadIdx.x & (WAVE - 1);
   const size_t fo = (size_t)frame * st.n;
   const double* sx = st.x + fo; const double* sy = st.y + fo; const double* sz = st.z + fo;
@@ -393,7 +392,6 @@ __device__ __forceinline__ T real_b_wave(const Cell& cell, T alpha, T eta, doubl
     phi_out[(size_t)frame * el.n + og] = (T)KE * acc;
     if (b_out) b_out[og] = -(double)((T)KE * acc) - slab_b_term(*sl, og, 0);
   }
-  if (orig) *orig = og;
   return (T)KE * acc;
 }
 
